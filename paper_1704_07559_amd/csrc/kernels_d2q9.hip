@@ -436,38 +436,44 @@ __global__ __launch_bounds__(kMaxBlock) void set_kernel(Geo G, S* buf, const flo
   scatter_rows<Lat, S>(buf, G, nb.rows, y, g);
 }
 
-template <typename S>
-__global__ __launch_bounds__(256) void reduce_kernel(Geo G, ModelF M, ViscF V, ForceF Fo, const S* buf,
+template <typename S, bool CORR, bool IMPLICIT>
+__global__ __launch_bounds__(256) void reduce_kernel(Geo G, ModelF M, ViscF V, ForceF Fo, NodeWalk W, const S* buf,
                                                      const float* snu_f, double* partials) {
   double acc[kReduceVals] = {0, 0, 0, 0, 0, 0, 0, 0};
-  // blocks take whole x-rows in turn; the threads of a block walk along the row
-  for (int y = blockIdx.x; y < G.ny; y += gridDim.x) {
-    for (int x = threadIdx.x; x < G.nx; x += blockDim.x) {
-      const Node<Q, S> nb = node_at<Q, S>(G, x, y, 0);
-      float g[Q];
-      pull_rows<Lat, S>(buf, G, nb.rows, y, g);
+  const double per_jj = 0.5 / M.rho0;
+  for (unsigned self = blockIdx.x * 256 + threadIdx.x; self < G.N; self += gridDim.x * 256) {
+    const Coord c = coord_of(G, W, self);
+    // (loaded ahead of the populations: behind them its latency would stand alone)
+    float snu = (!IMPLICIT && snu_f) ? snu_f[self] : M.s[7];
+    float g[Q];
+    pull_rows<Lat, S, true, false>(buf, G, rows_of<Q, S>(G, c.x, c.y, c.z), c.y, g);
+    const Pairs P = make_pairs(g);
+    const float drho = delta_rho(P);
+    // (their sum is non-finite where a population is, so that finite nodes pay one test)
+    if (!isfinite(drho)) {
       int bad = 0;
 #pragma unroll
       for (int i = 0; i < Q; ++i) bad += !isfinite(g[i]);
-      const Pairs P = make_pairs(g);
-      const float drho = delta_rho(P);
-      float Fx, Fy;
-      load_force(Fo, G.N, nb.self, Fx, Fy);
-      const float jx = momentum<0>(P) + 0.5f * Fx, jy = momentum<1>(P) + 0.5f * Fy;
-      const Neq n = noneq_moments(P, drho, jx, jy, M.inv_rho0);
-      float S3[3];
-      const StrainIn<true> si = strain_in_state(n, jx, jy, Fx, Fy, M, Fo);
-      strain_yu(si.ns, M.s[1], query_rate(P, drho, jx, jy, si, M, V, snu_f, nb.self), M.inv_rho0, S3);
-      const double jj = static_cast<double>(jx) * jx + static_cast<double>(jy) * jy;
-      acc[0] += drho;
-      acc[1] += jx;
-      acc[2] += jy;
-      acc[4] += jj * (0.5 / M.rho0);
-      acc[5] += static_cast<double>(S3[0]) * S3[0] + static_cast<double>(S3[1]) * S3[1] +
-                2.0 * static_cast<double>(S3[2]) * S3[2];
-      acc[6] = fmax(acc[6], jj);  // max |j|^2: the final pass takes sqrt(.) / rho0 once
       acc[7] += bad;
     }
+    float Fx, Fy;
+    load_force(Fo, G.N, self, Fx, Fy);
+    const float jx = momentum<0>(P) + 0.5f * Fx, jy = momentum<1>(P) + 0.5f * Fy;
+    const Neq n = noneq_moments(P, drho, jx, jy, M.inv_rho0);
+    float SF[Q];
+    if constexpr (CORR) force_moments(jx, jy, Fx, Fy, M.inv_rho0, SF);
+    const StrainIn<CORR> si = strain_in<CORR>(n, SF);
+    if constexpr (IMPLICIT) snu = implicit_rate(P, drho, jx, jy, si, M, V);
+    float S3[3];
+    strain_yu(si.ns, M.s[1], snu, M.inv_rho0, S3);
+    const double jj = static_cast<double>(jx) * jx + static_cast<double>(jy) * jy;
+    acc[0] += drho;
+    acc[1] += jx;
+    acc[2] += jy;
+    acc[4] += jj * per_jj;
+    acc[5] += static_cast<double>(S3[0]) * S3[0] + static_cast<double>(S3[1]) * S3[1] +
+              2.0 * static_cast<double>(S3[2]) * S3[2];
+    acc[6] = fmax(acc[6], jj);  // max |j|^2: the final pass takes sqrt(.) / rho0 once
   }
   block_reduce_store(acc, partials);
 }
@@ -603,14 +609,29 @@ hipError_t launch_set(int storage, const Geo& G, void* buf, const float* canon, 
   return hipGetLastError();
 }
 
+// The force-corrected strain and the implicit rate are instances of their own: their code costs
+// the plain diagnostics 10 VGPRs and a tenth of its instructions.
+template <typename S>
+static void launch_reduce_t(unsigned nb, hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V,
+                            const ForceF& Fo, const S* buf, const float* snu, double* partials) {
+  constexpr size_t cap = 0;
+  decltype(&reduce_kernel<S, false, false>) f;
+  switch ((Fo.strain_corr ? 1 : 0) + (V.kind == 3 ? 2 : 0)) {
+    case 0: f = reduce_kernel<S, false, false>; break;
+    case 1: f = reduce_kernel<S, true, false>; break;
+    case 2: f = reduce_kernel<S, false, true>; break;
+    default: f = reduce_kernel<S, true, true>; break;
+  }
+  hipLaunchKernelGGL(f, dim3(nb), dim3(256), cap, st, G, M, V, Fo, node_walk(G), buf, snu, partials);
+}
+
 hipError_t launch_reduce(int storage, const Geo& G, const ModelF& M, const ViscF& V, const ForceF& Fo,
                          const void* buf, const float* snu, double* partials, double* out, hipStream_t st) {
-  unsigned nb = static_cast<unsigned>(G.ny);  // one x-row per block at a time
-  if (nb > static_cast<unsigned>(kReduceBlocks)) nb = kReduceBlocks;
+  const unsigned nb = reduce_blocks(G);
   switch (storage) {
-    case 0: hipLaunchKernelGGL(reduce_kernel<float>, dim3(nb), dim3(256), 0, st, G, M, V, Fo, cb<float>(buf), snu, partials); break;
-    case 1: hipLaunchKernelGGL(reduce_kernel<_Float16>, dim3(nb), dim3(256), 0, st, G, M, V, Fo, cb<_Float16>(buf), snu, partials); break;
-    case 2: hipLaunchKernelGGL(reduce_kernel<__bf16>, dim3(nb), dim3(256), 0, st, G, M, V, Fo, cb<__bf16>(buf), snu, partials); break;
+    case 0: launch_reduce_t<float>(nb, st, G, M, V, Fo, cb<float>(buf), snu, partials); break;
+    case 1: launch_reduce_t<_Float16>(nb, st, G, M, V, Fo, cb<_Float16>(buf), snu, partials); break;
+    case 2: launch_reduce_t<__bf16>(nb, st, G, M, V, Fo, cb<__bf16>(buf), snu, partials); break;
     default: return hipErrorInvalidValue;
   }
   hipError_t e = hipGetLastError();

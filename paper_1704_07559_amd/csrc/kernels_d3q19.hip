@@ -120,48 +120,52 @@ __global__ __launch_bounds__(kMaxBlock) void set_kernel(Geo G, S* buf, const flo
 // ------------------------------------------------------------------------------------------
 // Diagnostics: mass, momentum, kinetic energy, sum S:S (Yu), max |u|, non-finite count
 // ------------------------------------------------------------------------------------------
-template <typename S>
-__global__ __launch_bounds__(256) void reduce_kernel(Geo G, ModelF M, ViscF V, ForceF Fo, const S* buf,
+// Bound by HBM in FP32 (256^3: 0.222 ms = 6.05 TB/s, 0.231 with whole rows per block; 128^3 35 us
+// against 56) and by instruction issue with 16-bit storage (256^3 FP16 0.150 ms against 0.169).
+template <typename S, bool CORR, bool IMPLICIT>
+__global__ __launch_bounds__(256) void reduce_kernel(Geo G, ModelF M, ViscF V, ForceF Fo, NodeWalk W, const S* buf,
                                                      const float* snu_f, double* partials) {
   double acc[kReduceVals] = {0, 0, 0, 0, 0, 0, 0, 0};
-  // blocks take whole x-rows in turn; the threads of a block walk along the row
-  const unsigned rows = static_cast<unsigned>(G.ny) * G.nz;
-  for (unsigned r = blockIdx.x; r < rows; r += gridDim.x) {
-    const int y = r % G.ny;
-    const int z = r / G.ny;
-    for (int x = threadIdx.x; x < G.nx; x += blockDim.x) {
-      const Node<Q, S> nb = node_at<Q, S>(G, x, y, z);
-      float g[Q];
-      pull_rows<Lat, S>(buf, G, nb.rows, y, g);
+  const double per_jj = 0.5 / M.rho0;
+  for (unsigned self = blockIdx.x * 256 + threadIdx.x; self < G.N; self += gridDim.x * 256) {
+    const Coord c = coord_of(G, W, self);
+    // (loaded ahead of the populations: behind them its latency would stand alone)
+    float snu = (!IMPLICIT && snu_f) ? snu_f[self] : M.s[9];
+    float g[Q];
+    pull_rows<Lat, S, true, false>(buf, G, rows_of<Q, S>(G, c.x, c.y, c.z), c.y, g);
+    const Pairs P = make_pairs(g);
+    const float drho = delta_rho(P);
+    // (their sum is non-finite where a population is, so that finite nodes pay one test)
+    if (!isfinite(drho)) {
       int bad = 0;
 #pragma unroll
       for (int i = 0; i < Q; ++i) bad += !isfinite(g[i]);
-      const Pairs P = make_pairs(g);
-      const float drho = delta_rho(P);
-      float jx = momentum<0>(P), jy = momentum<1>(P), jz = momentum<2>(P);
-      float Fx, Fy, Fz;
-      load_force(Fo, G.N, nb.self, Fx, Fy, Fz);
-      jx += 0.5f * Fx;
-      jy += 0.5f * Fy;
-      jz += 0.5f * Fz;
-      const Neq n = noneq_moments(P, drho, jx, jy, jz, M);
-      const StrainIn<true> si = strain_in_state(n, jx, jy, jz, Fx, Fy, Fz, M, Fo);
-      const float snu = V.kind == 3 ? implicit_rate(P, drho, jx, jy, jz, si, M, V) : (snu_f ? snu_f[nb.self] : M.s[9]);
-      float S6[6];
-      strain_yu(si.ns, M.s[1], snu, M.inv_rho0, S6);
-      const double jj = static_cast<double>(jx) * jx + static_cast<double>(jy) * jy + static_cast<double>(jz) * jz;
-      acc[0] += drho;
-      acc[1] += jx;
-      acc[2] += jy;
-      acc[3] += jz;
-      acc[4] += jj * (0.5 / M.rho0);
-      double ss = 0.0;
-#pragma unroll
-      for (int c = 0; c < 6; ++c) ss += (c < 3 ? 1.0 : 2.0) * static_cast<double>(S6[c]) * S6[c];
-      acc[5] += ss;
-      acc[6] = fmax(acc[6], jj);  // max |j|^2: the final pass takes sqrt(.) / rho0 once
       acc[7] += bad;
     }
+    float jx = momentum<0>(P), jy = momentum<1>(P), jz = momentum<2>(P);
+    float Fx, Fy, Fz;
+    load_force(Fo, G.N, self, Fx, Fy, Fz);
+    jx += 0.5f * Fx;
+    jy += 0.5f * Fy;
+    jz += 0.5f * Fz;
+    const Neq n = noneq_moments(P, drho, jx, jy, jz, M);
+    float SF[Q];
+    if constexpr (CORR) force_moments(jx, jy, jz, Fx, Fy, Fz, M.inv_rho0, SF);
+    const StrainIn<CORR> si = strain_in<CORR>(n, SF);
+    if constexpr (IMPLICIT) snu = implicit_rate(P, drho, jx, jy, jz, si, M, V);
+    float S6[6];
+    strain_yu(si.ns, M.s[1], snu, M.inv_rho0, S6);
+    const double jj = static_cast<double>(jx) * jx + static_cast<double>(jy) * jy + static_cast<double>(jz) * jz;
+    acc[0] += drho;
+    acc[1] += jx;
+    acc[2] += jy;
+    acc[3] += jz;
+    acc[4] += jj * per_jj;
+    double ss = 0.0;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) ss += (k < 3 ? 1.0 : 2.0) * static_cast<double>(S6[k]) * S6[k];
+    acc[5] += ss;
+    acc[6] = fmax(acc[6], jj);  // max |j|^2: the final pass takes sqrt(.) / rho0 once
   }
   block_reduce_store(acc, partials);
 }
@@ -222,17 +226,31 @@ hipError_t launch_set(int storage, const Geo& G, void* buf, const float* canon, 
   return hipGetLastError();
 }
 
+// The force-corrected strain and the implicit rate are instances of their own: their code costs
+// the plain diagnostics 10 VGPRs and a tenth of its instructions.
+template <typename S>
+static void launch_reduce_t(unsigned nb, hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V,
+                            const ForceF& Fo, const S* buf, const float* snu, double* partials) {
+  // FP32 with more blocks than fit at once: 4 blocks per CU instead of the 6 its registers allow
+  // (3.5 % less time per call at 256^3; 3 blocks 7 % more)
+  const size_t cap = sizeof(S) == 4 && nb > kReduceFill ? lds_cap_bytes(4, 4 * kReduceVals * sizeof(double)) : 0;
+  decltype(&reduce_kernel<S, false, false>) f;
+  switch ((Fo.strain_corr ? 1 : 0) + (V.kind == 3 ? 2 : 0)) {
+    case 0: f = reduce_kernel<S, false, false>; break;
+    case 1: f = reduce_kernel<S, true, false>; break;
+    case 2: f = reduce_kernel<S, false, true>; break;
+    default: f = reduce_kernel<S, true, true>; break;
+  }
+  hipLaunchKernelGGL(f, dim3(nb), dim3(256), cap, st, G, M, V, Fo, node_walk(G), buf, snu, partials);
+}
+
 hipError_t launch_reduce(int storage, const Geo& G, const ModelF& M, const ViscF& V, const ForceF& Fo, const void* buf,
                          const float* snu, double* partials, double* out, hipStream_t st) {
-  unsigned nb = static_cast<unsigned>(G.ny) * G.nz;  // one x-row per block at a time
-  if (nb > static_cast<unsigned>(kReduceBlocks)) nb = kReduceBlocks;
-  // FP32: 4 blocks per CU instead of the 5 its registers allow (3.5 % less time per call at
-  // 256^3; 3 blocks 7 % more)
-  const size_t lds = lds_cap_bytes(4, 4 * kReduceVals * sizeof(double));
+  const unsigned nb = reduce_blocks(G);
   switch (storage) {
-    case 0: hipLaunchKernelGGL(reduce_kernel<float>, dim3(nb), dim3(256), lds, st, G, M, V, Fo, cbuf<float>(buf), snu, partials); break;
-    case 1: hipLaunchKernelGGL(reduce_kernel<_Float16>, dim3(nb), dim3(256), 0, st, G, M, V, Fo, cbuf<_Float16>(buf), snu, partials); break;
-    case 2: hipLaunchKernelGGL(reduce_kernel<__bf16>, dim3(nb), dim3(256), 0, st, G, M, V, Fo, cbuf<__bf16>(buf), snu, partials); break;
+    case 0: launch_reduce_t<float>(nb, st, G, M, V, Fo, cbuf<float>(buf), snu, partials); break;
+    case 1: launch_reduce_t<_Float16>(nb, st, G, M, V, Fo, cbuf<_Float16>(buf), snu, partials); break;
+    case 2: launch_reduce_t<__bf16>(nb, st, G, M, V, Fo, cbuf<__bf16>(buf), snu, partials); break;
     default: return hipErrorInvalidValue;
   }
   hipError_t e = hipGetLastError();

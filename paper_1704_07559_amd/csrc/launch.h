@@ -7,7 +7,7 @@
 
 namespace lbm {
 
-// Reductions: 8 doubles per block (at most kReduceBlocks blocks, each taking whole x-rows),
+// Reductions: 8 doubles per block (at most kReduceBlocks blocks over the nodes in memory order),
 // then one block folds the partials in a fixed order.
 constexpr int kReduceBlocks = 4096;
 constexpr int kReduceVals = 8;
