@@ -422,9 +422,8 @@ lbm_status lbm_save_state(lbm_ctx* c, void* dst, void* stream) {
   if (st != LBM_OK) return st;
   if (!dst || !aligned(dst, 4)) return fail(LBM_EINVAL, "dst must be a 4-byte aligned device pointer");
   const hipStream_t s = as_stream(stream);
-  hipError_t e = hipMemcpyAsync(dst, c->buf[c->cur], c->pop_bytes, hipMemcpyDeviceToDevice, s);
-  if (e == hipSuccess && c->snu)
-    e = hipMemcpyAsync(static_cast<char*>(dst) + c->pop_bytes, c->snu, sizeof(float) * c->G.N, hipMemcpyDeviceToDevice, s);
+  const hipError_t e = launch_copy2(c->buf[c->cur], dst, c->pop_bytes, c->snu, static_cast<char*>(dst) + c->pop_bytes,
+                                    c->snu ? sizeof(float) * c->G.N : 0, s);
   return e == hipSuccess ? LBM_OK : hip_fail(e, "lbm_save_state");
 }
 
@@ -433,9 +432,8 @@ lbm_status lbm_load_state(lbm_ctx* c, const void* src, void* stream) {
   if (st != LBM_OK) return st;
   if (!src || !aligned(src, 4)) return fail(LBM_EINVAL, "src must be a 4-byte aligned device pointer");
   const hipStream_t s = as_stream(stream);
-  hipError_t e = hipMemcpyAsync(c->buf[c->cur], src, c->pop_bytes, hipMemcpyDeviceToDevice, s);
-  if (e == hipSuccess && c->snu)
-    e = hipMemcpyAsync(c->snu, static_cast<const char*>(src) + c->pop_bytes, sizeof(float) * c->G.N, hipMemcpyDeviceToDevice, s);
+  const hipError_t e = launch_copy2(src, c->buf[c->cur], c->pop_bytes, static_cast<const char*>(src) + c->pop_bytes,
+                                    c->snu, c->snu ? sizeof(float) * c->G.N : 0, s);
   return e == hipSuccess ? LBM_OK : hip_fail(e, "lbm_load_state");
 }
 
@@ -497,7 +495,7 @@ lbm_status lbm_adjoint_steps(lbm_ctx* c, int nsteps, const float* rec, float* la
     out = t;
   }
   if (in != lam_a) {
-    hipError_t e = hipMemcpyAsync(lam_a, in, lam_bytes, hipMemcpyDeviceToDevice, s);
+    const hipError_t e = launch_copy2(in, lam_a, lam_bytes, nullptr, nullptr, 0, s);
     if (e != hipSuccess) return hip_fail(e, "lbm_adjoint_steps copy");
   }
   return LBM_OK;
@@ -535,7 +533,7 @@ lbm_status lbm_adjoint_steps_noalloc(lbm_ctx* c, int nsteps, const float* rec, f
     out = t;
   }
   if (in != lam) {
-    e = hipMemcpyAsync(lam, in, lam_bytes, hipMemcpyDeviceToDevice, s);
+    e = launch_copy2(in, lam, lam_bytes, nullptr, nullptr, 0, s);
     if (e != hipSuccess) return hip_fail(e, "lbm_adjoint_steps_noalloc copy");
   }
   return LBM_OK;

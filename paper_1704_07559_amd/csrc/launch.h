@@ -79,5 +79,8 @@ hipError_t noalloc_scratch(hipStream_t stream, void** out);
 // largest |j|^2 and leaves as max |u| = sqrt(.) / rho0.
 hipError_t launch_reduce_final(const double* partials, int nblocks, double* out, hipStream_t, double rho0 = 0.0);
 hipError_t launch_stream_copy(const void* src, void* dst, size_t bytes, hipStream_t);
+// Two device-to-device copies (the second may be empty) in one launch.
+hipError_t launch_copy2(const void* src1, void* dst1, size_t bytes1, const void* src2, void* dst2, size_t bytes2,
+                        hipStream_t);
 
 }  // namespace lbm
