@@ -129,8 +129,8 @@ size_t lbm_population_bytes(const lbm_params* p);
  * Create a context over caller-owned device buffers and write the initial state.
  *  f_a, f_b     two distinct population buffers of lbm_population_bytes(p) bytes.
  *  s_nu_field   device float[N]; required for LBM_VISC_SMAGORINSKY and LBM_VISC_POWERLAW
- *               (may be NULL otherwise). Filled with the initial s_nu. For D2Q9 boxes that
- *               take two steps per launch (see lbm_step) the context allocates a second
+ *               (may be NULL otherwise). Filled with the initial s_nu. For D2Q9, whose
+ *               steps go two per launch (see lbm_step), the context allocates a second
  *               float[N] for the field between the two launches of a four-step group.
  *  rho_u        device float[4*N]: planes delta_rho, u_x, u_y, u_z (u_z ignored for D2Q9);
  *               NULL = fluid at rest. Initial populations are g^eq(delta_rho, rho0 u)
@@ -148,9 +148,9 @@ lbm_status lbm_init(lbm_ctx** out, const lbm_params* p, void* f_a, void* f_b, fl
 
 /*
  * Advance nsteps steps of Eq. mrteq (collide with moment-space relaxation, Eq. mrteqvT,
- * then pull streaming), one fused kernel per step. D2Q9 on boxes at least 256 nodes wide
- * (periodic, or with walls in y) takes its steps in groups of four as two launches of two steps each (the intermediate level never leaves the
- * chip; half the HBM traffic); the remaining steps run singly. The result is the same, bit for
+ * then pull streaming), one fused kernel per step. D2Q9 takes its steps in groups of four
+ * as two launches of two steps each (the intermediate level never leaves the chip: half the HBM
+ * traffic, half the launches); the remaining steps run singly. The result is the same, bit for
  * bit, as that of nsteps single steps.
  *  S_out        device float[6*N] (D3Q19, D3Q15) / [3*N] (D2Q9) or NULL: receives, at every step
  *               (at the second step of a launch of two), the strain (formula `strain_kind`) of

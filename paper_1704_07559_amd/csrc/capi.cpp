@@ -29,7 +29,7 @@ struct lbm_ctx {
   void* buf[2];
   int cur;          // buffer holding the current internal state
   float* snu;       // lagged s_nu field (variable viscosity) or nullptr
-  float* snu_pair;  // D2Q9 two-step launches with a lagged s_nu: the field between two of them
+  float* snu_pair;  // D2Q9 two-step launches with a lagged s_nu: the field between two of them (in scratch's allocation)
   double* scratch;  // reduction partials (kReduceBlocks * 8) + result (8)
   long long step;
 };
@@ -230,21 +230,17 @@ lbm_status lbm_init(lbm_ctx** out, const lbm_params* p, void* f_a, void* f_b, fl
   c->snu = lagged ? s_nu_field : nullptr;
   c->step = 0;
   fill_model(c);
-  hipError_t e = hipMalloc(reinterpret_cast<void**>(&c->scratch), sizeof(double) * (kReduceBlocks + 1) * kReduceVals);
+  // one allocation: the reduction scratch and, behind it, the second s_nu field of the D2Q9
+  // two-step launches
+  const size_t scratch_bytes = sizeof(double) * (kReduceBlocks + 1) * kReduceVals;
+  const bool pairs = c->Q == 9 && c->snu && d2q9::pair_supported(c->G);
+  hipError_t e = hipMalloc(reinterpret_cast<void**>(&c->scratch), scratch_bytes + (pairs ? sizeof(float) * N : 0));
   if (e != hipSuccess) {
     delete c;
     (void)hipGetLastError();
     return fail(LBM_ENOMEM, std::string("hipMalloc of the reduction scratch failed: ") + hipGetErrorString(e));
   }
-  if (c->Q == 9 && c->snu && d2q9::pair_supported(c->G)) {
-    e = hipMalloc(reinterpret_cast<void**>(&c->snu_pair), sizeof(float) * N);
-    if (e != hipSuccess) {
-      (void)hipFree(c->scratch);
-      delete c;
-      (void)hipGetLastError();
-      return fail(LBM_ENOMEM, std::string("hipMalloc of the second s_nu field failed: ") + hipGetErrorString(e));
-    }
-  }
+  if (pairs) c->snu_pair = reinterpret_cast<float*>(reinterpret_cast<char*>(c->scratch) + scratch_bytes);
   const hipStream_t s = as_stream(stream);
   switch (c->Q) {
     case 19: e = d3q19::launch_init(p->storage, c->G, c->M, c->buf[0], c->snu, rho_u, grad_u, s); break;
@@ -253,7 +249,6 @@ lbm_status lbm_init(lbm_ctx** out, const lbm_params* p, void* f_a, void* f_b, fl
   }
   if (e != hipSuccess) {
     (void)hipFree(c->scratch);
-    if (c->snu_pair) (void)hipFree(c->snu_pair);
     delete c;
     return hip_fail(e, "lbm_init");
   }
@@ -575,7 +570,6 @@ lbm_status lbm_init_adjoint(lbm_ctx* c, const float* rho_u, const float* lam0, f
 void lbm_destroy(lbm_ctx* c) {
   if (!c) return;
   if (c->scratch) (void)hipFree(c->scratch);
-  if (c->snu_pair) (void)hipFree(c->snu_pair);
   delete c;
 }
 

@@ -232,9 +232,9 @@ __global__ __launch_bounds__(kMaxBlock) void step_kernel(Geo G, ModelF M, ViscF 
 // Two steps per launch: the
 // result is that of two launches of step_kernel, bit for bit, for the algorithmic HBM
 // traffic of one (the rows at block edges are read twice).
-// A block of 256 lanes owns a strip of kPairStrip columns (lane l at column x0 - 1 + l, the
-// two edge lanes a ring column on either side, wrapped periodically) and kPairRows rows of
-// the result, and walks its rows upwards. At row t it pulls the incoming state from HBM and
+// A block of B lanes owns a strip of B - 2 columns (lane l at column x0 - 1 + l, the two edge
+// lanes a ring column on either side, wrapped periodically) and R rows of the result, and walks
+// its rows upwards. At row t it pulls the incoming state from HBM and
 // collides it (level 1, rounded to the storage type as a store would round it); the
 // populations a neighbouring lane pulls at level 2 (c_x != 0) go to an LDS ring of rows,
 // those the lane itself pulls (c_x = 0) stay in registers. After one barrier it pulls row
@@ -242,16 +242,32 @@ __global__ __launch_bounds__(kMaxBlock) void step_kernel(Geo G, ModelF M, ViscF 
 // is deep enough that one barrier per row suffices: the slot written at row t + 1 is none of
 // those read at row t. Level 1 is computed for the two ring columns and for
 // one extra row below and above the block's rows, as the neighbouring blocks compute them
-// too: 256 / 254 more columns and (kPairRows + 2) / kPairRows more rows of level-1 work.
+// too: B / (B - 2) more columns and (R + 2) / R more rows of level-1 work.
 // The lagged rate s_nu cannot be updated in place (a neighbour still reads the old value of
 // a ring node after this block has passed it), so it is read from snu_in and written to
 // snu_out.
-constexpr int kPairStrip = 254;
-// Rows per block: fewer rows mean more level-1 rows computed twice, more rows fewer blocks
-// to overlap one another's barriers and memory waits. Measured at 4096^2: FP32 105.6k MLUPS
-// at 6 rows, 102.9k at 8 and 103.8k at 12; FP16 156.5k, 159.4k and 159.8k.
+//
+// Rows per block (pair_rows): fewer rows mean more level-1 rows computed twice, more rows fewer
+// blocks to overlap one another's barriers and memory waits, and a longer chain of rows (about
+// 2 us each) where the blocks do not fill the chip. Large boxes, 4096^2: FP32 160 us per step
+// at 6 rows, 176 at 2, 163 at 8 and 162 at 12; FP16 111 at 12, 116 at 6, 143 at 2. Below 1280
+// blocks of 256 lanes (5 per CU; 2560 of 128) every row fewer wins: 600 x 201 between walls 5.0 us per step at 1 row, 5.7
+// at 2, 8.7 at 6; 256^2 4.4, 5.0, 8.4; 1024^2 FP32 18.3 at 1, 13.6 at 4 (1280 blocks), 14.5 at 6,
+// FP16 15.5, 11.0, 12.1 and 16.3 at 12; 100 x 3000 (128 lanes) 6.3 at 1, 6.1 at 2, 6.4 at 3.
 template <typename S>
-constexpr int kPairRows = sizeof(S) == 4 ? 6 : 12;
+constexpr int kPairMaxRows = sizeof(S) == 4 ? 6 : 12;
+template <typename S>
+inline int pair_rows(int strips, int ny, int B) {
+  const long long all = static_cast<long long>(strips) * ny, fill = 1280 * 256 / B;
+  const long long r = (all + fill - 1) / fill;
+  return r < kPairMaxRows<S> ? static_cast<int>(r) : kPairMaxRows<S>;
+}
+
+// Lanes per block: 256, or 128 where that leaves at least a quarter fewer lanes without a column
+// (rows up to 126 nodes, or 300 to 378): wide rows favour 256 (4096^2 160 us per step against 181,
+// the strips' ends being partial lines), 100^2 takes 3.4 us either way.
+constexpr int pair_strips(int nx, int B) { return (nx + B - 3) / (B - 2); }
+inline int pair_lanes(int nx) { return 4 * 128 * pair_strips(nx, 128) <= 3 * 256 * pair_strips(nx, 256) ? 128 : 256; }
 
 // LDS ring rows of the x-shifted populations: one with c_y = -1 is read in the row it was
 // written (2 slots: a fast thread writes the next row while a slow one still reads this one),
@@ -269,22 +285,22 @@ constexpr int ring_row(int i) { return i == 0 ? 0 : ring_row<WALLS>(i - 1) + rin
 // EMIT: the strain output S_out (emit 1 Yu, 2 Chai), taken at level 2 only (the strain of
 // the second step's incoming state, which single steps leave in S_out last); a template
 // parameter, as its code costs the instances without it 15 VGPRs otherwise.
-template <typename S, bool WALLS, bool CORR, bool EMIT>
-__global__ __launch_bounds__(256) void pair_kernel(Geo G, ModelF M, ViscF V, ForceF Fo, const S* __restrict__ src,
-                                                   S* __restrict__ dst, const float* snu_in, float* snu_out,
-                                                   float* S_out, int emit) {
+template <typename S, int B, bool WALLS, bool CORR, bool EMIT>
+__global__ __launch_bounds__(B) void pair_kernel(Geo G, int R, ModelF M, ViscF V, ForceF Fo, const S* __restrict__ src,
+                                                 S* __restrict__ dst, const float* snu_in, float* snu_out,
+                                                 float* S_out, int emit) {
   // (in the storage type: level 1 is rounded to it anyway, and 16-bit rows halve the LDS)
-  __shared__ S ring[ring_row<WALLS>(Q)][256];
+  __shared__ S ring[ring_row<WALLS>(Q)][B];
   const int lane = threadIdx.x;
-  const int x0 = blockIdx.x * kPairStrip;
+  const int x0 = blockIdx.x * (B - 2);
   const int xl = x0 - 1 + lane;  // this lane's column, unwrapped
-  // (nx >= 256, so that every lane's column wraps into the box: lanes past the ring column
-  // of a ragged last strip compute level 1 of a column no one reads, and every lane takes
-  // the same path through level 1)
-  const int x = xl < 0 ? xl + G.nx : (xl >= G.nx ? xl - G.nx : xl);
-  const bool kept = lane >= 1 && lane <= kPairStrip && xl < G.nx;  // level 2 owned here
-  const int y0 = blockIdx.y * kPairRows<S>;
-  const int rows = min(kPairRows<S>, G.ny - y0);
+  // (lanes past the ring column of a ragged last strip compute level 1 of a column no one reads,
+  // so that every lane takes the same path through level 1)
+  int x = xl < 0 ? xl + G.nx : (xl >= G.nx ? xl - G.nx : xl);
+  if (x >= G.nx) x = 0;
+  const bool kept = lane >= 1 && lane <= B - 2 && xl < G.nx;  // level 2 owned here
+  const int y0 = blockIdx.y * R;
+  const int rows = min(R, G.ny - y0);
   // level-1 values of the c_x = 0 populations this lane pulls back one and two rows later
   float prev[Q], prev2[Q], snu_prev = 0.0f;
   constexpr auto slot = [](int i, int row) { return ring_row<WALLS>(i) + (row & (ring_rows<WALLS>(i) - 1)); };
@@ -515,36 +531,35 @@ hipError_t launch_step(int storage, const Geo& G, const ModelF& M, const ViscF& 
   return hipGetLastError();
 }
 
-template <typename S, bool W, bool C, bool E>
-static void launch_pair_k(const dim3& grid, hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V,
-                          const ForceF& Fo, const void* src, void* dst, const float* snu_in, float* snu_out,
-                          float* S_out, int emit) {
-  hipLaunchKernelGGL((pair_kernel<S, W, C, E>), grid, dim3(256), 0, st, G, M, V, Fo, cb<S>(src), static_cast<S*>(dst),
-                     snu_in, snu_out, S_out, emit);
+template <typename S, int B>
+static void launch_pair_b(hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V, const ForceF& Fo,
+                          const void* src, void* dst, const float* snu_in, float* snu_out, float* S_out, int emit) {
+  const int strips = pair_strips(G.nx, B), R = pair_rows<S>(strips, G.ny, B);
+  decltype(&pair_kernel<S, B, false, false, false>) k;
+  switch ((G.walls ? 1 : 0) + (Fo.strain_corr ? 2 : 0) + (S_out ? 4 : 0)) {
+    case 0: k = pair_kernel<S, B, false, false, false>; break;
+    case 1: k = pair_kernel<S, B, true, false, false>; break;
+    case 2: k = pair_kernel<S, B, false, true, false>; break;
+    case 3: k = pair_kernel<S, B, true, true, false>; break;
+    case 4: k = pair_kernel<S, B, false, false, true>; break;
+    case 5: k = pair_kernel<S, B, true, false, true>; break;
+    case 6: k = pair_kernel<S, B, false, true, true>; break;
+    default: k = pair_kernel<S, B, true, true, true>; break;
+  }
+  hipLaunchKernelGGL(k, dim3(strips, (G.ny + R - 1) / R, 1), dim3(B), 0, st, G, R, M, V, Fo, cb<S>(src),
+                     static_cast<S*>(dst), snu_in, snu_out, S_out, emit);
 }
 
 template <typename S>
-static void launch_pair_s(unsigned strips, hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V,
-                          const ForceF& Fo, const void* src, void* dst, const float* snu_in, float* snu_out,
-                          float* S_out, int emit) {
-  const dim3 grid(strips, (G.ny + kPairRows<S> - 1) / kPairRows<S>, 1);
-  decltype(&launch_pair_k<S, false, false, false>) k;
-  switch ((G.walls ? 1 : 0) + (Fo.strain_corr ? 2 : 0) + (S_out ? 4 : 0)) {
-    case 0: k = launch_pair_k<S, false, false, false>; break;
-    case 1: k = launch_pair_k<S, true, false, false>; break;
-    case 2: k = launch_pair_k<S, false, true, false>; break;
-    case 3: k = launch_pair_k<S, true, true, false>; break;
-    case 4: k = launch_pair_k<S, false, false, true>; break;
-    case 5: k = launch_pair_k<S, true, false, true>; break;
-    case 6: k = launch_pair_k<S, false, true, true>; break;
-    default: k = launch_pair_k<S, true, true, true>; break;
-  }
-  k(grid, st, G, M, V, Fo, src, dst, snu_in, snu_out, S_out, emit);
+static void launch_pair_s(hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V, const ForceF& Fo,
+                          const void* src, void* dst, const float* snu_in, float* snu_out, float* S_out, int emit) {
+  if (pair_lanes(G.nx) == 128) launch_pair_b<S, 128>(st, G, M, V, Fo, src, dst, snu_in, snu_out, S_out, emit);
+  else launch_pair_b<S, 256>(st, G, M, V, Fo, src, dst, snu_in, snu_out, S_out, emit);
 }
 
 bool pair_supported(const Geo& G) {
-  // (narrower boxes leave most lanes of a strip idle; the grid's y extent is at most 65535)
-  return G.nz == 1 && G.nx >= 256 && (G.ny + 5) / 6 <= 65535;
+  // (the grid's y extent is at most 65535; boxes that tall have 6 rows or more per block)
+  return G.nz == 1 && (G.ny + 5) / 6 <= 65535;
 }
 
 hipError_t launch_pair(int storage, const Geo& G, const ModelF& M, const ViscF& V, const ForceF& Fo, const void* src,
@@ -553,11 +568,10 @@ hipError_t launch_pair(int storage, const Geo& G, const ModelF& M, const ViscF& 
   if ((V.kind == 1 || V.kind == 2) != (snu_in != nullptr) || (snu_in != nullptr) != (snu_out != nullptr) ||
       (snu_in && snu_in == snu_out))
     return hipErrorInvalidValue;
-  const unsigned strips = (G.nx + kPairStrip - 1) / kPairStrip;
   switch (storage) {
-    case 0: launch_pair_s<float>(strips, st, G, M, V, Fo, src, dst, snu_in, snu_out, S_out, emit); break;
-    case 1: launch_pair_s<_Float16>(strips, st, G, M, V, Fo, src, dst, snu_in, snu_out, S_out, emit); break;
-    case 2: launch_pair_s<__bf16>(strips, st, G, M, V, Fo, src, dst, snu_in, snu_out, S_out, emit); break;
+    case 0: launch_pair_s<float>(st, G, M, V, Fo, src, dst, snu_in, snu_out, S_out, emit); break;
+    case 1: launch_pair_s<_Float16>(st, G, M, V, Fo, src, dst, snu_in, snu_out, S_out, emit); break;
+    case 2: launch_pair_s<__bf16>(st, G, M, V, Fo, src, dst, snu_in, snu_out, S_out, emit); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
