@@ -33,6 +33,7 @@ struct Codec<float> {
   static __device__ __forceinline__ float load_cached(const float* p) { return *p; }
   static __device__ __forceinline__ float load(const float* p) { return stream_load(p); }
   static __device__ __forceinline__ void store(float* p, float v) { stream_store(p, v); }
+  static __device__ __forceinline__ void put(float* p, float v) { *p = v; }
 };
 
 template <>
@@ -42,6 +43,11 @@ struct Codec<_Float16> {
   static __device__ __forceinline__ float load(const _Float16* p) { return static_cast<float>(stream_load(p)); }
   // fptrunc float -> half rounds to nearest even (default rounding mode).
   static __device__ __forceinline__ void store(_Float16* p, float v) { stream_store(p, static_cast<_Float16>(v)); }
+  // (the value rounded as it is: opaque, so that an FMA producing it is not fused with the rounding)
+  static __device__ __forceinline__ void put(_Float16* p, float v) {
+    asm("" : "+v"(v));
+    *p = static_cast<_Float16>(v);
+  }
   // Two values rounded by one packed conversion: a in the low half, b in the high half.
   // (Taken apart as a 32-bit word: element access on the converted vector is avoided.)
   static __device__ __forceinline__ unsigned encode2(float a, float b) {
@@ -56,6 +62,7 @@ struct Codec<__bf16> {
   static __device__ __forceinline__ float load(const __bf16* p) { return static_cast<float>(stream_load(p)); }
   // fptrunc float -> bfloat rounds to nearest even.
   static __device__ __forceinline__ void store(__bf16* p, float v) { stream_store(p, static_cast<__bf16>(v)); }
+  static __device__ __forceinline__ void put(__bf16* p, float v) { *p = static_cast<__bf16>(v); }
   static __device__ __forceinline__ unsigned encode2(float a, float b) {
     return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){a, b}, bf16x2));
   }

@@ -167,7 +167,7 @@ __device__ __forceinline__ Rows<Q, S> rows_of(const Geo& G, int x, int y, int z)
 // (ROW_BLOCKS false) the x-shifted populations when a block holds only part of an x-row:
 // their first or last cache line is also read by the neighbouring block, which may run on
 // another XCD, and a streaming hint there costs a refetch from HBM.
-template <class L, typename S, bool WALLS = true, bool ROW_BLOCKS = true>
+template <class L, typename S, bool WALLS = true, bool ROW_BLOCKS = true, bool CACHED = false>
 __device__ __forceinline__ void pull_rows(const S* __restrict__ src, const Geo& G, const Rows<L::Q, S>& r, int y,
                                           float (&g)[L::Q]) {
   const char* cb = reinterpret_cast<const char*>(src);
@@ -182,7 +182,7 @@ __device__ __forceinline__ void pull_rows(const S* __restrict__ src, const Geo& 
     }
     const char* base = cb + r.zb[L::cz(i) + 1] + i * run;
     const unsigned off = r.yb[L::cy(i) + 1] + r.xb[L::cx(i) + 1];
-    if constexpr (L::cx(i) != 0 && !ROW_BLOCKS) g[i] = load_at_cached<S>(base, off);
+    if constexpr (CACHED || (L::cx(i) != 0 && !ROW_BLOCKS)) g[i] = load_at_cached<S>(base, off);
     else g[i] = load_at<S>(base, off);
   });
 }
@@ -291,6 +291,23 @@ __device__ __forceinline__ void pull_staged(const S* __restrict__ src, const Geo
   });
 }
 
+// Boxes whose steps store their rows packed (store_rows_packed) and load the populations through
+// the caches: runs that do not start on 64-byte boundaries (and FP32 rows between 256 and 512
+// nodes that no 64-node segment divides), where nontemporal loads fetch the line that two runs
+// share twice. A D3Q19 LES step, us, before and now: FP32 171x133x95 72 and 59, 250^3 550 and 432,
+// 200^3 250 and 220, 300x200x200 571 and 328 (its second 256-lane segment was mostly idle),
+// 257x200x200 497 and 303, 288x200x200 381 and 315; FP16 200^3 150 and 138, 300x200x200 333 and
+// 257. Not below 2^18 nodes, where a launch is bound by one block's chain of latencies and
+// the extra barrier shows (60^3 8.5 and 9.5), nor for 16-bit runs of a multiple of 64 bytes
+// (224 x 200 x 200 138 and 145; 352 x 150 x 150 151 and 164).
+inline bool packed_rows(const Geo& G, size_t elem) {
+  if (G.nx > 512 || G.N < (1u << 18)) return false;
+  return (G.nx * elem) % 64 != 0 || (elem == 4 && G.nx > 256 && G.nx % 64 != 0);
+}
+// Their stores stream only where the two population buffers outgrow the 256 MB last-level cache
+// (171x133x95 FP16, 82 MB a buffer: 35 us cached, 40 streamed; 250^3 FP32 462 and 432).
+inline bool packed_stream(const Geo& G, int q, size_t elem) { return G.N * elem * q > (size_t(128) << 20); }
+
 // How a step launch pulls along x: 0 blocks hold part of a row (x-shifted loads cached, as
 // a neighbouring block reads their edge lines too); 1 blocks hold whole rows with masked
 // lanes (every load streams); 2 blocks hold whole rows exactly (LDS exchange above).
@@ -350,6 +367,49 @@ __device__ __forceinline__ void store_rows(S* __restrict__ dst, const Geo& G, co
       store_at<S>(cb + i * run, r.self, g[i]);
     });
   }
+}
+
+// Store whole rows through LDS. The R rows of a block (blockDim = (nx, R)) are one contiguous
+// chunk of R * Q * nx elements; where the runs of nx elements do not start on 64-byte boundaries,
+// storing run by run writes part of a line at both ends of every run. Here the block lays its
+// chunk out in LDS (shifted so that LDS and memory agree modulo 16 bytes) and writes it as one
+// stream of 16-byte stores; only the first and last few elements of a chunk are stored singly.
+// All threads of the block must call it (`on`: the thread has a node); sh holds
+// packed_lds_bytes. stream: nontemporal stores.
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+template <int Q, typename S>
+constexpr size_t packed_lds_bytes(int nx, int rows) {
+  return (static_cast<size_t>(rows) * Q * nx + 16 / sizeof(S) - 1) * sizeof(S);
+}
+template <int Q, typename S>
+__device__ __forceinline__ void store_rows_packed(S* __restrict__ dst, const Geo& G, S* sh, bool on, int z, bool stream,
+                                                  const float (&g)[Q]) {
+  constexpr unsigned V = 16 / sizeof(S);
+  const int y0 = blockIdx.y * blockDim.y;
+  const unsigned rows = min(static_cast<int>(blockDim.y), G.ny - y0);
+  S* chunk = dst + (static_cast<size_t>(z) * G.ny + y0) * Q * G.nx;
+  const unsigned head = (reinterpret_cast<uintptr_t>(chunk) & 15) / sizeof(S);
+  const unsigned end = head + rows * Q * G.nx;
+  if (on) {
+    S* p = sh + head + threadIdx.y * Q * G.nx + threadIdx.x;
+    static_for<Q>([&](auto ii) {
+      constexpr int i = ii;
+      Codec<S>::put(p + i * G.nx, g[i]);
+    });
+  }
+  __syncthreads();
+  S* al = chunk - head;  // 16-byte aligned; elements head .. end - 1 are the chunk's
+  const unsigned t = threadIdx.y * blockDim.x + threadIdx.x, threads = blockDim.x * blockDim.y;
+  const unsigned first = head ? 1 : 0, last = end / V;  // whole vectors
+  const u32x4* from = reinterpret_cast<const u32x4*>(sh);
+  u32x4* to = reinterpret_cast<u32x4*>(al);
+  if (stream) {
+    for (unsigned v = first + t; v < last; v += threads) stream_store(to + v, from[v]);
+  } else {
+    for (unsigned v = first + t; v < last; v += threads) to[v] = from[v];
+  }
+  for (unsigned e = head + t; e < min(first * V, end); e += threads) al[e] = sh[e];
+  for (unsigned e = max(last * V, first * V) + t; e < end; e += threads) al[e] = sh[e];
 }
 
 // Node index of (x, y, z) in the node-indexed fields (s_nu, forces, strain, canonical
@@ -459,13 +519,17 @@ struct Launch {
 inline Launch node_launch(const Geo& G) {
   // 256-thread blocks (one wave per SIMD of a CU). The row segment tx is the widest power
   // of two (<= 256) dividing nx when nx is a multiple of 64; ragged rows use the smallest
-  // power of two covering nx (masked lanes).
+  // power of two covering nx (masked lanes), or above 256 nodes equal segments of whole waves
+  // (288 as 192 + 96 instead of 256 + 32: D3Q19 FP16 288x200x40 53 us and 45, 352x352x96 231 and 194).
   int tx = 256;
   if (G.nx % 64 == 0) {
     while (G.nx % tx != 0) tx /= 2;
+  } else if (G.nx > 256) {
+    const int k = (G.nx + 255) / 256;
+    tx = ((G.nx + k - 1) / k + 63) / 64 * 64;
   } else {
     tx = 1;
-    while (tx < G.nx && tx < 256) tx *= 2;
+    while (tx < G.nx) tx *= 2;
   }
   int ty = 256 / tx;
   int py = 1;
@@ -474,6 +538,16 @@ inline Launch node_launch(const Geo& G) {
   Launch L;
   L.block = dim3(tx, ty, 1);
   L.grid = dim3((G.nx + tx - 1) / tx, (G.ny + ty - 1) / ty, G.nz);
+  return L;
+}
+
+// The launch of the packed rows: as many whole rows as fit 256 threads, at least one.
+constexpr int kMaxPackedBlock = 512;
+inline Launch packed_launch(const Geo& G) {
+  const int r = G.nx > 256 ? 1 : (256 / G.nx < G.ny ? 256 / G.nx : G.ny);
+  Launch L;
+  L.block = dim3(G.nx, r, 1);
+  L.grid = dim3(1, (G.ny + r - 1) / r, G.nz);
   return L;
 }
 
@@ -510,6 +584,7 @@ struct StepIO {
   float* S_out;   // strain output or nullptr
   int emit;       // 1 Yu, 2 Chai
   float* save;    // per-step adjoint record (save_planes(V) * N floats) or nullptr
+  bool stream;    // packed rows: nontemporal stores
 };
 
 // Planes of the per-step record the step writes for the adjoint: j (3), plus, for a

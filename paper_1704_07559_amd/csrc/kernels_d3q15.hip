@@ -121,95 +121,113 @@ __device__ __forceinline__ float query_rate(const Pairs& P, float drho, float jx
 }
 
 // XMODE: how a block pulls along x (pull_mode: 0 part rows, 1 whole rows, 2 whole rows with
-// the LDS exchange). CORR: the force-corrected strain (a separate instance, so that the plain
+// the LDS exchange, 3 whole rows, cached loads and packed stores). CORR: the force-corrected strain (a separate instance, so that the plain
 // step keeps its register budget).
 template <typename S, bool WALLS, int XMODE, bool CORR>
-__global__ __launch_bounds__(kMaxBlock) void step_kernel(Geo G, ModelF M, ViscF V, ForceF Fo, StepIO io) {
+__global__ __launch_bounds__(XMODE == 3 ? kMaxPackedBlock : kMaxBlock) void step_kernel(Geo G, ModelF M, ViscF V,
+                                                                                       ForceF Fo, StepIO io) {
   const int x = blockIdx.x * blockDim.x + threadIdx.x;
   const int y = blockIdx.y * blockDim.y + threadIdx.y;
   const int z = blockIdx.z;
-  if (x >= G.nx || y >= G.ny) return;
-  const unsigned self = node_index(G, x, y, z);
-  const Rows<Q, S> r = rows_of<Q, S>(G, x, y, z);
+  // (in a packed-row block a thread below the box's last row has no node, but joins the store)
+  const bool on = x < G.nx && y < G.ny;
+  if constexpr (XMODE != 3) {
+    if (!on) return;
+  }
   float g[Q];
-  if constexpr (XMODE == 2) pull_rows_staged<Lat, S, WALLS>(static_cast<const S*>(io.src), G, r, y, g);
-  else pull_rows<Lat, S, WALLS, XMODE == 1>(static_cast<const S*>(io.src), G, r, y, g);
-  const Pairs P = make_pairs(g);
-  const float drho = delta_rho(P);
-  float jx = momentum<0>(P), jy = momentum<1>(P), jz = momentum<2>(P);
-  float Fx, Fy, Fz;
-  load_force(Fo, G.N, self, Fx, Fy, Fz);
-  if (Fo.mode) {
-    jx = __builtin_fmaf(0.5f, Fx, jx);
-    jy = __builtin_fmaf(0.5f, Fy, jy);
-    jz = __builtin_fmaf(0.5f, Fz, jz);
-  }
-  const Neq n = noneq_moments(P, drho, jx, jy, jz, M.inv_rho0);
-  // the Guo source in moment space; with CORR formed before the strain (half of it joins the
-  // non-equilibrium part the strain takes)
-  float SF[Q];
-  if constexpr (CORR) force_moments(jx, jy, jz, Fx, Fy, Fz, M.inv_rho0, SF);
-  const StrainIn<CORR> si = strain_in<CORR>(n, SF);
-  float Syu[6], Sch[6];
-  float snu = M.s[9];
-  if (V.kind == 3) {
-    // implicit coupling: the strain at the rate of this very collision
-    snu = implicit_rate(P, drho, jx, jy, jz, si, M, V);
-    if (io.S_out) {
-      if (io.emit == 2) {
-        float r[Q];
-        rates_with(M, snu, r);
-        strain_chai_in(P, drho, jx, jy, jz, r, si, M.inv_rho0, Sch);
-      } else {
-        strain_yu(si.ns, M.s[1], snu, M.inv_rho0, Syu);
+  if (XMODE != 3 || on) {
+    const unsigned self = node_index(G, x, y, z);
+    const Rows<Q, S> r = rows_of<Q, S>(G, x, y, z);
+    float snu_ahead = io.snu ? io.snu[self] : 0.0f;  // (its latency hides behind the populations')
+    if constexpr (XMODE == 2) pull_rows_staged<Lat, S, WALLS>(static_cast<const S*>(io.src), G, r, y, g);
+    else pull_rows<Lat, S, WALLS, XMODE == 1, XMODE == 3>(static_cast<const S*>(io.src), G, r, y, g);
+    const Pairs P = make_pairs(g);
+    const float drho = delta_rho(P);
+    float jx = momentum<0>(P), jy = momentum<1>(P), jz = momentum<2>(P);
+    float Fx, Fy, Fz;
+    load_force(Fo, G.N, self, Fx, Fy, Fz);
+    if (Fo.mode) {
+      jx = __builtin_fmaf(0.5f, Fx, jx);
+      jy = __builtin_fmaf(0.5f, Fy, jy);
+      jz = __builtin_fmaf(0.5f, Fz, jz);
+    }
+    const Neq n = noneq_moments(P, drho, jx, jy, jz, M.inv_rho0);
+    // the Guo source in moment space; with CORR formed before the strain (half of it joins the
+    // non-equilibrium part the strain takes)
+    float SF[Q];
+    if constexpr (CORR) force_moments(jx, jy, jz, Fx, Fy, Fz, M.inv_rho0, SF);
+    const StrainIn<CORR> si = strain_in<CORR>(n, SF);
+    float Syu[6], Sch[6];
+    float snu = M.s[9];
+    if (V.kind == 3) {
+      // implicit coupling: the strain at the rate of this very collision
+      snu = implicit_rate(P, drho, jx, jy, jz, si, M, V);
+      if (io.S_out) {
+        if (io.emit == 2) {
+          float r[Q];
+          rates_with(M, snu, r);
+          strain_chai_in(P, drho, jx, jy, jz, r, si, M.inv_rho0, Sch);
+        } else {
+          strain_yu(si.ns, M.s[1], snu, M.inv_rho0, Syu);
+        }
+#pragma unroll
+        for (int c = 0; c < 6; ++c)
+          stream_store(&io.S_out[static_cast<size_t>(c) * G.N + self], io.emit == 2 ? Sch[c] : Syu[c]);
       }
+    } else {
+      // lagged coupling: the strain of the incoming state with the rates of the previous collision
+      // (taken over opaque inside the branch: merging it into the code around changes which products
+      // of a sum the compiler fuses)
+      float snu_prev = M.s[9];
+      if (io.snu) {
+        asm volatile("" : "+v"(snu_ahead));
+        snu_prev = snu_ahead;
+      }
+      const bool need_yu = io.emit == 1 || (V.kind != 0 && !V.drive_chai);
+      const bool need_chai = io.emit == 2 || (V.kind != 0 && V.drive_chai);
+      if (need_yu) strain_yu(si.ns, M.s[1], snu_prev, M.inv_rho0, Syu);
+      if (need_chai) {
+        float r[Q];
+        rates_with(M, snu_prev, r);
+        strain_chai_in(P, drho, jx, jy, jz, r, si, M.inv_rho0, Sch);
+      }
+      if (io.S_out) {
 #pragma unroll
-      for (int c = 0; c < 6; ++c)
-        stream_store(&io.S_out[static_cast<size_t>(c) * G.N + self], io.emit == 2 ? Sch[c] : Syu[c]);
+        for (int c = 0; c < 6; ++c)
+          stream_store(&io.S_out[static_cast<size_t>(c) * G.N + self], io.emit == 2 ? Sch[c] : Syu[c]);
+      }
+      if (V.kind != 0) {
+        snu = viscous_rate(V.drive_chai ? strain_sq(Sch) : strain_sq(Syu), V);
+        io.snu[self] = snu;
+      }
     }
-  } else {
-    // lagged coupling: the strain of the incoming state with the rates of the previous collision
-    const float snu_prev = io.snu ? io.snu[self] : M.s[9];
-    const bool need_yu = io.emit == 1 || (V.kind != 0 && !V.drive_chai);
-    const bool need_chai = io.emit == 2 || (V.kind != 0 && V.drive_chai);
-    if (need_yu) strain_yu(si.ns, M.s[1], snu_prev, M.inv_rho0, Syu);
-    if (need_chai) {
-      float r[Q];
-      rates_with(M, snu_prev, r);
-      strain_chai_in(P, drho, jx, jy, jz, r, si, M.inv_rho0, Sch);
-    }
-    if (io.S_out) {
-#pragma unroll
-      for (int c = 0; c < 6; ++c)
-        stream_store(&io.S_out[static_cast<size_t>(c) * G.N + self], io.emit == 2 ? Sch[c] : Syu[c]);
-    }
-    if (V.kind != 0) {
-      snu = viscous_rate(V.drive_chai ? strain_sq(Sch) : strain_sq(Syu), V);
-      io.snu[self] = snu;
-    }
-  }
-  // relaxation in moment space with the Guo term, then the back-transform
-  float dm[Q];
-  dm[0] = 0.0f;
-  dm[3] = Fx;
-  dm[5] = Fy;
-  dm[7] = Fz;
-  static_for<Q>([&](auto ki) {
-    constexpr int k = ki;
-    if constexpr (k != 0 && k != 3 && k != 5 && k != 7) dm[k] = -(is_nu_slot(k) ? snu : M.s[k]) * n.m[k];
-  });
-  if (Fo.mode) {
-    if constexpr (!CORR) force_moments(jx, jy, jz, Fx, Fy, Fz, M.inv_rho0, SF);
+    // relaxation in moment space with the Guo term, then the back-transform
+    float dm[Q];
+    dm[0] = 0.0f;
+    dm[3] = Fx;
+    dm[5] = Fy;
+    dm[7] = Fz;
     static_for<Q>([&](auto ki) {
       constexpr int k = ki;
-      if constexpr (k != 0 && k != 3 && k != 5 && k != 7 && k != 14) {
-        const float sk = is_nu_slot(k) ? snu : M.s[k];
-        dm[k] = __builtin_fmaf(1.0f - 0.5f * sk, SF[k], dm[k]);
-      }
+      if constexpr (k != 0 && k != 3 && k != 5 && k != 7) dm[k] = -(is_nu_slot(k) ? snu : M.s[k]) * n.m[k];
     });
+    if (Fo.mode) {
+      if constexpr (!CORR) force_moments(jx, jy, jz, Fx, Fy, Fz, M.inv_rho0, SF);
+      static_for<Q>([&](auto ki) {
+        constexpr int k = ki;
+        if constexpr (k != 0 && k != 3 && k != 5 && k != 7 && k != 14) {
+          const float sk = is_nu_slot(k) ? snu : M.s[k];
+          dm[k] = __builtin_fmaf(1.0f - 0.5f * sk, SF[k], dm[k]);
+        }
+      });
+    }
+    add_back_transform(dm, g);
+    if constexpr (XMODE != 3) store_rows<Q>(static_cast<S*>(io.dst), G, r, g);
   }
-  add_back_transform(dm, g);
-  store_rows<Q>(static_cast<S*>(io.dst), G, r, g);
+  if constexpr (XMODE == 3) {
+    extern __shared__ __align__(16) char chunk[];
+    store_rows_packed<Q>(static_cast<S*>(io.dst), G, reinterpret_cast<S*>(chunk), on, z, io.stream, g);
+  }
 }
 
 template <typename S>
@@ -361,6 +379,15 @@ static const S* cb(const void* p) {
 template <typename S, bool CORR>
 static void launch_step_c(bool walls, const Launch& L, hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V,
                           const ForceF& Fo, const StepIO& io) {
+  if (packed_rows(G, sizeof(S))) {
+    const Launch R = packed_launch(G);
+    const size_t chunk = packed_lds_bytes<Q, S>(R.block.x, R.block.y);
+    StepIO pio = io;
+    pio.stream = packed_stream(G, Q, sizeof(S));
+    if (walls) hipLaunchKernelGGL((step_kernel<S, true, 3, CORR>), R.grid, R.block, chunk, st, G, M, V, Fo, pio);
+    else hipLaunchKernelGGL((step_kernel<S, false, 3, CORR>), R.grid, R.block, chunk, st, G, M, V, Fo, pio);
+    return;
+  }
   const int mode = pull_mode(G, L.block);
   // FP32 in whole 256-node rows: 4 blocks per CU instead of 7 (+4.4 % at 256^3; 3 blocks lost
   // 2 %). See lds_cap_bytes.

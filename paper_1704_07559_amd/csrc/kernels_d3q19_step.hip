@@ -9,6 +9,8 @@
 // at most one element), stores are aligned and coalesced.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "d3q19.h"
 #include "d3q19_node.h"
 #include "internal.h"
@@ -23,10 +25,14 @@ namespace d3q19 {
 // populations on entry and the post-collision populations on exit; `self` is the node's
 // element offset in the fields. PACK: g was converted from FP16 on load; the FP16 values are
 // kept packed (pack_pairs) and both their uses, the pair sums and the final sums, read them
-// through mixed-precision FMAs.
+// through mixed-precision FMAs. snu_ahead: the node's lagged rate (read only where io.snu is
+// given), which the caller loads ahead of the populations so that its latency hides behind theirs:
+// behind the pull it cost 7 % of the BF16 384 x 384 x 48 step (105 us against 97.5) and 9 % of FP16
+// 200^3 (139 against 126). It is taken over inside the branch, and opaque, because merging that
+// branch into the code around changes which products of a sum the compiler fuses.
 template <bool CORR, bool PACK>
 __device__ __forceinline__ void node_update(float (&g)[Q], unsigned self, const Geo& G, const ModelF& M,
-                                            const ViscF& V, const ForceF& Fo, const StepIO& io) {
+                                            const ViscF& V, const ForceF& Fo, const StepIO& io, float snu_ahead) {
   HalfPairs hp;
   Pairs P_;
   if constexpr (PACK) {
@@ -72,7 +78,11 @@ __device__ __forceinline__ void node_update(float (&g)[Q], unsigned self, const 
     }
   } else {
     // lagged coupling: the strain of the incoming state with the rates of the previous collision
-    const float snu_prev = io.snu ? io.snu[self] : M.s[9];
+    float snu_prev = M.s[9];
+    if (io.snu) {
+      asm volatile("" : "+v"(snu_ahead));
+      snu_prev = snu_ahead;
+    }
     s_strain = snu_prev;
     const bool need_yu = io.emit == 1 || (V.kind != 0 && !V.drive_chai);
     const bool need_chai = io.emit == 2 || (V.kind != 0 && V.drive_chai);
@@ -148,7 +158,7 @@ __device__ __forceinline__ void node_update(float (&g)[Q], unsigned self, const 
 // The fused step: one thread per node
 // ------------------------------------------------------------------------------------------
 // XMODE: how a block pulls along x (pull_mode: 0 part rows, 1 whole rows, 2 whole rows with
-// the LDS exchange). CORR: the force-corrected strain (a separate instance, so that the plain
+// the LDS exchange, 3 whole rows, cached loads and packed stores). CORR: the force-corrected strain (a separate instance, so that the plain
 // step keeps its register budget).
 // FP16 storage without the LDS exchange (whose x-shifted values arrive through LDS as FP32)
 // keeps the pulled values packed; that instance fits 80 VGPRs without spilling and is asked
@@ -157,35 +167,63 @@ __device__ __forceinline__ void node_update(float (&g)[Q], unsigned self, const 
 template <typename S, int XMODE>
 constexpr bool kPackHalves = Codec<S>::kMixedFma && XMODE != 2;
 template <typename S, int XMODE, bool CORR>
-constexpr int kMinWavesPerEU = (kPackHalves<S, XMODE> && !CORR) ? 6 : 1;
+constexpr int kMinWavesPerEU = (kPackHalves<S, XMODE> && !CORR && XMODE != 3) ? 6 : 1;
 
 template <typename S, bool WALLS, int XMODE, bool CORR>
-__global__ __launch_bounds__(kMaxBlock, (kMinWavesPerEU<S, XMODE, CORR>)) void step_kernel(Geo G, ModelF M, ViscF V,
+__global__ __launch_bounds__(XMODE == 3 ? kMaxPackedBlock : kMaxBlock, (kMinWavesPerEU<S, XMODE, CORR>)) void step_kernel(Geo G, ModelF M, ViscF V,
                                                                                        ForceF Fo, StepIO io) {
   const int x = blockIdx.x * blockDim.x + threadIdx.x;
   const int y = blockIdx.y * blockDim.y + threadIdx.y;
   const int z = blockIdx.z;
-  if (x >= G.nx || y >= G.ny) return;
-  const Rows<Q, S> r = rows_of<Q, S>(G, x, y, z);
-  float g[Q];
-  if constexpr (XMODE == 2) pull_rows_staged<Lat, S, WALLS>(static_cast<const S*>(io.src), G, r, y, g);
-  else pull_rows<Lat, S, WALLS, XMODE == 1>(static_cast<const S*>(io.src), G, r, y, g);
-  node_update<CORR, kPackHalves<S, XMODE>>(g, node_index(G, x, y, z), G, M, V, Fo, io);
-  store_rows<Q>(static_cast<S*>(io.dst), G, r, g);
+  if constexpr (XMODE == 3) {
+    extern __shared__ __align__(16) char chunk[];
+    const bool on = y < G.ny;
+    float g[Q];
+    if (on) {
+      const unsigned self = node_index(G, x, y, z);
+      const float snu_ahead = io.snu ? io.snu[self] : 0.0f;
+      pull_rows<Lat, S, WALLS, true, true>(static_cast<const S*>(io.src), G, rows_of<Q, S>(G, x, y, z), y, g);
+      node_update<CORR, kPackHalves<S, XMODE>>(g, self, G, M, V, Fo, io, snu_ahead);
+    }
+    store_rows_packed<Q>(static_cast<S*>(io.dst), G, reinterpret_cast<S*>(chunk), on, z, io.stream, g);
+  } else {
+    if (x >= G.nx || y >= G.ny) return;
+    const Rows<Q, S> r = rows_of<Q, S>(G, x, y, z);
+    const unsigned self = node_index(G, x, y, z);
+    const float snu_ahead = io.snu ? io.snu[self] : 0.0f;
+    float g[Q];
+    if constexpr (XMODE == 2) pull_rows_staged<Lat, S, WALLS>(static_cast<const S*>(io.src), G, r, y, g);
+    else pull_rows<Lat, S, WALLS, XMODE == 1>(static_cast<const S*>(io.src), G, r, y, g);
+    node_update<CORR, kPackHalves<S, XMODE>>(g, self, G, M, V, Fo, io, snu_ahead);
+    store_rows<Q>(static_cast<S*>(io.dst), G, r, g);
+  }
 }
 
 template <typename S, bool CORR>
 static void launch_step_c(bool walls, const Launch& L, hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V,
                           const ForceF& Fo, const StepIO& io) {
+  if (packed_rows(G, sizeof(S))) {
+    const Launch R = packed_launch(G);
+    StepIO pio = io;
+    pio.stream = packed_stream(G, Q, sizeof(S));
+    // FP32 streaming blocks of four waves: 3 per CU (250^3 429 us against 445, 200^3 214 against 224;
+    // three-wave blocks lose, 171x200x200 187 against 207, and so does FP16, 128 against 166)
+    const unsigned threads = R.block.x * R.block.y;
+    const size_t cap = (sizeof(S) == 4 && pio.stream && threads > 192 && threads <= 256) ? lds_cap_bytes(3, 0) : 0;
+    const size_t chunk = std::max(packed_lds_bytes<Q, S>(R.block.x, R.block.y), cap);
+    if (walls) hipLaunchKernelGGL((step_kernel<S, true, 3, CORR>), R.grid, R.block, chunk, st, G, M, V, Fo, pio);
+    else hipLaunchKernelGGL((step_kernel<S, false, 3, CORR>), R.grid, R.block, chunk, st, G, M, V, Fo, pio);
+    return;
+  }
   const int mode = pull_mode(G, L.block);
-  // FP32: 4 blocks per CU instead of the 5 its registers allow, in the two shapes where that
-  // was measured faster (whole 256-node rows: +2.2-3.0 % at 256^3; 128 x 2 part rows: +1.8 % at
-  // 384^3); whole 128-node rows (the 128 x 128 x 512 channel) ran as fast uncapped and 4.4 %
-  // slower capped, so other shapes keep their occupancy. The 16-bit steps want more waves,
-  // not fewer.
+  // FP32: fewer blocks per CU than the 5 its registers allow, in the two shapes where that was
+  // measured faster (whole 256-node rows: 3 blocks, 415 us at 256^3 against 419 with 4 and 425 with
+  // 5, constant viscosity 419 against 427; 128 x 2 part rows: 4 blocks, +1.8 % at 384^3); whole
+  // 128-node rows (the 128 x 128 x 512 channel) ran as fast uncapped and 4.4 % slower capped, so
+  // other shapes keep their occupancy. The 16-bit steps want more waves, not fewer.
   size_t lds = 0;
   if constexpr (sizeof(S) == 4) {
-    if (mode == 2 && L.block.x == 256 && L.block.y == 1) lds = lds_cap_bytes(4, staged_lds_bytes<Lat>());
+    if (mode == 2 && L.block.x == 256 && L.block.y == 1) lds = lds_cap_bytes(3, staged_lds_bytes<Lat>());
     else if (mode == 0 && L.block.x == 128 && L.block.y == 2) lds = lds_cap_bytes(4, 0);
   }
   switch (mode + (walls ? 3 : 0)) {
