@@ -97,6 +97,11 @@ __device__ __forceinline__ void store_at(void* base, unsigned byte_off, float v)
   Codec<S>::store(reinterpret_cast<S*>(static_cast<char*>(base) + byte_off), v);
 }
 
+template <typename S>
+__device__ __forceinline__ void put_at(void* base, unsigned byte_off, float v) {
+  Codec<S>::put(reinterpret_cast<S*>(static_cast<char*>(base) + byte_off), v);
+}
+
 // True when population i arriving at row y crossed a y-wall (its source row y - c_y is
 // outside 0..ny-1); bounce-back then takes the opposite population of the same node.
 template <int CYI>
@@ -109,8 +114,10 @@ __device__ __forceinline__ bool crosses_wall(const Geo& G, int y) {
 // Pull along -c on a node-indexed array (structure of arrays, plane i at i * N): element i
 // of node x - c_i (periodic), or element opp(i) of x across a y-wall. Used for the adjoint
 // state, whose transposed streaming is a pull along -c; nb holds byte offsets for S.
-template <class L, typename S, bool WALLS = true>
+// CACHED: loaded through the caches.
+template <class L, typename S, bool CACHED>
 __device__ __forceinline__ void pull(const S* __restrict__ src, const Geo& G, const Nbr& nb, int y, float (&g)[L::Q]) {
+  constexpr bool WALLS = true;
   const char* cb = reinterpret_cast<const char*>(src);
   const size_t plane = static_cast<size_t>(G.N) * sizeof(S);
   static_for<L::Q>([&](auto ii) {
@@ -122,7 +129,8 @@ __device__ __forceinline__ void pull(const S* __restrict__ src, const Geo& G, co
         return;
       }
     }
-    g[i] = load_at<S>(cb + i * plane, off);
+    if constexpr (CACHED) g[i] = load_at_cached<S>(cb + i * plane, off);
+    else g[i] = load_at<S>(cb + i * plane, off);
   });
 }
 
@@ -317,6 +325,35 @@ inline int pull_mode(const Geo& G, const dim3& block) {
   return bx >= G.nx ? 1 : 0;
 }
 
+// Whether the runs of nx elements start on multiples of `bytes`. Where they do not, a line is shared
+// by two runs, and nontemporal accesses move it twice.
+inline bool runs_aligned(const Geo& G, size_t elem, size_t bytes) { return (G.nx * elem) % bytes == 0; }
+// The strain query loads through the caches where runs share 32-byte sectors, and where the state
+// fits the 256 MB last-level cache, which nontemporal loads do not fill. us, streaming and cached:
+// FP32 171x133x95 42.5 and 36, 300x100x100 78 and 59, FP16 200^3 114 and 97; FP32 128^3 (159 MB) 35.6
+// and 30.5, 128x128x192 (239 MB) 51 and 44, but 128x128x256 (319 MB) 74 and 74, 256^3 253 and 296, and
+// 200^3 (runs of 800 bytes) 154 and 160.
+inline bool cached_strain(const Geo& G, int q, size_t elem) {
+  return !runs_aligned(G, elem, 32) || G.N * elem * q <= (size_t(1) << 28);
+}
+// The populations query (canonical planes out, as many bytes again) loads and stores through the
+// caches where runs share lines, and where both ends fit: FP32 171x133x95 110 and 66, 200^3 321 and
+// 278, FP16 171x133x95 93 and 45; FP32 128^3 (318 MB both) 56.5 and 52, FP16 128^3 46 and 36, but
+// 128x128x152 (378 MB) 67 and 71.
+inline bool cached_get(const Geo& G, int q, size_t elem) {
+  return !runs_aligned(G, elem, 64) || G.N * (elem + 4) * q <= (size_t(320) << 20);
+}
+// Strain planes are stored streaming unless their rows leave 32-byte sectors half written (FP16
+// 200^3, loads cached: 97 us streaming, 107 cached; FP32 171x133x95 37.6 and 36.5).
+inline bool plane_stream(const Geo& G) { return G.nx % 8 == 0; }
+// (STREAM is a template parameter because the compiler would merge the two stores of a run-time
+// choice into a plain one: the 256^3 strain query fell from 252 to 292 us)
+template <bool STREAM>
+__device__ __forceinline__ void plane_store(float* p, float v) {
+  if constexpr (STREAM) stream_store(p, v);
+  else *p = v;
+}
+
 // Inverse of pull_rows: write canonical g_i(x) to the internal slot it is pulled from.
 template <class L, typename S>
 __device__ __forceinline__ void scatter_rows(S* __restrict__ dst, const Geo& G, const Rows<L::Q, S>& r, int y,
@@ -430,16 +467,17 @@ __device__ __forceinline__ Node<Q, S> node_at(const Geo& G, int x, int y, int z)
   return Node<Q, S>{node_index(G, x, y, z), rows_of<Q, S>(G, x, y, z)};
 }
 
-// Store Q values of node `self_bytes` (byte offset for S) into a node-indexed array
+// Store Q values of node `self_bytes` (its byte offset in a plane) into a node-indexed array
 // (structure of arrays, plane i at i * N): canonical populations and adjoint states.
-template <int Q, typename S>
-__device__ __forceinline__ void store_local(S* __restrict__ dst, const Geo& G, unsigned self_bytes,
+template <int Q, bool STREAM>
+__device__ __forceinline__ void store_local(float* __restrict__ dst, const Geo& G, unsigned self_bytes,
                                             const float (&g)[Q]) {
   char* cb = reinterpret_cast<char*>(dst);
-  const size_t plane = static_cast<size_t>(G.N) * sizeof(S);
+  const size_t plane = static_cast<size_t>(G.N) * sizeof(float);
   static_for<Q>([&](auto ii) {
     constexpr int i = ii;
-    store_at<S>(cb + i * plane, self_bytes, g[i]);
+    if constexpr (STREAM) store_at<float>(cb + i * plane, self_bytes, g[i]);
+    else put_at<float>(cb + i * plane, self_bytes, g[i]);
   });
 }
 

@@ -150,7 +150,9 @@ __device__ __forceinline__ StrainParts strain_parts(const float (&mn)[6], float 
 // canonical planes; a multi-step sweep keeps its intermediate states that way, so that
 // a wave's 38 adjoint streams fall into the DRAM pages of a few rows. Plane 19 stays a plane
 // (at 19 N) in both.
-template <bool VISC, bool STAGE, bool IN_ROWS, bool OUT_ROWS>
+// XMODE: 1 direct loads, 2 the LDS exchange, 3 loads and stores through the caches (rows that are
+// not multiples of 32 bytes).
+template <bool VISC, int XMODE, bool IN_ROWS, bool OUT_ROWS>
 __global__ __launch_bounds__(kMaxBlock) void adjoint_kernel(Geo G, ModelF M, ViscF V, ForceF Fo,
                                                             const float* __restrict__ rec,
                                                             const float* __restrict__ lam_in,
@@ -169,11 +171,11 @@ __global__ __launch_bounds__(kMaxBlock) void adjoint_kernel(Geo G, ModelF M, Vis
 
   float lt[Q];
   if constexpr (IN_ROWS) {
-    if constexpr (STAGE) pull_rows_staged<LatRev, float, true>(lam_in, G, rows, y, lt);
-    else pull_rows<LatRev, float>(lam_in, G, rows, y, lt);
+    if constexpr (XMODE == 2) pull_rows_staged<LatRev, float, true>(lam_in, G, rows, y, lt);
+    else pull_rows<LatRev, float, true, true, XMODE == 3>(lam_in, G, rows, y, lt);
   } else {
-    if constexpr (STAGE) pull_staged<LatRev, float, true>(lam_in, G, nb, y, lt);
-    else pull<LatRev, float>(lam_in, G, nb, y, lt);
+    if constexpr (XMODE == 2) pull_staged<LatRev, float, true>(lam_in, G, nb, y, lt);
+    else pull<LatRev, float, XMODE == 3>(lam_in, G, nb, y, lt);
   }
 
   // mu = D^-1 T lam~
@@ -288,8 +290,18 @@ __global__ __launch_bounds__(kMaxBlock) void adjoint_kernel(Geo G, ModelF M, Vis
 
   float lo[Q];
   apply_transpose(nu, lo);
-  if constexpr (OUT_ROWS) store_rows<Q, float>(lam_out, G, rows, lo);
-  else store_local<Q>(lam_out, G, nb.self, lo);
+  if constexpr (!OUT_ROWS) {
+    store_local<Q, XMODE != 3>(lam_out, G, nb.self, lo);
+  } else if constexpr (XMODE == 3) {
+    char* cb = reinterpret_cast<char*>(lam_out) + rows.zb[1];
+    const size_t run = static_cast<size_t>(G.nx) * sizeof(float);
+    static_for<Q>([&](auto ii) {
+      constexpr int i = ii;
+      put_at<float>(cb + i * run, rows.self, lo[i]);
+    });
+  } else {
+    store_rows<Q, float>(lam_out, G, rows, lo);
+  }
 
   if (grad_force) {
     // G(j) = d S_F / d F
@@ -391,7 +403,7 @@ __global__ __launch_bounds__(256) void loss_seed_kernel(Geo G, ModelF M, ViscF V
       constexpr int i = ii;
       lam[i] -= a + static_cast<float>(CX[i]) * bx + static_cast<float>(CY[i]) * by + static_cast<float>(CZ[i]) * bz;
     });
-    store_local<Q>(lam_out, G, self * 4u, lam);
+    store_local<Q, true>(lam_out, G, self * 4u, lam);
     if (grad_force) {
       grad_force[self] += hfx - 0.5f * bx;
       grad_force[G.N + self] += hfy - 0.5f * by;
@@ -432,26 +444,24 @@ static hipError_t launch_adjoint_layout(const Geo& G, const ModelF& M, const Vis
                                         const float* rec, const float* lam_in, float* lam_out, float* grad_force,
                                         hipStream_t st) {
   const Launch L = node_launch(G);
-  // whole-row blocks exchange the x-shifted adjoint elements through LDS (pull_mode 2)
-  const bool stage = pull_mode(G, L.block) == 2;
-  if (V.kind == 0) {
-    // constant viscosity, whole 256-node rows: 6 blocks per CU instead of 7 (+2.5 % at 256^3;
-    // 4 blocks lost 4 %; the 128^3 shape and the lagged kernel run as fast uncapped)
-    const size_t lds = (stage && L.block.x == 256) ? lds_cap_bytes(6, staged_lds_bytes<LatRev>()) : 0;
-    if (stage)
-      hipLaunchKernelGGL((adjoint_kernel<false, true, IN_ROWS, OUT_ROWS>), L.grid, L.block, lds, st, G, M, V, Fo, rec,
-                         lam_in, lam_out, grad_force);
-    else
-      hipLaunchKernelGGL((adjoint_kernel<false, false, IN_ROWS, OUT_ROWS>), L.grid, L.block, 0, st, G, M, V, Fo, rec,
-                         lam_in, lam_out, grad_force);
-  } else {
-    if (stage)
-      hipLaunchKernelGGL((adjoint_kernel<true, true, IN_ROWS, OUT_ROWS>), L.grid, L.block, 0, st, G, M, V, Fo, rec,
-                         lam_in, lam_out, grad_force);
-    else
-      hipLaunchKernelGGL((adjoint_kernel<true, false, IN_ROWS, OUT_ROWS>), L.grid, L.block, 0, st, G, M, V, Fo, rec,
-                         lam_in, lam_out, grad_force);
+  // rows that share 32-byte sectors go through the caches (100x90x80 29 us a step and 24, 171x133x95 85
+  // and 80; 200^3, rows of 800 bytes, 289 and 297); whole-row blocks (pull_mode 2) exchange the
+  // x-shifted adjoint elements through LDS
+  const int mode = !runs_aligned(G, sizeof(float), 32) ? 3 : (pull_mode(G, L.block) == 2 ? 2 : 1);
+  // constant viscosity, whole 256-node rows: 6 blocks per CU instead of 7 (+2.5 % at 256^3;
+  // 4 blocks lost 4 %; the 128^3 shape and the lagged kernel run as fast uncapped)
+  const size_t lds =
+      (V.kind == 0 && mode == 2 && L.block.x == 256) ? lds_cap_bytes(6, staged_lds_bytes<LatRev>()) : 0;
+  decltype(&adjoint_kernel<false, 1, IN_ROWS, OUT_ROWS>) k;
+  switch (mode + (V.kind == 0 ? 0 : 3)) {
+    case 1: k = adjoint_kernel<false, 1, IN_ROWS, OUT_ROWS>; break;
+    case 2: k = adjoint_kernel<false, 2, IN_ROWS, OUT_ROWS>; break;
+    case 3: k = adjoint_kernel<false, 3, IN_ROWS, OUT_ROWS>; break;
+    case 4: k = adjoint_kernel<true, 1, IN_ROWS, OUT_ROWS>; break;
+    case 5: k = adjoint_kernel<true, 2, IN_ROWS, OUT_ROWS>; break;
+    default: k = adjoint_kernel<true, 3, IN_ROWS, OUT_ROWS>; break;
   }
+  hipLaunchKernelGGL(k, L.grid, L.block, lds, st, G, M, V, Fo, rec, lam_in, lam_out, grad_force);
   return hipGetLastError();
 }
 

@@ -112,14 +112,6 @@ __device__ __forceinline__ float implicit_rate(const Pairs& P_, float drho, floa
   return implicit_smagorinsky(P, A, V.nu0, V.csmag2);
 }
 
-// The s_nu a strain query or the diagnostics take the strain with: the stored lagged rate,
-// the implicit rate of the state itself, or the constant rate.
-__device__ __forceinline__ float query_rate(const Pairs& P, float drho, float jx, float jy, float jz, const StrainIn<true>& si,
-                                            const ModelF& M, const ViscF& V, const float* snu_f, unsigned self) {
-  if (V.kind == 3) return implicit_rate(P, drho, jx, jy, jz, si, M, V);
-  return snu_f ? snu_f[self] : M.s[9];
-}
-
 // XMODE: how a block pulls along x (pull_mode: 0 part rows, 1 whole rows, 2 whole rows with
 // the LDS exchange, 3 whole rows, cached loads and packed stores). CORR: the force-corrected strain (a separate instance, so that the plain
 // step keeps its register budget).
@@ -230,7 +222,8 @@ __global__ __launch_bounds__(XMODE == 3 ? kMaxPackedBlock : kMaxBlock) void step
   }
 }
 
-template <typename S>
+// CACHED: the loads go through the caches (cached_strain); STREAM: streaming stores (plane_stream).
+template <typename S, bool CACHED, bool STREAM>
 __global__ __launch_bounds__(kMaxBlock) void strain_kernel(Geo G, ModelF M, ViscF V, ForceF Fo, const S* buf,
                                                            const float* snu_f, int kind, float* S_out) {
   const int x = blockIdx.x * blockDim.x + threadIdx.x;
@@ -239,7 +232,7 @@ __global__ __launch_bounds__(kMaxBlock) void strain_kernel(Geo G, ModelF M, Visc
   if (x >= G.nx || y >= G.ny) return;
   const Node<Q, S> nb = node_at<Q, S>(G, x, y, z);
   float g[Q];
-  pull_rows<Lat, S>(buf, G, nb.rows, y, g);
+  pull_rows<Lat, S, true, true, CACHED>(buf, G, nb.rows, y, g);
   const Pairs P = make_pairs(g);
   const float drho = delta_rho(P);
   float Fx, Fy, Fz;
@@ -247,7 +240,7 @@ __global__ __launch_bounds__(kMaxBlock) void strain_kernel(Geo G, ModelF M, Visc
   const float jx = momentum<0>(P) + 0.5f * Fx, jy = momentum<1>(P) + 0.5f * Fy, jz = momentum<2>(P) + 0.5f * Fz;
   const Neq n = noneq_moments(P, drho, jx, jy, jz, M.inv_rho0);
   const StrainIn<true> si = strain_in_state(n, jx, jy, jz, Fx, Fy, Fz, M, Fo);
-  const float snu = query_rate(P, drho, jx, jy, jz, si, M, V, snu_f, nb.self);
+  const float snu = V.kind == 3 ? implicit_rate(P, drho, jx, jy, jz, si, M, V) : (snu_f ? snu_f[nb.self] : M.s[9]);
   float S6[6];
   if (kind == 2) {
     float r[Q];
@@ -257,7 +250,7 @@ __global__ __launch_bounds__(kMaxBlock) void strain_kernel(Geo G, ModelF M, Visc
     strain_yu(si.ns, M.s[1], snu, M.inv_rho0, S6);
   }
 #pragma unroll
-  for (int c = 0; c < 6; ++c) stream_store(&S_out[static_cast<size_t>(c) * G.N + nb.self], S6[c]);
+  for (int c = 0; c < 6; ++c) plane_store<STREAM>(&S_out[static_cast<size_t>(c) * G.N + nb.self], S6[c]);
 }
 
 template <typename S>
@@ -301,7 +294,8 @@ __global__ __launch_bounds__(kMaxBlock) void init_kernel(Geo G, ModelF M, S* buf
   if (snu) snu[self] = M.s[9];
 }
 
-template <typename S>
+// CACHED: loads and stores through the caches (cached_get).
+template <typename S, bool CACHED>
 __global__ __launch_bounds__(kMaxBlock) void get_kernel(Geo G, const S* buf, float* canon) {
   const int x = blockIdx.x * blockDim.x + threadIdx.x;
   const int y = blockIdx.y * blockDim.y + threadIdx.y;
@@ -309,8 +303,8 @@ __global__ __launch_bounds__(kMaxBlock) void get_kernel(Geo G, const S* buf, flo
   if (x >= G.nx || y >= G.ny) return;
   const Node<Q, S> nb = node_at<Q, S>(G, x, y, z);
   float g[Q];
-  pull_rows<Lat, S>(buf, G, nb.rows, y, g);
-  store_local<Q>(canon, G, nb.self * 4u, g);
+  pull_rows<Lat, S, true, true, CACHED>(buf, G, nb.rows, y, g);
+  store_local<Q, !CACHED>(canon, G, nb.self * 4u, g);
 }
 
 template <typename S>
@@ -424,13 +418,23 @@ hipError_t launch_step(int storage, const Geo& G, const ModelF& M, const ViscF& 
   return hipGetLastError();
 }
 
+template <typename S>
+static void launch_strain_t(const Launch& L, size_t lds, hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V,
+                            const ForceF& Fo, const void* buf, const float* snu, int kind, float* S_out) {
+  // (rows whose runs are aligned are multiples of 8 nodes)
+  const auto k = !cached_strain(G, Q, sizeof(S)) ? strain_kernel<S, false, true>
+                 : plane_stream(G)               ? strain_kernel<S, true, true>
+                                                 : strain_kernel<S, true, false>;
+  hipLaunchKernelGGL(k, L.grid, L.block, lds, st, G, M, V, Fo, cb<S>(buf), snu, kind, S_out);
+}
+
 hipError_t launch_strain(int storage, const Geo& G, const ModelF& M, const ViscF& V, const ForceF& Fo, const void* buf,
                          const float* snu, int kind, float* S_out, hipStream_t st) {
   const Launch L = node_launch(G);
   switch (storage) {
-    case 0: hipLaunchKernelGGL(strain_kernel<float>, L.grid, L.block, 0, st, G, M, V, Fo, cb<float>(buf), snu, kind, S_out); break;
-    case 1: hipLaunchKernelGGL(strain_kernel<_Float16>, L.grid, L.block, 0, st, G, M, V, Fo, cb<_Float16>(buf), snu, kind, S_out); break;
-    case 2: hipLaunchKernelGGL(strain_kernel<__bf16>, L.grid, L.block, 0, st, G, M, V, Fo, cb<__bf16>(buf), snu, kind, S_out); break;
+    case 0: launch_strain_t<float>(L, 0, st, G, M, V, Fo, buf, snu, kind, S_out); break;
+    case 1: launch_strain_t<_Float16>(L, 0, st, G, M, V, Fo, buf, snu, kind, S_out); break;
+    case 2: launch_strain_t<__bf16>(L, 0, st, G, M, V, Fo, buf, snu, kind, S_out); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -448,12 +452,18 @@ hipError_t launch_init(int storage, const Geo& G, const ModelF& M, void* buf, fl
   return hipGetLastError();
 }
 
-hipError_t launch_get(int storage, const Geo& G, const void* buf, float* canon, hipStream_t st) {
+template <typename S>
+static void launch_get_t(hipStream_t st, const Geo& G, const void* buf, float* canon) {
   const Launch L = node_launch(G);
+  const auto k = cached_get(G, Q, sizeof(S)) ? get_kernel<S, true> : get_kernel<S, false>;
+  hipLaunchKernelGGL(k, L.grid, L.block, 0, st, G, cb<S>(buf), canon);
+}
+
+hipError_t launch_get(int storage, const Geo& G, const void* buf, float* canon, hipStream_t st) {
   switch (storage) {
-    case 0: hipLaunchKernelGGL(get_kernel<float>, L.grid, L.block, 0, st, G, cb<float>(buf), canon); break;
-    case 1: hipLaunchKernelGGL(get_kernel<_Float16>, L.grid, L.block, 0, st, G, cb<_Float16>(buf), canon); break;
-    case 2: hipLaunchKernelGGL(get_kernel<__bf16>, L.grid, L.block, 0, st, G, cb<__bf16>(buf), canon); break;
+    case 0: launch_get_t<float>(st, G, buf, canon); break;
+    case 1: launch_get_t<_Float16>(st, G, buf, canon); break;
+    case 2: launch_get_t<__bf16>(st, G, buf, canon); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

@@ -15,7 +15,8 @@ namespace d3q19 {
 // ------------------------------------------------------------------------------------------
 // Strain of the current state (read only)
 // ------------------------------------------------------------------------------------------
-template <typename S>
+// CACHED: the loads go through the caches (cached_strain); STREAM: streaming stores (plane_stream).
+template <typename S, bool CACHED, bool STREAM>
 __global__ __launch_bounds__(kMaxBlock) void strain_kernel(Geo G, ModelF M, ViscF V, ForceF Fo, const S* buf,
                                                      const float* snu_f, int kind, float* S_out) {
   const int x = blockIdx.x * blockDim.x + threadIdx.x;
@@ -24,7 +25,7 @@ __global__ __launch_bounds__(kMaxBlock) void strain_kernel(Geo G, ModelF M, Visc
   if (x >= G.nx || y >= G.ny) return;
   const Node<Q, S> nb = node_at<Q, S>(G, x, y, z);
   float g[Q];
-  pull_rows<Lat, S>(buf, G, nb.rows, y, g);
+  pull_rows<Lat, S, true, true, CACHED>(buf, G, nb.rows, y, g);
   const Pairs P = make_pairs(g);
   const float drho = delta_rho(P);
   float jx = momentum<0>(P), jy = momentum<1>(P), jz = momentum<2>(P);
@@ -45,7 +46,7 @@ __global__ __launch_bounds__(kMaxBlock) void strain_kernel(Geo G, ModelF M, Visc
     strain_yu(si.ns, M.s[1], snu, M.inv_rho0, S6);
   }
 #pragma unroll
-  for (int c = 0; c < 6; ++c) stream_store(&S_out[static_cast<size_t>(c) * G.N + nb.self], S6[c]);
+  for (int c = 0; c < 6; ++c) plane_store<STREAM>(&S_out[static_cast<size_t>(c) * G.N + nb.self], S6[c]);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -92,7 +93,8 @@ __global__ __launch_bounds__(kMaxBlock) void init_kernel(Geo G, ModelF M, S* buf
   if (snu) snu[self] = M.s[9];
 }
 
-template <typename S>
+// CACHED: loads and stores through the caches (cached_get).
+template <typename S, bool CACHED>
 __global__ __launch_bounds__(kMaxBlock) void get_kernel(Geo G, const S* buf, float* canon) {
   const int x = blockIdx.x * blockDim.x + threadIdx.x;
   const int y = blockIdx.y * blockDim.y + threadIdx.y;
@@ -100,8 +102,8 @@ __global__ __launch_bounds__(kMaxBlock) void get_kernel(Geo G, const S* buf, flo
   if (x >= G.nx || y >= G.ny) return;
   const Node<Q, S> nb = node_at<Q, S>(G, x, y, z);
   float g[Q];
-  pull_rows<Lat, S>(buf, G, nb.rows, y, g);
-  store_local<Q>(canon, G, nb.self * 4u, g);
+  pull_rows<Lat, S, true, true, CACHED>(buf, G, nb.rows, y, g);
+  store_local<Q, !CACHED>(canon, G, nb.self * 4u, g);
 }
 
 template <typename S>
@@ -178,15 +180,25 @@ static const S* cbuf(const void* p) {
   return static_cast<const S*>(p);
 }
 
+template <typename S>
+static void launch_strain_t(const Launch& L, size_t lds, hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V,
+                            const ForceF& Fo, const void* buf, const float* snu, int kind, float* S_out) {
+  // (rows whose runs are aligned are multiples of 8 nodes)
+  const auto k = !cached_strain(G, Q, sizeof(S)) ? strain_kernel<S, false, true>
+                 : plane_stream(G)               ? strain_kernel<S, true, true>
+                                                 : strain_kernel<S, true, false>;
+  hipLaunchKernelGGL(k, L.grid, L.block, lds, st, G, M, V, Fo, cbuf<S>(buf), snu, kind, S_out);
+}
+
 hipError_t launch_strain(int storage, const Geo& G, const ModelF& M, const ViscF& V, const ForceF& Fo, const void* buf,
                          const float* snu, int kind, float* S_out, hipStream_t st) {
   const Launch L = node_launch(G);
   // whole 256-node rows: 5 blocks per CU instead of 8 (+1.9 % at 256^3; 4 blocks lost 0.6 %)
-  const size_t lds = (L.block.x == 256 && L.block.y == 1) ? lds_cap_bytes(5, 0) : 0;
+  const size_t lds = (storage == 0 && L.block.x == 256 && L.block.y == 1) ? lds_cap_bytes(5, 0) : 0;
   switch (storage) {
-    case 0: hipLaunchKernelGGL(strain_kernel<float>, L.grid, L.block, lds, st, G, M, V, Fo, cbuf<float>(buf), snu, kind, S_out); break;
-    case 1: hipLaunchKernelGGL(strain_kernel<_Float16>, L.grid, L.block, 0, st, G, M, V, Fo, cbuf<_Float16>(buf), snu, kind, S_out); break;
-    case 2: hipLaunchKernelGGL(strain_kernel<__bf16>, L.grid, L.block, 0, st, G, M, V, Fo, cbuf<__bf16>(buf), snu, kind, S_out); break;
+    case 0: launch_strain_t<float>(L, lds, st, G, M, V, Fo, buf, snu, kind, S_out); break;
+    case 1: launch_strain_t<_Float16>(L, lds, st, G, M, V, Fo, buf, snu, kind, S_out); break;
+    case 2: launch_strain_t<__bf16>(L, lds, st, G, M, V, Fo, buf, snu, kind, S_out); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -204,12 +216,18 @@ hipError_t launch_init(int storage, const Geo& G, const ModelF& M, void* buf, fl
   return hipGetLastError();
 }
 
-hipError_t launch_get(int storage, const Geo& G, const void* buf, float* canon, hipStream_t st) {
+template <typename S>
+static void launch_get_t(hipStream_t st, const Geo& G, const void* buf, float* canon) {
   const Launch L = node_launch(G);
+  const auto k = cached_get(G, Q, sizeof(S)) ? get_kernel<S, true> : get_kernel<S, false>;
+  hipLaunchKernelGGL(k, L.grid, L.block, 0, st, G, cbuf<S>(buf), canon);
+}
+
+hipError_t launch_get(int storage, const Geo& G, const void* buf, float* canon, hipStream_t st) {
   switch (storage) {
-    case 0: hipLaunchKernelGGL(get_kernel<float>, L.grid, L.block, 0, st, G, cbuf<float>(buf), canon); break;
-    case 1: hipLaunchKernelGGL(get_kernel<_Float16>, L.grid, L.block, 0, st, G, cbuf<_Float16>(buf), canon); break;
-    case 2: hipLaunchKernelGGL(get_kernel<__bf16>, L.grid, L.block, 0, st, G, cbuf<__bf16>(buf), canon); break;
+    case 0: launch_get_t<float>(st, G, buf, canon); break;
+    case 1: launch_get_t<_Float16>(st, G, buf, canon); break;
+    case 2: launch_get_t<__bf16>(st, G, buf, canon); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
