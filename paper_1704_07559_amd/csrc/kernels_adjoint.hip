@@ -445,9 +445,10 @@ static hipError_t launch_adjoint_layout(const Geo& G, const ModelF& M, const Vis
                                         hipStream_t st) {
   const Launch L = node_launch(G);
   // rows that share 32-byte sectors go through the caches (100x90x80 29 us a step and 24, 171x133x95 85
-  // and 80; 200^3, rows of 800 bytes, 289 and 297); whole-row blocks (pull_mode 2) exchange the
-  // x-shifted adjoint elements through LDS
-  const int mode = !runs_aligned(G, sizeof(float), 32) ? 3 : (pull_mode(G, L.block) == 2 ? 2 : 1);
+  // and 80; 200^3, rows of 800 bytes, 289 and 297), except in boxes whose step is one latency long
+  // (101x17x75 7.5 us streaming and 8.8 cached, 60^3 11.0 and 9.7); whole-row blocks (pull_mode 2)
+  // exchange the x-shifted adjoint elements through LDS
+  const int mode = !runs_aligned(G, sizeof(float), 32) && G.N >= (3u << 16) ? 3 : (pull_mode(G, L.block) == 2 ? 2 : 1);
   // constant viscosity, whole 256-node rows: 6 blocks per CU instead of 7 (+2.5 % at 256^3;
   // 4 blocks lost 4 %; the 128^3 shape and the lagged kernel run as fast uncapped)
   const size_t lds =

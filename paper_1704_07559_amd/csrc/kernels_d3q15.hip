@@ -130,9 +130,16 @@ __global__ __launch_bounds__(XMODE == 3 ? kMaxPackedBlock : kMaxBlock) void step
   if (XMODE != 3 || on) {
     const unsigned self = node_index(G, x, y, z);
     const Rows<Q, S> r = rows_of<Q, S>(G, x, y, z);
-    float snu_ahead = io.snu ? io.snu[self] : 0.0f;  // (its latency hides behind the populations')
-    if constexpr (XMODE == 2) pull_rows_staged<Lat, S, WALLS>(static_cast<const S*>(io.src), G, r, y, g);
-    else pull_rows<Lat, S, WALLS, XMODE == 1, XMODE == 3>(static_cast<const S*>(io.src), G, r, y, g);
+    // the rate's latency hides behind the populations' (loaded ahead of the exchange's barrier, else
+    // after their loads: in front of them its branch drags every kernel argument's load there)
+    float snu_ahead = 0.0f;
+    if constexpr (XMODE == 2) {
+      if (io.snu) snu_ahead = io.snu[self];
+      pull_rows_staged<Lat, S, WALLS>(static_cast<const S*>(io.src), G, r, y, g);
+    } else {
+      pull_rows<Lat, S, WALLS, XMODE == 1, XMODE == 3>(static_cast<const S*>(io.src), G, r, y, g);
+      if (XMODE != 1 && io.snu) snu_ahead = io.snu[self];
+    }
     const Pairs P = make_pairs(g);
     const float drho = delta_rho(P);
     float jx = momentum<0>(P), jy = momentum<1>(P), jz = momentum<2>(P);
@@ -172,8 +179,12 @@ __global__ __launch_bounds__(XMODE == 3 ? kMaxPackedBlock : kMaxBlock) void step
       // of a sum the compiler fuses)
       float snu_prev = M.s[9];
       if (io.snu) {
-        asm volatile("" : "+v"(snu_ahead));
-        snu_prev = snu_ahead;
+        if constexpr (XMODE != 1) {
+          asm volatile("" : "+v"(snu_ahead));
+          snu_prev = snu_ahead;
+        } else {
+          snu_prev = io.snu[self];  // (small ragged boxes: 60^3 7.6 us a step against 8.0)
+        }
       }
       const bool need_yu = io.emit == 1 || (V.kind != 0 && !V.drive_chai);
       const bool need_chai = io.emit == 2 || (V.kind != 0 && V.drive_chai);

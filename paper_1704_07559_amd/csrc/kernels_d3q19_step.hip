@@ -25,12 +25,14 @@ namespace d3q19 {
 // populations on entry and the post-collision populations on exit; `self` is the node's
 // element offset in the fields. PACK: g was converted from FP16 on load; the FP16 values are
 // kept packed (pack_pairs) and both their uses, the pair sums and the final sums, read them
-// through mixed-precision FMAs. snu_ahead: the node's lagged rate (read only where io.snu is
-// given), which the caller loads ahead of the populations so that its latency hides behind theirs:
-// behind the pull it cost 7 % of the BF16 384 x 384 x 48 step (105 us against 97.5) and 9 % of FP16
+// through mixed-precision FMAs. snu_ahead (AHEAD): the node's lagged rate (read only where io.snu is
+// given), which the caller loads along with the populations, so that its latency hides behind theirs
+// (ahead of the exchange's barrier, else right after their loads: in front of them its branch drags
+// every kernel argument's load there, 0.3 us more in a small box): at its use it cost 7 % of the BF16 384 x 384 x 48 step (105 us against 97.5) and 9 % of FP16
 // 200^3 (139 against 126). It is taken over inside the branch, and opaque, because merging that
-// branch into the code around changes which products of a sum the compiler fuses.
-template <bool CORR, bool PACK>
+// branch into the code around changes which products of a sum the compiler fuses. Whole rows
+// pulled directly (small ragged boxes) keep the late load: 60^3 8.1 us a step against 8.8.
+template <bool CORR, bool PACK, bool AHEAD>
 __device__ __forceinline__ void node_update(float (&g)[Q], unsigned self, const Geo& G, const ModelF& M,
                                             const ViscF& V, const ForceF& Fo, const StepIO& io, float snu_ahead) {
   HalfPairs hp;
@@ -80,8 +82,12 @@ __device__ __forceinline__ void node_update(float (&g)[Q], unsigned self, const 
     // lagged coupling: the strain of the incoming state with the rates of the previous collision
     float snu_prev = M.s[9];
     if (io.snu) {
-      asm volatile("" : "+v"(snu_ahead));
-      snu_prev = snu_ahead;
+      if constexpr (AHEAD) {
+        asm volatile("" : "+v"(snu_ahead));
+        snu_prev = snu_ahead;
+      } else {
+        snu_prev = io.snu[self];
+      }
     }
     s_strain = snu_prev;
     const bool need_yu = io.emit == 1 || (V.kind != 0 && !V.drive_chai);
@@ -180,21 +186,25 @@ __global__ __launch_bounds__(XMODE == 3 ? kMaxPackedBlock : kMaxBlock, (kMinWave
     const bool on = y < G.ny;
     float g[Q];
     if (on) {
+      pull_rows<Lat, S, WALLS, true, true>(static_cast<const S*>(io.src), G, rows_of<Q, S>(G, x, y, z), y, g);
       const unsigned self = node_index(G, x, y, z);
       const float snu_ahead = io.snu ? io.snu[self] : 0.0f;
-      pull_rows<Lat, S, WALLS, true, true>(static_cast<const S*>(io.src), G, rows_of<Q, S>(G, x, y, z), y, g);
-      node_update<CORR, kPackHalves<S, XMODE>>(g, self, G, M, V, Fo, io, snu_ahead);
+      node_update<CORR, kPackHalves<S, XMODE>, true>(g, self, G, M, V, Fo, io, snu_ahead);
     }
     store_rows_packed<Q>(static_cast<S*>(io.dst), G, reinterpret_cast<S*>(chunk), on, z, io.stream, g);
   } else {
     if (x >= G.nx || y >= G.ny) return;
     const Rows<Q, S> r = rows_of<Q, S>(G, x, y, z);
     const unsigned self = node_index(G, x, y, z);
-    const float snu_ahead = io.snu ? io.snu[self] : 0.0f;
-    float g[Q];
-    if constexpr (XMODE == 2) pull_rows_staged<Lat, S, WALLS>(static_cast<const S*>(io.src), G, r, y, g);
-    else pull_rows<Lat, S, WALLS, XMODE == 1>(static_cast<const S*>(io.src), G, r, y, g);
-    node_update<CORR, kPackHalves<S, XMODE>>(g, self, G, M, V, Fo, io, snu_ahead);
+    float g[Q], snu_ahead = 0.0f;
+    if constexpr (XMODE == 2) {
+      if (io.snu) snu_ahead = io.snu[self];
+      pull_rows_staged<Lat, S, WALLS>(static_cast<const S*>(io.src), G, r, y, g);
+    } else {
+      pull_rows<Lat, S, WALLS, XMODE == 1>(static_cast<const S*>(io.src), G, r, y, g);
+      if (XMODE != 1 && io.snu) snu_ahead = io.snu[self];
+    }
+    node_update<CORR, kPackHalves<S, XMODE>, XMODE != 1>(g, self, G, M, V, Fo, io, snu_ahead);
     store_rows<Q>(static_cast<S*>(io.dst), G, r, g);
   }
 }

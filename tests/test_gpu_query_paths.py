@@ -71,7 +71,8 @@ def test_queries_across_the_cache_sized_rules(shape):
     b.close()
 
 
-@pytest.mark.parametrize("shape", [(5, 7, 9), (4, 6, 100), (3, 5, 257), (2, 4, 300), (6, 10, 40)])
+@pytest.mark.parametrize("shape", [(5, 7, 9), (4, 6, 100), (3, 5, 257), (2, 4, 300), (6, 10, 40),
+                                   (50, 63, 64), (44, 75, 60), (20, 98, 101)])
 @pytest.mark.parametrize("visc,walls", [("const", False), ("smagorinsky", True)])
 def test_ragged_adjoint_sweep_equals_single_steps(shape, visc, walls):
     import torch
