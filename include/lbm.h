@@ -29,7 +29,7 @@
  *   - Every pointer argument named as a field is a DEVICE pointer, caller-owned, and must
  *     stay valid while the context uses it. Population buffers must be 256-byte aligned,
  *     other fields 4-byte aligned. No entry point allocates device memory except lbm_init
- *     (a small reduction scratch) and none frees caller memory.
+ *     (a small reduction scratch, with a second s_nu field behind it where steps are grouped) and none frees caller memory.
  *   - `stream` is a hipStream_t passed as void* (NULL = the null stream). Every call is
  *     asynchronous on that stream, except where a host result is returned (lbm_reduce,
  *     lbm_strain_loss_seed), which synchronise the stream before returning
@@ -148,14 +148,15 @@ lbm_status lbm_init(lbm_ctx** out, const lbm_params* p, void* f_a, void* f_b, fl
 
 /*
  * Advance nsteps steps of Eq. mrteq (collide with moment-space relaxation, Eq. mrteqvT,
- * then pull streaming), one fused kernel per step. D2Q9 takes its steps in groups of four
+ * then pull streaming), one fused kernel per step. D2Q9, and D3Q19 in FP32 without walls, body
+ * force or `save`, at constant viscosity or the lagged Smagorinsky model with the Yu strain (boxes
+ * beyond 2^18 nodes that the launch fills well), take their steps in groups of four
  * as two launches of two steps each (the intermediate level never leaves the chip: half the HBM
  * traffic, half the launches); the remaining steps run singly. The result is the same, bit for
  * bit, as that of nsteps single steps.
- *  S_out        device float[6*N] (D3Q19, D3Q15) / [3*N] (D2Q9) or NULL: receives, at every step
- *               (at the second step of a launch of two), the strain (formula `strain_kind`) of
- *               that step's pre-collision state; after the call it holds the strain of the
- *               state at level n_end - 1.
+ *  S_out        device float[6*N] (D3Q19, D3Q15) / [3*N] (D2Q9) or NULL: the strain (formula
+ *               `strain_kind`) of the last step's pre-collision state, i.e. of the state at
+ *               level n_end - 1 (steps before it may write theirs there on the way).
  *  strain_kind  LBM_STRAIN_YU or LBM_STRAIN_CHAI (ignored when S_out is NULL).
  *  save         device float[nsteps*R*N] or NULL, R = lbm_save_planes(ctx) (D3Q19 only;
  *               LBM_EUNSUPPORTED otherwise):

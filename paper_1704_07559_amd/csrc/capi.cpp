@@ -29,7 +29,9 @@ struct lbm_ctx {
   void* buf[2];
   int cur;          // buffer holding the current internal state
   float* snu;       // lagged s_nu field (variable viscosity) or nullptr
-  float* snu_pair;  // D2Q9 two-step launches with a lagged s_nu: the field between two of them (in scratch's allocation)
+  bool pairs;       // steps run two per launch where a call allows it
+  lbm::d3q19::PairPlan pair_plan;  // (D3Q19)
+  float* snu_pair;  // two-step launches with a lagged s_nu: the field between two of them (in scratch's allocation)
   double* scratch;  // reduction partials (kReduceBlocks * 8) + result (8)
   long long step;
 };
@@ -230,17 +232,24 @@ lbm_status lbm_init(lbm_ctx** out, const lbm_params* p, void* f_a, void* f_b, fl
   c->snu = lagged ? s_nu_field : nullptr;
   c->step = 0;
   fill_model(c);
-  // one allocation: the reduction scratch and, behind it, the second s_nu field of the D2Q9
-  // two-step launches
+  // one allocation: the reduction scratch and, behind it, the second s_nu field of the two-step
+  // launches (where there is no room for it, every step is a launch of its own)
   const size_t scratch_bytes = sizeof(double) * (kReduceBlocks + 1) * kReduceVals;
-  const bool pairs = c->Q == 9 && c->snu && d2q9::pair_supported(c->G);
-  hipError_t e = hipMalloc(reinterpret_cast<void**>(&c->scratch), scratch_bytes + (pairs ? sizeof(float) * N : 0));
+  if (c->Q == 19) c->pair_plan = d3q19::pair_plan(p->storage, c->G, c->V, c->F);
+  c->pairs = c->Q == 9 ? d2q9::pair_supported(c->G) : c->pair_plan.planes > 0;
+  const size_t pair_bytes = c->pairs && c->snu ? sizeof(float) * N : 0;
+  hipError_t e = hipMalloc(reinterpret_cast<void**>(&c->scratch), scratch_bytes + pair_bytes);
+  if (e != hipSuccess && pair_bytes) {
+    (void)hipGetLastError();
+    c->pairs = false;
+    e = hipMalloc(reinterpret_cast<void**>(&c->scratch), scratch_bytes);
+  }
   if (e != hipSuccess) {
     delete c;
     (void)hipGetLastError();
     return fail(LBM_ENOMEM, std::string("hipMalloc of the reduction scratch failed: ") + hipGetErrorString(e));
   }
-  if (pairs) c->snu_pair = reinterpret_cast<float*>(reinterpret_cast<char*>(c->scratch) + scratch_bytes);
+  if (c->pairs && pair_bytes) c->snu_pair = reinterpret_cast<float*>(reinterpret_cast<char*>(c->scratch) + scratch_bytes);
   const hipStream_t s = as_stream(stream);
   switch (c->Q) {
     case 19: e = d3q19::launch_init(p->storage, c->G, c->M, c->buf[0], c->snu, rho_u, grad_u, s); break;
@@ -277,16 +286,20 @@ lbm_status lbm_step(lbm_ctx* c, int nsteps, float* S_out, int strain_kind, float
   const size_t rec_elems = static_cast<size_t>(has_adjoint(c) ? save_planes(c->V) : 0) * c->G.N;
   const hipStream_t s = as_stream(stream);
   int n = 0;
-  if (c->Q == 9 && d2q9::pair_supported(c->G)) {
-    // D2Q9: two steps per launch, two launches at a time, so that the population buffers and
-    // the lagged field end where single steps leave them (s_nu: field -> snu_pair -> field)
-    for (; nsteps - n >= 4; n += 4) {
+  if (c->pairs && !save) {
+    // two steps per launch, two launches at a time, so that the population buffers and the lagged
+    // field end where single steps leave them (s_nu: field -> snu_pair -> field). The strain is the
+    // last step's: D2Q9 launches write it themselves, for D3Q19 that step runs singly.
+    const int single = c->Q == 19 && S_out ? 1 : 0;
+    for (; nsteps - n >= 4 + single; n += 4) {
       for (int h = 0; h < 2; ++h) {
-        float* from = h == 0 ? c->snu : c->snu_pair;
-        float* to = h == 0 ? c->snu_pair : c->snu;
-        hipError_t e = d2q9::launch_pair(c->p.storage, c->G, c->M, c->V, c->F, c->buf[c->cur], c->buf[1 - c->cur],
-                                         c->snu ? from : nullptr, c->snu ? to : nullptr, S_out,
-                                         S_out ? strain_kind : 0, s);
+        const float* from = h == 0 ? c->snu : c->snu_pair;
+        float* to = !c->snu ? nullptr : (h == 0 ? c->snu_pair : c->snu);
+        if (!c->snu) from = nullptr;
+        hipError_t e = c->Q == 19 ? d3q19::launch_pair(c->pair_plan, c->G, c->M, c->V, c->buf[c->cur], c->buf[1 - c->cur],
+                                                       from, to, s)
+                                  : d2q9::launch_pair(c->p.storage, c->G, c->M, c->V, c->F, c->buf[c->cur],
+                                                      c->buf[1 - c->cur], from, to, S_out, S_out ? strain_kind : 0, s);
         if (e != hipSuccess) return hip_fail(e, "lbm_step");
         c->cur = 1 - c->cur;
         c->step += 2;

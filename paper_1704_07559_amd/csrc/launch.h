@@ -33,6 +33,15 @@ hipError_t launch_loss_seed(int storage, const Geo&, const ModelF&, const ViscF&
                             hipStream_t);
 hipError_t launch_init_adjoint(const Geo&, const ModelF&, const float* rho_u, const float* lam0, float* grad_u0,
                                hipStream_t);
+// Two steps in one launch: src -> dst, the lagged s_nu field (if any) snu_in -> snu_out (distinct
+// buffers). The result equals two launch_step calls bit for bit. The plan (how blocks of `rows` rows
+// and `planes` planes cover the box) is empty, planes = 0, where single steps are to be taken.
+struct PairPlan {
+  int rows, planes, tx, ty, tiles;
+};
+PairPlan pair_plan(int storage, const Geo&, const ViscF&, const ForceF&);
+hipError_t launch_pair(const PairPlan&, const Geo&, const ModelF&, const ViscF&, const void* src, void* dst,
+                       const float* snu_in, float* snu_out, hipStream_t);
 }  // namespace d3q19
 
 namespace d2q9 {
