@@ -13,11 +13,12 @@ has none inside and is checked once after the timing).
 Output: one JSON line. ``value`` is MLUPS (million lattice-node updates per second) with
 inputs resident in HBM, over exactly --steps timed steps after --warmup untimed ones (the
 device is first kept busy for a quarter second with STREAM-style copies, so the run does not
-start from an idle GPU). ``roofline`` prices the step kernel's algorithmic bytes per node
-(19 reads + 19 writes of 4 B, plus the 4 B read and write of the lagged s_nu field) against
-the 8 TB/s HBM peak; its kernel time is the device time of all timed launches (HIP events
+start from an idle GPU). ``roofline`` prices the step kernel's algorithmic bytes per node and
+launch (19 reads + 19 writes of 4 B, plus the 4 B read and write of the lagged s_nu field) against
+the 8 TB/s HBM peak; a launch takes ``steps_per_launch`` steps (two for the headline: 80 B per node
+and step); its kernel time is the device time of all timed launches (HIP events
 on the launch stream around every run of launches between two diagnostics), divided by the
-number of launches. ``extra`` carries the other workloads (FP16/BF16-stored 384^3 runs and
+number of steps. ``extra`` carries the other workloads (FP16/BF16-stored 384^3 runs and
 their FP32 reference, the one-rank slab, implicit Smagorinsky, D3Q15, D2Q9 in FP32 and FP16
 one and two steps per launch, the power-law channel, the adjoint, the Yu/Chai cost comparison
 of Section 5.2): each is warmed up for at
@@ -55,6 +56,8 @@ def log(msg):
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
 
 
+# ... those of the kernel that takes two D3Q19 steps per launch
+PAIR_SOURCES = KERNEL_SOURCES + ["paper_1704_07559_amd/csrc/kernels_d3q19_pair.hip"]
 # ... and, with the strain query kernel, those of the Section 5.2 comparison
 STRAIN_SOURCES = KERNEL_SOURCES + ["paper_1704_07559_amd/csrc/kernels_d3q19.hip"]
 
@@ -90,11 +93,10 @@ def read_traffic(name: str, sha: str):
 VALU_WAVE_INSTS_PER_S = 256 * 4 * 2.4e9 / 4
 
 
-def read_valu(label: str, sha: str):
+def read_valu(label: str, sha: str, name: str = "valu_step_d3q19_les.txt"):
     """VALU instructions per launch of the step kernel from the committed rocprofv3 counter
-    summary (profiles/valu_step_d3q19_les.txt), if it was taken on the current kernel
-    source (else None)."""
-    f = ROOT / "profiles" / "valu_step_d3q19_les.txt"
+    summary (a file of profiles/), if it was taken on the current kernel source (else None)."""
+    f = ROOT / "profiles" / name
     if not f.exists():
         return None
     kv = {}
@@ -233,6 +235,35 @@ def leg(torch, capi, sim, nodes, steps, warmup, bytes_per_node, **extra):
            "ke": r["diag"]["ke"], "nonfinite": r["diag"]["nonfinite"]}
     out.update(extra)
     return out, r
+
+
+def pair_plan(nx, ny, nz):
+    """Rows of the tile with which the library takes two FP32 steps per launch (its launch rule
+    restated), 0 where it takes them singly. For the cases it groups: periodic, no body force,
+    constant viscosity or the lagged Smagorinsky model with the Yu strain."""
+    least, rows = 0, 0
+    for r in (13, 9):
+        for chunks in range(1, min(64, nz) + 1):
+            planes = -(-nz // chunks)
+            tiles = -(-nx // 64) * -(-ny // r) * -(-nz // planes)
+            cost = -(-tiles // 256) * 256 * (planes + 2) * 64 * r
+            cost += cost // 20 if r == 9 else 0
+            if not rows or cost < least:
+                least, rows = cost, r
+    n = nx * ny * nz
+    fits = n * 76 <= 1 << 27
+    return rows if (fits and n > 1 << 18 and 10 * n >= 3 * least) or (not fits and 10 * n >= 6 * least) else 0
+
+
+def les_step(n):
+    """(kernel instance, bytes per node and step, source sha, steps per launch) of the FP32 LES step on n^3."""
+    rows = pair_plan(n, n, n)
+    if not rows:
+        return step_kernel_name(n, n), 160, kernel_source_sha(), 1
+    whole = "true" if step_kernel_name(n, n).split(", ")[2] == "2" else "false"
+    stream = "false" if n ** 3 * 76 <= 1 << 27 or (n % 16 and n ** 3 * 76 > 1 << 28) else "true"
+    return (f"lbm::d3q19::(anonymous namespace)::pair_kernel<{1024 if rows == 13 else 768}, 64, {rows}, 1, {whole}, "
+            f"{stream}>", 80, kernel_source_sha(PAIR_SOURCES), 2)
 
 
 def step_kernel_name(nx, ny, storage="f32", walls=False, corrected=False):
@@ -725,7 +756,7 @@ def main():
             for _ in range(5):
                 sims["yu"].step(1, S_out=S, strain_kind=kind)
         for drive in ("yu", "chai"):
-            sims[drive].step(5)
+            SingleSteps(sims[drive]).step(5)
         torch.cuda.synchronize()
         for s_ in sims.values():
             s_.close()
@@ -749,10 +780,11 @@ def main():
     torch.cuda.empty_cache()
     wall, kern, diag = r["wall"], r["kernel_s"], r["diag"]
     mlups = N * args.steps / wall / 1e6
-    bytes_per_node = 19 * 4 * 2 + 4 * 2
+    # 160 B a node and launch; the library takes two steps per launch where pair_plan says so
+    kernel, bytes_per_node, psha, per_launch = les_step(n)
     achieved = bytes_per_node * N / kern / 1e9
     sha = kernel_source_sha()
-    traffic = read_traffic("step_d3q19_f32_les256", sha) if n == 256 else None  # taken on 256^3
+    traffic = read_traffic("pair_d3q19_f32_les256", psha) if n == 256 else None  # taken on 256^3
     result = {
         "metric": METRIC,
         "value": round(mlups, 1),
@@ -773,10 +805,11 @@ def main():
                    "nodes": N, "lattice": "D3Q19", "storage": "f32"},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4),
-                     "traffic": traffic, "kernel": step_kernel_name(n, n),
-                     "kernel_ms": round(kern * 1e3, 4), "kernel_time": "device time of all timed launches / launches",
-                     "bytes_per_node": bytes_per_node, "kernel_source_sha": sha,
-                     "valu_issue_frac": valu_frac(read_valu("f32_les256", sha) if n == 256 else None, kern)},
+                     "traffic": traffic, "kernel": kernel, "steps_per_launch": per_launch,
+                     "kernel_ms": round(kern * 1e3, 4), "kernel_time": "device time of all timed launches / steps",
+                     "bytes_per_node": bytes_per_node, "kernel_source_sha": psha,
+                     "valu_issue_frac": valu_frac(read_valu("f32_les256_pair", psha, "valu_pair_d3q19_les.txt")
+                                                  if n == 256 else None, kern * per_launch)},
         "diagnostics": {"mass": diag["mass"], "ke": diag["ke"], "umax": diag["umax"], "nonfinite": diag["nonfinite"]},
     }
     if win:
@@ -794,10 +827,11 @@ def main():
         rho_u3 = lbm.rho_u_field(np.zeros((m, m, m)), u3)
         del u3
         for name, st, bpn in (("f16", capi.LBM_F16, 19 * 2 * 2 + 8), ("bf16", capi.LBM_BF16, 19 * 2 * 2 + 8),
-                              ("f32", capi.LBM_F32, 19 * 4 * 2 + 8)):
+                              ("f32", capi.LBM_F32, les_step(m)[1])):
             s3 = lbm.LBM(les_params(capi, m, st), rho_u3)
             log(f"{name} {m}^3")
-            o, r3 = leg(torch, capi, s3, m ** 3, K, W, bpn, kernel=step_kernel_name(m, m, name))
+            o, r3 = leg(torch, capi, s3, m ** 3, K, W, bpn,
+                        kernel=les_step(m)[0] if name == "f32" else step_kernel_name(m, m, name))
             if name == "f16":
                 o["valu_issue_frac"] = valu_frac(read_valu("f16_les384", sha), r3["kernel_s"])
             extra[f"les384_{name}"] = o
