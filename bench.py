@@ -57,7 +57,8 @@ def log(msg):
 
 
 # ... those of the kernel that takes two D3Q19 steps per launch
-PAIR_SOURCES = KERNEL_SOURCES + ["paper_1704_07559_amd/csrc/kernels_d3q19_pair.hip"]
+PAIR_SOURCES = KERNEL_SOURCES + ["paper_1704_07559_amd/csrc/kernels_d3q19_pair.hip",
+                                 "paper_1704_07559_amd/csrc/pair_march.h"]
 # ... and, with the strain query kernel, those of the Section 5.2 comparison
 STRAIN_SOURCES = KERNEL_SOURCES + ["paper_1704_07559_amd/csrc/kernels_d3q19.hip"]
 
@@ -237,7 +238,7 @@ def leg(torch, capi, sim, nodes, steps, warmup, bytes_per_node, **extra):
     return out, r
 
 
-def pair_plan(nx, ny, nz):
+def pair_plan(nx, ny, nz, q=19):
     """Rows of the tile with which the library takes two FP32 steps per launch (its launch rule
     restated), 0 where it takes them singly. For the cases it groups: periodic, no body force,
     constant viscosity or the lagged Smagorinsky model with the Yu strain."""
@@ -251,8 +252,7 @@ def pair_plan(nx, ny, nz):
             if not rows or cost < least:
                 least, rows = cost, r
     n = nx * ny * nz
-    fits = n * 76 <= 1 << 27
-    return rows if (fits and n > 1 << 18 and 10 * n >= 3 * least) or (not fits and 10 * n >= 6 * least) else 0
+    return rows if n > 1 << 18 and 100 * n >= (38 if n * q * 4 <= 1 << 27 else 60) * least else 0
 
 
 def les_step(n):
@@ -262,7 +262,7 @@ def les_step(n):
         return step_kernel_name(n, n), 160, kernel_source_sha(), 1
     whole = "true" if step_kernel_name(n, n).split(", ")[2] == "2" else "false"
     stream = "false" if n ** 3 * 76 <= 1 << 27 or (n % 16 and n ** 3 * 76 > 1 << 28) else "true"
-    return (f"lbm::d3q19::(anonymous namespace)::pair_kernel<{1024 if rows == 13 else 768}, 64, {rows}, 1, {whole}, "
+    return (f"lbm::pair_kernel<lbm::d3q19::PairUpdate<1, {whole}>, {1024 if rows == 13 else 768}, 64, {rows}, "
             f"{stream}>", 80, kernel_source_sha(PAIR_SOURCES), 2)
 
 
@@ -863,12 +863,12 @@ def main():
         del si
         torch.cuda.empty_cache()
         # the same LES on the D3Q15 lattice (Yu-type formula of the Section 5.4 route):
-        # 15 x 4 B read + written + 8 B lagged s_nu = 128 B/node
+        # 15 x 4 B read + written + 8 B lagged s_nu = 128 B a node and launch
         w = _workloads()
         p15 = w.params(w.load("C1"), lattice="D3Q15", grid={"nx": n, "ny": n, "nz": n})
         s15 = lbm.LBM(p15, lbm.rho_u_field(np.zeros((n, n, n)), u))
         log(f"D3Q15 FP32 {n}^3 LES")
-        extra["les256_d3q15"], _ = leg(torch, capi, s15, N, K, W, 128)
+        extra["les256_d3q15"], _ = leg(torch, capi, s15, N, K, W, 64 if pair_plan(n, n, n, 15) else 128)
         s15.close()
         del s15
         torch.cuda.empty_cache()

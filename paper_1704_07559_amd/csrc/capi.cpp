@@ -30,7 +30,7 @@ struct lbm_ctx {
   int cur;          // buffer holding the current internal state
   float* snu;       // lagged s_nu field (variable viscosity) or nullptr
   bool pairs;       // steps run two per launch where a call allows it
-  lbm::d3q19::PairPlan pair_plan;  // (D3Q19)
+  PairPlan pair_plan;  // (D3Q19, D3Q15)
   float* snu_pair;  // two-step launches with a lagged s_nu: the field between two of them (in scratch's allocation)
   double* scratch;  // reduction partials (kReduceBlocks * 8) + result (8)
   long long step;
@@ -236,6 +236,7 @@ lbm_status lbm_init(lbm_ctx** out, const lbm_params* p, void* f_a, void* f_b, fl
   // launches (where there is no room for it, every step is a launch of its own)
   const size_t scratch_bytes = sizeof(double) * (kReduceBlocks + 1) * kReduceVals;
   if (c->Q == 19) c->pair_plan = d3q19::pair_plan(p->storage, c->G, c->V, c->F);
+  else if (c->Q == 15) c->pair_plan = d3q15::pair_plan(p->storage, c->G, c->V, c->F);
   c->pairs = c->Q == 9 ? d2q9::pair_supported(c->G) : c->pair_plan.planes > 0;
   const size_t pair_bytes = c->pairs && c->snu ? sizeof(float) * N : 0;
   hipError_t e = hipMalloc(reinterpret_cast<void**>(&c->scratch), scratch_bytes + pair_bytes);
@@ -289,17 +290,22 @@ lbm_status lbm_step(lbm_ctx* c, int nsteps, float* S_out, int strain_kind, float
   if (c->pairs && !save) {
     // two steps per launch, two launches at a time, so that the population buffers and the lagged
     // field end where single steps leave them (s_nu: field -> snu_pair -> field). The strain is the
-    // last step's: D2Q9 launches write it themselves, for D3Q19 that step runs singly.
-    const int single = c->Q == 19 && S_out ? 1 : 0;
+    // last step's: D2Q9 launches write it themselves, for the others that step runs singly.
+    const int single = c->Q != 9 && S_out ? 1 : 0;
     for (; nsteps - n >= 4 + single; n += 4) {
       for (int h = 0; h < 2; ++h) {
-        const float* from = h == 0 ? c->snu : c->snu_pair;
+        const float* from = !c->snu ? nullptr : (h == 0 ? c->snu : c->snu_pair);
         float* to = !c->snu ? nullptr : (h == 0 ? c->snu_pair : c->snu);
-        if (!c->snu) from = nullptr;
-        hipError_t e = c->Q == 19 ? d3q19::launch_pair(c->pair_plan, c->G, c->M, c->V, c->buf[c->cur], c->buf[1 - c->cur],
-                                                       from, to, s)
-                                  : d2q9::launch_pair(c->p.storage, c->G, c->M, c->V, c->F, c->buf[c->cur],
-                                                      c->buf[1 - c->cur], from, to, S_out, S_out ? strain_kind : 0, s);
+        const void* src = c->buf[c->cur];
+        void* dst = c->buf[1 - c->cur];
+        hipError_t e;
+        switch (c->Q) {
+          case 19: e = d3q19::launch_pair(c->pair_plan, c->G, c->M, c->V, src, dst, from, to, s); break;
+          case 15: e = d3q15::launch_pair(c->pair_plan, c->G, c->M, c->V, src, dst, from, to, s); break;
+          default:
+            e = d2q9::launch_pair(c->p.storage, c->G, c->M, c->V, c->F, src, dst, from, to, S_out,
+                                  S_out ? strain_kind : 0, s);
+        }
         if (e != hipSuccess) return hip_fail(e, "lbm_step");
         c->cur = 1 - c->cur;
         c->step += 2;

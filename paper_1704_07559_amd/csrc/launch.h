@@ -12,6 +12,13 @@ namespace lbm {
 constexpr int kReduceBlocks = 4096;
 constexpr int kReduceVals = 8;
 
+// Two steps in one launch (the 3D lattices): src -> dst, the lagged s_nu field (if any) snu_in -> snu_out (distinct
+// buffers). The result equals two launch_step calls bit for bit. The plan (how blocks of `rows` rows
+// and `planes` planes cover the box) is empty, planes = 0, where single steps are to be taken.
+struct PairPlan {
+  int rows, planes, tx, ty, tiles;
+};
+
 namespace d3q19 {
 hipError_t launch_init(int storage, const Geo&, const ModelF&, void* buf, float* snu, const float* rho_u,
                        const float* grad_u, hipStream_t);
@@ -33,12 +40,6 @@ hipError_t launch_loss_seed(int storage, const Geo&, const ModelF&, const ViscF&
                             hipStream_t);
 hipError_t launch_init_adjoint(const Geo&, const ModelF&, const float* rho_u, const float* lam0, float* grad_u0,
                                hipStream_t);
-// Two steps in one launch: src -> dst, the lagged s_nu field (if any) snu_in -> snu_out (distinct
-// buffers). The result equals two launch_step calls bit for bit. The plan (how blocks of `rows` rows
-// and `planes` planes cover the box) is empty, planes = 0, where single steps are to be taken.
-struct PairPlan {
-  int rows, planes, tx, ty, tiles;
-};
 PairPlan pair_plan(int storage, const Geo&, const ViscF&, const ForceF&);
 hipError_t launch_pair(const PairPlan&, const Geo&, const ModelF&, const ViscF&, const void* src, void* dst,
                        const float* snu_in, float* snu_out, hipStream_t);
@@ -75,6 +76,9 @@ hipError_t launch_get(int storage, const Geo&, const void* buf, float* canon, hi
 hipError_t launch_set(int storage, const Geo&, void* buf, const float* canon, hipStream_t);
 hipError_t launch_reduce(int storage, const Geo&, const ModelF&, const ViscF&, const ForceF&, const void* buf,
                          const float* snu, double* partials, double* out, hipStream_t);
+PairPlan pair_plan(int storage, const Geo&, const ViscF&, const ForceF&);
+hipError_t launch_pair(const PairPlan&, const Geo&, const ModelF&, const ViscF&, const void* src, void* dst,
+                       const float* snu_in, float* snu_out, hipStream_t);
 }  // namespace d3q15
 
 // Fixed device scratch of the allocation-free adjoint sweep: room for one adjoint state of up
