@@ -156,7 +156,7 @@ lbm_status lbm_init(lbm_ctx** out, const lbm_params* p, void* f_a, void* f_b, fl
  * bit, as that of nsteps single steps.
  *  S_out        device float[6*N] (D3Q19, D3Q15) / [3*N] (D2Q9) or NULL: the strain (formula
  *               `strain_kind`) of the last step's pre-collision state, i.e. of the state at
- *               level n_end - 1 (steps before it may write theirs there on the way).
+ *               level n_end - 1.
  *  strain_kind  LBM_STRAIN_YU or LBM_STRAIN_CHAI (ignored when S_out is NULL).
  *  save         device float[nsteps*R*N] or NULL, R = lbm_save_planes(ctx) (D3Q19 only;
  *               LBM_EUNSUPPORTED otherwise):
