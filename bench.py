@@ -238,10 +238,10 @@ def leg(torch, capi, sim, nodes, steps, warmup, bytes_per_node, **extra):
     return out, r
 
 
-def pair_plan(nx, ny, nz, q=19):
+def pair_plan(nx, ny, nz, q=19, solve=False):
     """Rows of the tile with which the library takes two FP32 steps per launch (its launch rule
-    restated), 0 where it takes them singly. For the cases it groups: periodic, no body force,
-    constant viscosity or the lagged Smagorinsky model with the Yu strain."""
+    restated), 0 where it takes them singly. For the cases it groups: no body force, constant
+    viscosity or Smagorinsky (implicit: ``solve``) with the Yu strain."""
     least, rows = 0, 0
     for r in (13, 9):
         for chunks in range(1, min(64, nz) + 1):
@@ -252,18 +252,19 @@ def pair_plan(nx, ny, nz, q=19):
             if not rows or cost < least:
                 least, rows = cost, r
     n = nx * ny * nz
-    return rows if n > 1 << 18 and 100 * n >= (38 if n * q * 4 <= 1 << 27 else 60) * least else 0
+    fill = ((45, 70) if solve else (38, 60))[n * q * 4 > 1 << 27]
+    return rows if n > 1 << 18 and 100 * n >= fill * least else 0
 
 
-def les_step(n):
+def les_step(n, solve=False):
     """(kernel instance, bytes per node and step, source sha, steps per launch) of the FP32 LES step on n^3."""
-    rows = pair_plan(n, n, n)
+    rows = pair_plan(n, n, n, solve=solve)
     if not rows:
-        return step_kernel_name(n, n), 160, kernel_source_sha(), 1
+        return step_kernel_name(n, n), 152 if solve else 160, kernel_source_sha(), 1
     whole = "true" if step_kernel_name(n, n).split(", ")[2] == "2" else "false"
     stream = "false" if n ** 3 * 76 <= 1 << 27 or (n % 16 and n ** 3 * 76 > 1 << 28) else "true"
-    return (f"lbm::pair_kernel<lbm::d3q19::PairUpdate<1, {whole}>, {1024 if rows == 13 else 768}, 64, {rows}, "
-            f"{stream}>", 80, kernel_source_sha(PAIR_SOURCES), 2)
+    return (f"lbm::pair_kernel<lbm::d3q19::PairUpdate<{3 if solve else 1}, {whole}>, {1024 if rows == 13 else 768}, 64, "
+            f"{rows}, false, {stream}>", 76 if solve else 80, kernel_source_sha(PAIR_SOURCES), 2)
 
 
 def step_kernel_name(nx, ny, storage="f32", walls=False, corrected=False):
@@ -858,7 +859,8 @@ def main():
         pi.visc_kind = capi.LBM_VISC_SMAGORINSKY_IMPLICIT
         si = lbm.LBM(pi, lbm.rho_u_field(np.zeros((n, n, n)), u))
         log(f"FP32 {n}^3 implicit Smagorinsky")
-        extra["les256_implicit_smagorinsky"], _ = leg(torch, capi, si, N, K, W, 152, kernel=step_kernel_name(n, n))
+        ki = les_step(n, solve=True)
+        extra["les256_implicit_smagorinsky"], _ = leg(torch, capi, si, N, K, W, ki[1], kernel=ki[0])
         si.close()
         del si
         torch.cuda.empty_cache()

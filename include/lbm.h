@@ -148,8 +148,8 @@ lbm_status lbm_init(lbm_ctx** out, const lbm_params* p, void* f_a, void* f_b, fl
 
 /*
  * Advance nsteps steps of Eq. mrteq (collide with moment-space relaxation, Eq. mrteqvT,
- * then pull streaming), one fused kernel per step. D2Q9, and D3Q19 and D3Q15 in FP32 without walls, body
- * force or `save`, at constant viscosity or the lagged Smagorinsky model with the Yu strain (boxes
+ * then pull streaming), one fused kernel per step. D2Q9, and D3Q19 and D3Q15 in FP32 without body
+ * force or `save`, at constant viscosity or either Smagorinsky model with the Yu strain (boxes
  * beyond 2^18 nodes that the launch fills well), take their steps in groups of four
  * as two launches of two steps each (the intermediate level never leaves the chip: half the HBM
  * traffic, half the launches); the remaining steps run singly. The result is the same, bit for

@@ -14,7 +14,7 @@ namespace d3q15 {
 template <int KIND>
 struct PairUpdate {
   using Lat = d3q15::Lat;
-  static constexpr bool kLagged = KIND != 0;
+  static constexpr bool kLagged = KIND == 1;
   static __device__ __forceinline__ float run(float (&g)[Q], const ModelF& M, const ViscF& V, float snu_prev) {
 #pragma clang fp contract(off)
     const Pairs P = make_pairs(g);
@@ -53,6 +53,14 @@ struct PairUpdate {
       const float gamma = fast_sqrt(2.0f * fma3(2.0f, off, diag));
       snu = fast_rcp(fma3(3.0f, fma3(V.csmag2, gamma, V.nu0), 0.5f));
     }
+    if constexpr (KIND == 3) {
+      // implicit_rate: strain_yu at (s_e, 0) and at (0, 1)
+      const float a = M.s[1] * n1;
+      const float Pm[6] = {-a * (0.5f * ir), -(2.0f * a) * (0.25f * ir), -(2.0f * a) * (0.25f * ir), 0.0f, 0.0f, 0.0f};
+      const float A[6] = {-n9 * (0.5f * ir), -fma3(3.0f, n10, -n9) * (0.25f * ir), fma3(3.0f, n10, n9) * (0.25f * ir),
+                          -1.5f * n11 * ir,  -1.5f * n12 * ir,                    -1.5f * n13 * ir};
+      snu = implicit_smagorinsky(Pm, A, V.nu0, V.csmag2);
+    }
 
     // relaxation and back-transform (add_back_transform), w_k = dm_k / D_k
     constexpr float i4 = 1.0f / 40.0f, i9 = 1.0f / 12.0f;
@@ -90,8 +98,12 @@ PairPlan pair_plan(int storage, const Geo& G, const ViscF& V, const ForceF& Fo) 
 
 hipError_t launch_pair(const PairPlan& P, const Geo& G, const ModelF& M, const ViscF& V, const void* src, void* dst,
                        const float* snu_in, float* snu_out, hipStream_t st) {
-  return V.kind == 0 ? launch_march<PairUpdate<0>>(P, st, G, M, V, src, dst, snu_in, snu_out)
-                     : launch_march<PairUpdate<1>>(P, st, G, M, V, src, dst, snu_in, snu_out);
+  switch (V.kind) {
+    case 0: return launch_march<PairUpdate<0>>(P, st, G, M, V, src, dst, snu_in, snu_out);
+    case 1: return launch_march<PairUpdate<1>>(P, st, G, M, V, src, dst, snu_in, snu_out);
+    case 3: return launch_march<PairUpdate<3>>(P, st, G, M, V, src, dst, snu_in, snu_out);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 }  // namespace d3q15

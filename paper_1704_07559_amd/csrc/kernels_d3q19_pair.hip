@@ -18,7 +18,7 @@ namespace d3q19 {
 template <int KIND, bool XCHG>
 struct PairUpdate {
   using Lat = d3q19::Lat;
-  static constexpr bool kLagged = KIND != 0;
+  static constexpr bool kLagged = KIND == 1;
   static __device__ __forceinline__ float run(float (&g)[Q], const ModelF& M, const ViscF& V, float snu_prev) {
 #pragma clang fp contract(off)
     const Pairs P = make_pairs(g);
@@ -72,6 +72,15 @@ struct PairUpdate {
       const float gamma = fast_sqrt(2.0f * fma3(2.0f, off, diag));
       snu = fast_rcp(fma3(3.0f, fma3(V.csmag2, gamma, V.nu0), 0.5f));
     }
+    if constexpr (KIND == 3) {
+      // implicit_rate: strain_yu at (s_1, 0) and at (0, 1)
+      const float a = M.s[1] * n1, r76 = ir * (1.0f / 76.0f);
+      const float Pm[6] = {-a * (ir * (1.0f / 38.0f)), -(2.0f * a) * r76, -(2.0f * a) * r76, 0.0f, 0.0f, 0.0f};
+      const float A[6] = {-(19.0f * n9) * (ir * (1.0f / 38.0f)), (19.0f * fma3(-3.0f, n11, n9)) * r76,
+                          (19.0f * fma3(3.0f, n11, n9)) * r76,   -1.5f * n13 * ir,
+                          -1.5f * n14 * ir,                      -1.5f * n15 * ir};
+      snu = implicit_smagorinsky(Pm, A, V.nu0, V.csmag2);
+    }
 
     // relaxation, as w_k = dm_k / D_k
     const float w1 = M.sd[1] * n1, w2 = M.sd[2] * n2;
@@ -119,15 +128,22 @@ PairPlan pair_plan(int storage, const Geo& G, const ViscF& V, const ForceF& Fo) 
   return plan_pairs(Q, storage, G, V, Fo);
 }
 
+template <bool XCHG>
+static hipError_t launch_kind(const PairPlan& P, const Geo& G, const ModelF& M, const ViscF& V, const void* src, void* dst,
+                              const float* snu_in, float* snu_out, hipStream_t st) {
+  switch (V.kind) {
+    case 0: return launch_march<PairUpdate<0, XCHG>>(P, st, G, M, V, src, dst, snu_in, snu_out);
+    case 1: return launch_march<PairUpdate<1, XCHG>>(P, st, G, M, V, src, dst, snu_in, snu_out);
+    case 3: return launch_march<PairUpdate<3, XCHG>>(P, st, G, M, V, src, dst, snu_in, snu_out);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 hipError_t launch_pair(const PairPlan& P, const Geo& G, const ModelF& M, const ViscF& V, const void* src, void* dst,
                        const float* snu_in, float* snu_out, hipStream_t st) {
   const bool xchg = !packed_rows(G, sizeof(float)) && pull_mode(G, node_launch(G).block) == 2;
-  switch ((V.kind ? 1 : 0) + (xchg ? 2 : 0)) {
-    case 0: return launch_march<PairUpdate<0, false>>(P, st, G, M, V, src, dst, snu_in, snu_out);
-    case 1: return launch_march<PairUpdate<1, false>>(P, st, G, M, V, src, dst, snu_in, snu_out);
-    case 2: return launch_march<PairUpdate<0, true>>(P, st, G, M, V, src, dst, snu_in, snu_out);
-    default: return launch_march<PairUpdate<1, true>>(P, st, G, M, V, src, dst, snu_in, snu_out);
-  }
+  return xchg ? launch_kind<true>(P, G, M, V, src, dst, snu_in, snu_out, st)
+              : launch_kind<false>(P, G, M, V, src, dst, snu_in, snu_out, st);
 }
 
 }  // namespace d3q19

@@ -1,5 +1,5 @@
-// Two steps per launch for the 3D lattices (FP32 storage, periodic, no body force, constant viscosity or
-// the lagged Smagorinsky model with the Yu strain): the marching kernel, its launch rule and its launch.
+// Two steps per launch for the 3D lattices (FP32 storage, periodic or with walls, no body force, constant
+// viscosity or Smagorinsky, lagged or implicit, with the Yu strain): the marching kernel, its launch rule and its launch.
 // A lattice gives its node update as a type (Lat, kLagged, run).
 #pragma once
 #include <hip/hip_runtime.h>
@@ -27,9 +27,10 @@ __device__ __forceinline__ float fma3(float a, float b, float c) { return __buil
 // counted, 5.0 TB/s) and the vector unit side by side (0.45 of its issue rate).
 // us a step, against single steps, Smagorinsky: D3Q19 256^3 300 (418), 384^3 993 (1488), 128^3 44.3 (54.1),
 // 96^3 18.6 (24.8), D3Q15 256^3 249 (325), 200^3 157 (180), 96^3 16.0 (21.0); constant viscosity at 256^3
-// 278 (418) and 229 (323). Measured on the way, D3Q19 256^3: blocks dealt out over the XCDs in turn 325,
+// 278 (418) and 229 (323), implicit 296 (419) and 254 (320), Smagorinsky between walls 335 (446; its 64 x 13
+// instance spills 28 bytes) and 246 (337). Measured on the way, D3Q19 256^3: blocks dealt out over the XCDs in turn 325,
 // two barriers and one plane of LDS 310, without the early loads 304.
-template <class Update, int B, int WX, int HY, bool STREAM>
+template <class Update, int B, int WX, int HY, bool WALLS, bool STREAM>
 __global__ __launch_bounds__(B, B / 256) void pair_kernel(Geo G, PairPlan P, ModelF M, ViscF V,
                                                           const float* __restrict__ src, float* __restrict__ dst,
                                                           const float* __restrict__ snu_in,
@@ -47,7 +48,7 @@ __global__ __launch_bounds__(B, B / 256) void pair_kernel(Geo G, PairPlan P, Mod
   const int nz2 = min(P.planes, G.nz - z0);
   // level 1: this thread's node, wrapped
   const int xa = x0 - 1 + t % W1, ya = y0 - 1 + t / W1;
-  const bool on1 = t < N1 && xa <= G.nx && ya <= G.ny;
+  const bool on1 = t < N1 && xa <= G.nx && (WALLS ? ya >= 0 && ya < G.ny : ya <= G.ny);
   const int x1 = xa < 0 ? xa + G.nx : (xa >= G.nx ? xa - G.nx : xa);
   const int y1 = ya < 0 ? ya + G.ny : (ya >= G.ny ? ya - G.ny : ya);
   // level 2
@@ -60,11 +61,12 @@ __global__ __launch_bounds__(B, B / 256) void pair_kernel(Geo G, PairPlan P, Mod
     int z = z0 - 1 + k;
     z = z < 0 ? z + G.nz : (z >= G.nz ? z - G.nz : z);
     if (on1) {
-      pull_rows<Lat, float, false, true, true>(src, G, rows_of<Q, float>(G, x1, y1, z), y1, g);
+      pull_rows<Lat, float, WALLS, true, true>(src, G, rows_of<Q, float>(G, x1, y1, z), y1, g);
       if constexpr (LAGGED) rate = snu_in[node_index(G, x1, y1, z)];
     }
   };
   float hn[Q], hz[Q], hzz[Q];
+  float back[2] = {0.0f, 0.0f};
   float snu_l = 0.0f;
   load(0);
   for (int k = 0; k < nz2 + 2; ++k) {
@@ -85,14 +87,29 @@ __global__ __launch_bounds__(B, B / 256) void pair_kernel(Geo G, PairPlan P, Mod
         constexpr int i = ii;
         constexpr int cx = Lat::cx(i), cy = Lat::cy(i), cz = Lat::cz(i);
         const float v = sh[i][q - cx - cy * W1];
+        // a population that crosses a wall is the opposite one of the node itself, from the middle plane
+        const bool bounce = WALLS && crosses_wall<cy>(G, y2);
         if constexpr (cz < 0) {
           full[i] = v;
+          if constexpr (WALLS && cy != 0) {
+            constexpr int w = cx > 0 ? 1 : 0;  // (a node has one wall: boxes of one row are not filled well enough)
+            if (bounce) {
+              full[i] = back[w];
+              back[w] = sh[Lat::opp(i)][q];
+            }
+          }
         } else if constexpr (cz == 0) {
           full[i] = hn[i];
           hn[i] = v;
+          if constexpr (WALLS && cy != 0) {
+            if (bounce) hn[i] = sh[Lat::opp(i)][q];
+          }
         } else {
           full[i] = hzz[i];
           hzz[i] = hz[i];
+          if constexpr (WALLS && cy != 0) {
+            if (bounce) hzz[i] = sh[Lat::opp(i)][q];
+          }
           hz[i] = v;
         }
       });
@@ -128,21 +145,29 @@ inline bool pair_stream(const Geo& G, int q) {
 // One block per CU (LDS): 64 x 13 columns in 1024 threads (990 level-1 nodes), or 64 x 9 in 768 (726).
 constexpr int kPairCols = 64, kPairRowsBig = 13, kPairRowsSmall = 9;
 
+template <class Update, int B, int HY>
+hipError_t launch_tile(const PairPlan& P, hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V, const float* src,
+                       float* dst, const float* snu_in, float* snu_out) {
+  const bool stream = pair_stream(G, Update::Lat::Q);
+  const auto k = G.walls ? (stream ? pair_kernel<Update, B, kPairCols, HY, true, true>
+                                   : pair_kernel<Update, B, kPairCols, HY, true, false>)
+                         : (stream ? pair_kernel<Update, B, kPairCols, HY, false, true>
+                                   : pair_kernel<Update, B, kPairCols, HY, false, false>);
+  hipLaunchKernelGGL(k, dim3((P.tiles + kXcds - 1) / kXcds * kXcds), dim3(B), 0, st, G, P, M, V, src, dst, snu_in, snu_out);
+  return hipGetLastError();
+}
+
 template <class Update>
 hipError_t launch_march(const PairPlan& P, hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V,
                         const void* src, void* dst, const float* snu_in, float* snu_out) {
-  constexpr int Q = Update::Lat::Q, W = kPairCols, H1 = kPairRowsBig, H2 = kPairRowsSmall;
-  if (P.rows != H1 && P.rows != H2) return hipErrorInvalidValue;
   if (Update::kLagged != (snu_in != nullptr) || (snu_in != nullptr) != (snu_out != nullptr) ||
       (snu_in && snu_in == snu_out))
     return hipErrorInvalidValue;
-  const dim3 grid((P.tiles + kXcds - 1) / kXcds * kXcds), block(P.rows == H1 ? 1024 : 768);
-  const bool stream = pair_stream(G, Q);
-  const auto k = P.rows == H1 ? (stream ? pair_kernel<Update, 1024, W, H1, true> : pair_kernel<Update, 1024, W, H1, false>)
-                              : (stream ? pair_kernel<Update, 768, W, H2, true> : pair_kernel<Update, 768, W, H2, false>);
-  hipLaunchKernelGGL(k, grid, block, 0, st, G, P, M, V, static_cast<const float*>(src), static_cast<float*>(dst), snu_in,
-                     snu_out);
-  return hipGetLastError();
+  const float* s = static_cast<const float*>(src);
+  float* d = static_cast<float*>(dst);
+  if (P.rows == kPairRowsBig) return launch_tile<Update, 1024, kPairRowsBig>(P, st, G, M, V, s, d, snu_in, snu_out);
+  if (P.rows == kPairRowsSmall) return launch_tile<Update, 768, kPairRowsSmall>(P, st, G, M, V, s, d, snu_in, snu_out);
+  return hipErrorInvalidValue;
 }
 
 // The tile and the planes per block that cost the least: rounds of blocks over the CUs, times the planes
@@ -153,11 +178,12 @@ hipError_t launch_march(const PairPlan& P, hipStream_t st, const Geo& G, const M
 // 144^3, 0.62, 84 and 75, but 130^3, 0.54, 60.7 and 65.3). In the last-level cache a plane of a tile takes
 // half of that, and 0.38 is enough (80^3, 0.41, 17.7 and 13.4, D3Q15 15.0 and 11.9; 72^3, 0.34, 12.2 and
 // 11.6, D3Q15 9.9 and 10.4; 66^3, 0.27, 11.1 and 11.2). Up to 64^3 single steps run out of the L2s (7.1 and
-// 7.6 us).
+// 7.6 us). The implicit rate's solve hides under the memory time of single steps, not of pairs: 0.7 and
+// 0.45 (D3Q15 between walls 150^3, 0.68, 71.4 and 74.3, 80^3, 0.41, 14.3 and 14.6; 200^3, 0.72, 167 and 153).
 inline PairPlan plan_pairs(int q, int storage, const Geo& G, const ViscF& V, const ForceF& Fo) {
   PairPlan best{};
-  if (storage != 0 || G.walls || Fo.mode || Fo.strain_corr) return best;
-  if (V.kind != 0 && !(V.kind == 1 && !V.drive_chai)) return best;
+  if (storage != 0 || Fo.mode || Fo.strain_corr) return best;
+  if (V.kind == 2 || (V.kind != 0 && V.drive_chai)) return best;
   constexpr long long kCus = 256;
   long long least = 0;
   for (const int rows : {kPairRowsBig, kPairRowsSmall}) {
@@ -172,7 +198,8 @@ inline PairPlan plan_pairs(int q, int storage, const Geo& G, const ViscF& V, con
       best = PairPlan{rows, planes, static_cast<int>(tx), static_cast<int>(ty), static_cast<int>(tiles)};
     }
   }
-  const bool use = 100ll * G.N >= (pair_fits(G, q) ? 38 : 60) * least && G.N > (1u << 18);
+  const long long fill = V.kind == 3 ? (pair_fits(G, q) ? 45 : 70) : (pair_fits(G, q) ? 38 : 60);
+  const bool use = 100ll * G.N >= fill * least && G.N > (1u << 18);
   if (!use) return PairPlan{};
   return best;
 }

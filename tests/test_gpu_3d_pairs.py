@@ -1,5 +1,5 @@
 """D3Q19 and D3Q15 steps taken two per launch: bit for bit the single steps, on boxes of either tile, with
-partly filled tiles, wrapped single planes and rows, rows of every pull mode (exchanged, whole,
+partly filled tiles, periodic and between walls, wrapped single planes and rows, rows of every pull mode (exchanged, whole,
 packed, part rows), and buffers inside and beyond the last-level cache; the strain of the last step;
 records; and groups captured into a graph."""
 import pytest
@@ -12,7 +12,7 @@ SHAPES = [(80, 80, 80), (90, 90, 90), (128, 64, 64), (64, 64, 128), (40, 41, 256
           (97, 103, 60), (24, 24, 511), (128, 128, 128), (95, 133, 171), (150, 200, 250), (20, 300, 1024)]
 
 
-def _pair(lat, shape, visc):
+def _pair(lat, shape, visc, walls=0):
     import torch
     from paper_1704_07559_amd import capi, lbm
     nz, ny, nx = shape
@@ -20,7 +20,9 @@ def _pair(lat, shape, visc):
         s = [0.0, 1.19, 1.4, 0.0, 1.2, 0.0, 1.2, 0.0, 1.2, 1.7, 1.4, 1.7, 1.4, 1.7, 1.7, 1.7, 1.98, 1.96, 1.94]
     else:
         s = [0.0, 1.6, 1.2, 0.0, 1.55, 0.0, 1.6, 0.0, 1.65, 1.7, 1.7, 1.7, 1.7, 1.7, 1.2]
-    kw = dict(visc_kind=capi.LBM_VISC_SMAGORINSKY, visc_strain=capi.LBM_STRAIN_YU, nu0=0.01, c_smag=0.2) if visc else {}
+    kw = dict(visc_strain=capi.LBM_STRAIN_YU, nu0=0.01, c_smag=0.2, walls_y=walls,
+              visc_kind={"const": capi.LBM_VISC_CONST, "smag": capi.LBM_VISC_SMAGORINSKY,
+                         "implicit": capi.LBM_VISC_SMAGORINSKY_IMPLICIT}[visc])
     if lat == 19:
         kw.update(omega_eps=2.9, omega_epsj=-5.3, omega_xx=-0.47)
     p = capi.Params(lattice=lat, nx=nx, ny=ny, nz=nz, s=s, rho0=1.1, **kw)
@@ -36,13 +38,14 @@ def _same(a, b):
     return torch.equal(a.f_a, b.f_a) and (a.s_nu is None or torch.equal(a.s_nu, b.s_nu))
 
 
-@pytest.mark.parametrize("visc", [False, True], ids=["const", "smag"])
+@pytest.mark.parametrize("visc", ["const", "smag", "implicit"])
+@pytest.mark.parametrize("walls", [0, 1])
 @pytest.mark.parametrize("lat", [19, 15])
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
-def test_pairs_equal_single_steps(shape, lat, visc):
+def test_pairs_equal_single_steps(shape, lat, walls, visc):
     import torch
     from paper_1704_07559_amd import capi
-    a, b = _pair(lat, shape, visc)
+    a, b = _pair(lat, shape, visc, walls)
     Sa, Sb = torch.empty((6,) + shape, device="cuda"), torch.empty((6,) + shape, device="cuda")
     for n, emit in ((4, False), (8, True), (6, False)):  # (an even number of steps each: f_a is current)
         a.step(n, S_out=Sa if emit else None, strain_kind=capi.LBM_STRAIN_YU)
@@ -55,7 +58,7 @@ def test_pairs_equal_single_steps(shape, lat, visc):
     b.close()
 
 
-@pytest.mark.parametrize("visc", [False, True], ids=["const", "smag"])
+@pytest.mark.parametrize("visc", ["const", "smag"])
 @pytest.mark.parametrize("lat", [19, 15])
 def test_pairs_captured_in_a_graph_replay_exactly(lat, visc):
     import torch
