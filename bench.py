@@ -238,33 +238,39 @@ def leg(torch, capi, sim, nodes, steps, warmup, bytes_per_node, **extra):
     return out, r
 
 
-def pair_plan(nx, ny, nz, q=19, solve=False):
-    """Rows of the tile with which the library takes two FP32 steps per launch (its launch rule
-    restated), 0 where it takes them singly. For the cases it groups: no body force, constant
-    viscosity or Smagorinsky (implicit: ``solve``) with the Yu strain."""
-    least, rows = 0, 0
-    for r in (13, 9):
-        for chunks in range(1, min(64, nz) + 1):
-            planes = -(-nz // chunks)
-            tiles = -(-nx // 64) * -(-ny // r) * -(-nz // planes)
-            cost = -(-tiles // 256) * 256 * (planes + 2) * 64 * r
-            cost += cost // 20 if r == 9 else 0
-            if not rows or cost < least:
-                least, rows = cost, r
+def pair_plan(nx, ny, nz, q=19):
+    """Whether the library takes two FP32 steps per launch on a box (its launch rule restated), for the
+    cases it groups: no body force, constant viscosity or Smagorinsky with the Yu strain."""
     n = nx * ny * nz
-    fill = ((45, 70) if solve else (38, 60))[n * q * 4 > 1 << 27]
-    return rows if n > 1 << 18 and 100 * n >= fill * least else 0
+    if n <= 1 << 18:
+        return False
+    fits, aligned, least = n * q * 4 <= 1 << 27, nx % 16 == 0, None
+    for tx in range((nx + 125) // 126, (nx + 125) // 126 + 6):
+        cols = -(-nx // tx)
+        if not fits and aligned and tx > 1:
+            cols = -(-cols // 16) * 16
+        most = 1024 // (cols + 2) - 2
+        for rows in range(most, max(3, most // 2), -1) if cols <= 126 else ():
+            columns, waves = -(-nx // cols) * -(-ny // rows), ((cols + 2) * (rows + 2) + 63) // 64
+            plane = 217 * waves + (rows + 2) * (78 + (cols + 2) * 5 // 2)
+            for rounds in range(1, 9):
+                chunks = min(256 * rounds // columns, nz)
+                if chunks:
+                    planes = -(-nz // chunks)
+                    cost = -(-columns * -(-nz // planes) // 256) * (planes + 2) * plane
+                    least = cost if least is None else min(least, cost)
+    packed = nx <= 512 and (nx % 16 != 0 or (nx > 256 and nx % 64 != 0))
+    return least is not None and 500 * least <= (26 if not fits else 60 if packed else 37) * n
 
 
 def les_step(n, solve=False):
     """(kernel instance, bytes per node and step, source sha, steps per launch) of the FP32 LES step on n^3."""
-    rows = pair_plan(n, n, n, solve=solve)
-    if not rows:
+    if not pair_plan(n, n, n):
         return step_kernel_name(n, n), 152 if solve else 160, kernel_source_sha(), 1
     whole = "true" if step_kernel_name(n, n).split(", ")[2] == "2" else "false"
     stream = "false" if n ** 3 * 76 <= 1 << 27 or (n % 16 and n ** 3 * 76 > 1 << 28) else "true"
-    return (f"lbm::pair_kernel<lbm::d3q19::PairUpdate<{3 if solve else 1}, {whole}>, {1024 if rows == 13 else 768}, 64, "
-            f"{rows}, false, {stream}>", 76 if solve else 80, kernel_source_sha(PAIR_SOURCES), 2)
+    return (f"lbm::pair_kernel<lbm::d3q19::PairUpdate<{3 if solve else 1}, {whole}>, false, {stream}>",
+            76 if solve else 80, kernel_source_sha(PAIR_SOURCES), 2)
 
 
 def step_kernel_name(nx, ny, storage="f32", walls=False, corrected=False):

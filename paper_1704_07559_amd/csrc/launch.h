@@ -13,10 +13,10 @@ constexpr int kReduceBlocks = 4096;
 constexpr int kReduceVals = 8;
 
 // Two steps in one launch (the 3D lattices): src -> dst, the lagged s_nu field (if any) snu_in -> snu_out (distinct
-// buffers). The result equals two launch_step calls bit for bit. The plan (how blocks of `rows` rows
-// and `planes` planes cover the box) is empty, planes = 0, where single steps are to be taken.
+// buffers). The result equals two launch_step calls bit for bit. The plan (how blocks of `cols` x `rows`
+// columns and `planes` planes cover the box) is empty, planes = 0, where single steps are to be taken.
 struct PairPlan {
-  int rows, planes, tx, ty, tiles;
+  int cols, rows, planes, tx, ty, tiles, threads;
 };
 
 namespace d3q19 {

@@ -4,6 +4,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "internal.h"
 #include "launch.h"
 #include "static_for.h"
@@ -11,10 +13,11 @@
 namespace lbm {
 
 constexpr unsigned kXcds = 8;
+constexpr int kPairNodes = 1024;  // most level-1 nodes, a thread each, of a tile
 
 __device__ __forceinline__ float fma3(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 
-// A block owns WX x HY columns of nodes and marches through `planes` planes of z. Per plane, one
+// A block owns cols x rows (WX x HY) columns of nodes and marches through `planes` planes of z. Per plane, one
 // thread per node of the (WX + 2) x (HY + 2) level-1 tile takes the first step of that plane into
 // LDS; the second step of the plane below needs three level-1 planes, of which LDS holds the newest:
 // each thread has already gathered what its node pulls from the two before (the directions with
@@ -25,22 +28,21 @@ __device__ __forceinline__ float fma3(float a, float b, float c) { return __buil
 // What it saves is HBM traffic: a node is read once (and re-read at tile edges, mostly out of the L2) and
 // written once for two steps (D3Q19 160 bytes against 320). What is left is that traffic (178 bytes as
 // counted, 5.0 TB/s) and the vector unit side by side (0.45 of its issue rate).
-// us a step, against single steps, Smagorinsky: D3Q19 256^3 300 (418), 384^3 993 (1488), 128^3 44.3 (54.1),
-// 96^3 18.6 (24.8), D3Q15 256^3 249 (325), 200^3 157 (180), 96^3 16.0 (21.0); constant viscosity at 256^3
-// 278 (418) and 229 (323), implicit 296 (419) and 254 (320), Smagorinsky between walls 335 (446; its 64 x 13
-// instance spills 28 bytes) and 246 (337). Measured on the way, D3Q19 256^3: blocks dealt out over the XCDs in turn 325,
-// two barriers and one plane of LDS 310, without the early loads 304.
-template <class Update, int B, int WX, int HY, bool WALLS, bool STREAM>
-__global__ __launch_bounds__(B, B / 256) void pair_kernel(Geo G, PairPlan P, ModelF M, ViscF V,
+// us a step, against single steps, Smagorinsky: D3Q19 256^3 297 (418), 384x384x128 316 (490), 200^3 153 (217),
+// 128^3 42 (54), 96^3 17.0 (24.8), D3Q15 256^3 252 (325), 200^3 125 (180), 96^3 14.7 (21.0); constant viscosity
+// at 256^3 270 (418) and 231 (323), implicit 299 (419) and 262 (320), Smagorinsky between walls 335 (446; that
+// instance spills 44 bytes) and 246 (337). Measured on the way, D3Q19 256^3: blocks dealt out over the XCDs in
+// turn 325, two barriers and one plane of LDS 310, without the early loads 304.
+template <class Update, bool WALLS, bool STREAM>
+__global__ __launch_bounds__(kPairNodes, 4) void pair_kernel(Geo G, PairPlan P, ModelF M, ViscF V,
                                                           const float* __restrict__ src, float* __restrict__ dst,
                                                           const float* __restrict__ snu_in,
                                                           float* __restrict__ snu_out) {
   using Lat = typename Update::Lat;
   constexpr int Q = Lat::Q;
   constexpr bool LAGGED = Update::kLagged;
-  constexpr int W1 = WX + 2, H1 = HY + 2, N1 = W1 * H1;
-  static_assert(N1 <= B && WX * HY <= B, "a thread per node of either level");
-  __shared__ float planes[2][LAGGED ? Q + 1 : Q][N1];
+  const int WX = P.cols, HY = P.rows, W1 = WX + 2, N1 = W1 * (HY + 2);
+  __shared__ float planes[2][LAGGED ? Q + 1 : Q][kPairNodes];
   const int tile = (blockIdx.x % kXcds) * (gridDim.x / kXcds) + blockIdx.x / kXcds;
   if (tile >= P.tiles) return;
   const int t = threadIdx.x;
@@ -142,65 +144,65 @@ inline bool pair_stream(const Geo& G, int q) {
   return runs_aligned(G, sizeof(float), 64) || size_t(G.N) * sizeof(float) * q <= (size_t(1) << 28);
 }
 
-// One block per CU (LDS): 64 x 13 columns in 1024 threads (990 level-1 nodes), or 64 x 9 in 768 (726).
-constexpr int kPairCols = 64, kPairRowsBig = 13, kPairRowsSmall = 9;
-
-template <class Update, int B, int HY>
-hipError_t launch_tile(const PairPlan& P, hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V, const float* src,
-                       float* dst, const float* snu_in, float* snu_out) {
-  const bool stream = pair_stream(G, Update::Lat::Q);
-  const auto k = G.walls ? (stream ? pair_kernel<Update, B, kPairCols, HY, true, true>
-                                   : pair_kernel<Update, B, kPairCols, HY, true, false>)
-                         : (stream ? pair_kernel<Update, B, kPairCols, HY, false, true>
-                                   : pair_kernel<Update, B, kPairCols, HY, false, false>);
-  hipLaunchKernelGGL(k, dim3((P.tiles + kXcds - 1) / kXcds * kXcds), dim3(B), 0, st, G, P, M, V, src, dst, snu_in, snu_out);
-  return hipGetLastError();
-}
-
 template <class Update>
 hipError_t launch_march(const PairPlan& P, hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V,
                         const void* src, void* dst, const float* snu_in, float* snu_out) {
   if (Update::kLagged != (snu_in != nullptr) || (snu_in != nullptr) != (snu_out != nullptr) ||
       (snu_in && snu_in == snu_out))
     return hipErrorInvalidValue;
-  const float* s = static_cast<const float*>(src);
-  float* d = static_cast<float*>(dst);
-  if (P.rows == kPairRowsBig) return launch_tile<Update, 1024, kPairRowsBig>(P, st, G, M, V, s, d, snu_in, snu_out);
-  if (P.rows == kPairRowsSmall) return launch_tile<Update, 768, kPairRowsSmall>(P, st, G, M, V, s, d, snu_in, snu_out);
-  return hipErrorInvalidValue;
+  if (P.tiles <= 0 || (P.cols + 2) * (P.rows + 2) > P.threads || P.threads > kPairNodes) return hipErrorInvalidValue;
+  const bool stream = pair_stream(G, Update::Lat::Q);
+  const auto k = G.walls ? (stream ? pair_kernel<Update, true, true> : pair_kernel<Update, true, false>)
+                         : (stream ? pair_kernel<Update, false, true> : pair_kernel<Update, false, false>);
+  hipLaunchKernelGGL(k, dim3((P.tiles + kXcds - 1) / kXcds * kXcds), dim3(P.threads), 0, st, G, P, M, V,
+                     static_cast<const float*>(src), static_cast<float*>(dst), snu_in, snu_out);
+  return hipGetLastError();
 }
 
-// The tile and the planes per block that cost the least: rounds of blocks over the CUs, times the planes
-// that one marches through (two more than it stores), times the nodes of its tile (the small one costs 5 %
-// more a node: 128^3 45.2 us a step against 44.3). `fill` is the box's share of that product. A node of it
-// takes 32 ps of the chip for two steps and a node of a single step 26, so pairs need a fill of 0.6
-// (us a step, single and pairs, Smagorinsky: 171x133x95, fill 0.66, 58.8 and 54.2, 150^3, 0.68, 90 and 90,
-// 144^3, 0.62, 84 and 75, but 130^3, 0.54, 60.7 and 65.3). In the last-level cache a plane of a tile takes
-// half of that, and 0.38 is enough (80^3, 0.41, 17.7 and 13.4, D3Q15 15.0 and 11.9; 72^3, 0.34, 12.2 and
-// 11.6, D3Q15 9.9 and 10.4; 66^3, 0.27, 11.1 and 11.2). Up to 64^3 single steps run out of the L2s (7.1 and
-// 7.6 us). The implicit rate's solve hides under the memory time of single steps, not of pairs: 0.7 and
-// 0.45 (D3Q15 between walls 150^3, 0.68, 71.4 and 74.3, 80^3, 0.41, 14.3 and 14.6; 200^3, 0.72, 167 and 153).
+// The tile and the planes per block that take the least: rounds of blocks over the CUs (one block each,
+// for its LDS), times the planes one marches through (two more than it stores), times ns a plane.
+// A plane takes 217 ns per wave and 80 per 128-byte line of its tile's rows (64 x 13 6.9 us, 64 x 9 5.0,
+// 32 x 28 8.4); rows are cut into equal tiles, so that boxes of any width fill theirs (us a step against
+// tiles of 64 x 13 and 64 x 9 only, Smagorinsky: 200^3 153 and 195, 220^3 203 and 277, 171x133x95 51 and 54,
+// 96^3 17.0 and 18.9, 256^3 297 and 301). Streamed stores need tiles that meet between lines (256^3 in
+// three tiles of 86 columns 443). A single step takes about 26 ps a node out of HBM, in the last-level cache
+// 28 to 38 where runs are aligned and up to 50 where not, a pair there 0.6 to 0.8 of its estimate: pairs are
+// taken where the estimate is at most 26, 37 or 60 ps a node and step (us, single and pairs, estimate:
+// 512x24x24 9.0 and 8.7, 36 ps; 66^3 11.1 and 8.5, 38; 17x17x1000 14.8 and 9.7, 57; 150^3 90 and 83, 20).
+// Up to 2^18 nodes single steps run out of the L2s (64^3 7.1, two 64 x 9 tiles' planes 7.6).
 inline PairPlan plan_pairs(int q, int storage, const Geo& G, const ViscF& V, const ForceF& Fo) {
   PairPlan best{};
-  if (storage != 0 || Fo.mode || Fo.strain_corr) return best;
+  if (storage != 0 || Fo.mode || Fo.strain_corr || G.N <= (1u << 18)) return best;
   if (V.kind == 2 || (V.kind != 0 && V.drive_chai)) return best;
   constexpr long long kCus = 256;
   long long least = 0;
-  for (const int rows : {kPairRowsBig, kPairRowsSmall}) {
-    const long long tx = (G.nx + kPairCols - 1) / kPairCols, ty = (G.ny + rows - 1) / rows;
-    for (int chunks = 1; chunks <= 64 && chunks <= G.nz; ++chunks) {
-      const int planes = (G.nz + chunks - 1) / chunks;
-      const long long tiles = tx * ty * ((G.nz + planes - 1) / planes);
-      long long cost = (tiles + kCus - 1) / kCus * kCus * (planes + 2) * kPairCols * rows;
-      if (rows == kPairRowsSmall) cost += cost / 20;
-      if (best.planes && cost >= least) continue;
-      least = cost;
-      best = PairPlan{rows, planes, static_cast<int>(tx), static_cast<int>(ty), static_cast<int>(tiles)};
+  const bool whole = runs_aligned(G, sizeof(float), 64) && pair_stream(G, q);  // tiles meet between lines
+  const int tx0 = (G.nx + 125) / 126;
+  for (int tx = tx0; tx < tx0 + 6; ++tx) {
+    int cols = (G.nx + tx - 1) / tx;
+    if (whole && tx > 1) cols = (cols + 15) / 16 * 16;
+    if (cols > 126) continue;
+    const int most = kPairNodes / (cols + 2) - 2;
+    for (int rows = most; rows >= 4 && rows > most / 2; --rows) {
+      const long long ty = (G.ny + rows - 1) / rows, columns = ((G.nx + cols - 1) / cols) * ty;
+      const int waves = ((cols + 2) * (rows + 2) + 63) / 64;
+      const long long plane = 217 * waves + (rows + 2) * (78 + (cols + 2) * 5 / 2);
+      for (int rounds = 1; rounds <= 8; ++rounds) {
+        const long long chunks = std::min<long long>(kCus * rounds / columns, G.nz);
+        if (chunks < 1) continue;
+        const int planes = static_cast<int>((G.nz + chunks - 1) / chunks);
+        const long long tiles = columns * ((G.nz + planes - 1) / planes);
+        const long long cost = (tiles + kCus - 1) / kCus * (planes + 2) * plane;
+        if (best.planes && cost >= least) continue;
+        least = cost;
+        best = PairPlan{cols, rows, planes, static_cast<int>((G.nx + cols - 1) / cols), static_cast<int>(ty),
+                        static_cast<int>(tiles), waves * 64};
+      }
     }
   }
-  const long long fill = V.kind == 3 ? (pair_fits(G, q) ? 45 : 70) : (pair_fits(G, q) ? 38 : 60);
-  const bool use = 100ll * G.N >= fill * least && G.N > (1u << 18);
-  if (!use) return PairPlan{};
+  // least / N is 2 steps' ns a node
+  const long long ps = !pair_fits(G, q) ? 26 : packed_rows(G, sizeof(float)) ? 60 : 37;
+  if (500 * least > ps * G.N) return PairPlan{};
   return best;
 }
 

@@ -8,7 +8,7 @@ from tests._common import needs_gpu
 
 pytestmark = [pytest.mark.gpu, needs_gpu]
 
-SHAPES = [(80, 80, 80), (90, 90, 90), (128, 64, 64), (64, 64, 128), (40, 41, 256), (2, 512, 512), (1, 1024, 1024),
+SHAPES = [(66, 66, 66), (1000, 17, 17), (17, 17, 1000), (90, 90, 33), (80, 80, 80), (90, 90, 90), (128, 64, 64), (64, 64, 128), (40, 41, 256), (2, 512, 512), (1, 1024, 1024),
           (97, 103, 60), (24, 24, 511), (128, 128, 128), (95, 133, 171), (150, 200, 250), (20, 300, 1024)]
 
 
