@@ -26,8 +26,8 @@ __device__ __forceinline__ float fma3(float a, float b, float c) { return __buil
 // in turn, so that one barrier per plane is enough. Blocks that follow one another on an XCD are
 // neighbours, whose tile edges meet in its L2.
 // What it saves is HBM traffic: a node is read once (and re-read at tile edges, mostly out of the L2) and
-// written once for two steps (D3Q19 160 bytes against 320). What is left is that traffic (178 bytes as
-// counted, 5.0 TB/s) and the vector unit side by side (0.45 of its issue rate).
+// written once for two steps (D3Q19 160 bytes against 320). What is left is that traffic (166 bytes as
+// counted, 4.7 TB/s) and the vector unit side by side (0.48 of its issue rate).
 // us a step, against single steps, Smagorinsky: D3Q19 256^3 297 (418), 384x384x128 316 (490), 200^3 153 (217),
 // 128^3 42 (54), 96^3 17.0 (24.8), D3Q15 256^3 252 (325), 200^3 125 (180), 96^3 14.7 (21.0); constant viscosity
 // at 256^3 270 (418) and 231 (323), implicit 299 (419) and 262 (320), Smagorinsky between walls 335 (446; that
