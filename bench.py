@@ -253,12 +253,10 @@ def pair_plan(nx, ny, nz, q=19):
         for rows in range(most, max(3, most // 2), -1) if cols <= 126 else ():
             columns, waves = -(-nx // cols) * -(-ny // rows), ((cols + 2) * (rows + 2) + 63) // 64
             plane = 217 * waves + (rows + 2) * (78 + (cols + 2) * 5 // 2)
-            for rounds in range(1, 9):
-                chunks = min(256 * rounds // columns, nz)
-                if chunks:
-                    planes = -(-nz // chunks)
-                    cost = -(-columns * -(-nz // planes) // 256) * (planes + 2) * plane
-                    least = cost if least is None else min(least, cost)
+            for rounds in range(-(-columns // 256), -(-columns // 256) + 8):
+                planes = -(-nz // min(256 * rounds // columns, nz))
+                cost = -(-columns * -(-nz // planes) // 256) * (planes + 2) * plane
+                least = cost if least is None else min(least, cost)
     packed = nx <= 512 and (nx % 16 != 0 or (nx > 256 and nx % 64 != 0))
     return least is not None and 500 * least <= (26 if not fits else 60 if packed else 37) * n
 

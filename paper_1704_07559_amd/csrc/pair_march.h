@@ -187,9 +187,9 @@ inline PairPlan plan_pairs(int q, int storage, const Geo& G, const ViscF& V, con
       const long long ty = (G.ny + rows - 1) / rows, columns = ((G.nx + cols - 1) / cols) * ty;
       const int waves = ((cols + 2) * (rows + 2) + 63) / 64;
       const long long plane = 217 * waves + (rows + 2) * (78 + (cols + 2) * 5 / 2);
-      for (int rounds = 1; rounds <= 8; ++rounds) {
+      const long long first = (columns + kCus - 1) / kCus;
+      for (long long rounds = first; rounds < first + 8; ++rounds) {
         const long long chunks = std::min<long long>(kCus * rounds / columns, G.nz);
-        if (chunks < 1) continue;
         const int planes = static_cast<int>((G.nz + chunks - 1) / chunks);
         const long long tiles = columns * ((G.nz + planes - 1) / planes);
         const long long cost = (tiles + kCus - 1) / kCus * (planes + 2) * plane;
