@@ -1,15 +1,16 @@
-"""D3Q19 and D3Q15 steps taken two per launch: bit for bit the single steps, on boxes of either tile, with
-partly filled tiles, periodic and between walls, wrapped single planes and rows, rows of every pull mode (exchanged, whole,
-packed, part rows), and buffers inside and beyond the last-level cache; the strain of the last step;
-records; and groups captured into a graph."""
+"""D3Q19 and D3Q15 steps taken two per launch: bit for bit the single steps, on boxes whose tiles are of
+every kind of shape and partly filled, periodic and between walls, wrapped single planes and rows, rows
+of every pull mode (exchanged, whole, packed, part rows), and buffers inside and beyond the last-level
+cache; the strain of the last step; and groups captured into a graph."""
 import pytest
 
 from tests._common import needs_gpu
 
 pytestmark = [pytest.mark.gpu, needs_gpu]
 
-SHAPES = [(66, 66, 66), (1000, 17, 17), (17, 17, 1000), (90, 90, 33), (80, 80, 80), (90, 90, 90), (128, 64, 64), (64, 64, 128), (40, 41, 256), (2, 512, 512), (1, 1024, 1024),
-          (97, 103, 60), (24, 24, 511), (128, 128, 128), (95, 133, 171), (150, 200, 250), (20, 300, 1024)]
+SHAPES = [(66, 66, 66), (1000, 17, 17), (17, 17, 1000), (90, 90, 33), (80, 80, 80), (90, 90, 90), (128, 64, 64),
+          (64, 64, 128), (40, 41, 256), (2, 512, 512), (1, 1024, 1024), (97, 103, 60), (24, 24, 511),
+          (128, 128, 128), (95, 133, 171), (150, 200, 250), (20, 300, 1024)]
 
 
 def _pair(lat, shape, visc, walls=0):
