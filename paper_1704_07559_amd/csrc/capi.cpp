@@ -611,3 +611,11 @@ const char* lbm_status_string(int s) {
 const char* lbm_last_error(void) { return g_last_error.c_str(); }
 
 }  // extern "C"
+
+// Launch rules as the library applies them, for its tests and its benchmark: host code only, and not
+// part of the ABI (include/lbm.h).
+extern "C" {
+
+int lbm_internal_copy_is_one_launch(size_t bytes1, size_t bytes2) { return copy_fits_launch(bytes1, bytes2) ? 1 : 0; }
+
+}  // extern "C"

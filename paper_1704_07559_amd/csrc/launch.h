@@ -93,7 +93,13 @@ hipError_t noalloc_scratch(hipStream_t stream, void** out);
 // largest |j|^2 and leaves as max |u| = sqrt(.) / rho0.
 hipError_t launch_reduce_final(const double* partials, int nblocks, double* out, hipStream_t, double rho0 = 0.0);
 hipError_t launch_stream_copy(const void* src, void* dst, size_t bytes, hipStream_t);
-// Two device-to-device copies (the second may be empty) in one launch.
+// The copies take a block of 256 threads per 4096 bytes, and a launch has fewer than 2^32 threads
+// along x: just under 64 GiB. (A D3Q19 FP32 state with its rate field passes that at 859M nodes.)
+inline size_t copy_blocks(size_t bytes) { return (bytes + 4095) / 4096; }
+inline bool copy_fits_launch(size_t bytes1, size_t bytes2) {
+  return copy_blocks(bytes1) + copy_blocks(bytes2) <= 0xffffffffu / 256;
+}
+// Two device-to-device copies (the second may be empty) in one launch, or by the runtime where one does not do.
 hipError_t launch_copy2(const void* src1, void* dst1, size_t bytes1, const void* src2, void* dst2, size_t bytes2,
                         hipStream_t);
 

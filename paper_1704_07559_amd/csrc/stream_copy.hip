@@ -23,11 +23,10 @@ __global__ __launch_bounds__(256) void stream_copy_kernel(const v4f* __restrict_
 hipError_t launch_stream_copy(const void* src, void* dst, size_t bytes, hipStream_t st) {
   const size_t n4 = bytes / 16;
   if (n4 == 0) return hipSuccess;
-  const size_t blocks = (n4 + 255) / 256;
-  if (blocks > 0x7fffffffu) return hipErrorInvalidValue;
+  if (!copy_fits_launch(bytes, 0)) return hipErrorInvalidValue;
   // 5 blocks per CU instead of 8: the copy's own best (6.73 against 6.63 TB/s for 1 GiB; 6 blocks
   // 6.69, 4 blocks 6.38), so that it stays the ceiling the step is compared with
-  hipLaunchKernelGGL(stream_copy_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), lds_cap_bytes(5, 0), st,
+  hipLaunchKernelGGL(stream_copy_kernel, dim3(static_cast<unsigned>(copy_blocks(bytes))), dim3(256), lds_cap_bytes(5, 0), st,
                      static_cast<const v4f*>(src), static_cast<v4f*>(dst), n4);
   return hipGetLastError();
 }
@@ -86,12 +85,12 @@ hipError_t launch_copy2(const void* src1, void* dst1, size_t bytes1, const void*
                         hipStream_t st) {
   const CopyRange a{static_cast<const char*>(src1), static_cast<char*>(dst1), bytes1};
   const CopyRange b{static_cast<const char*>(src2), static_cast<char*>(dst2), bytes2};
-  const size_t na = (bytes1 + 4095) / 4096, nb = (bytes2 + 4095) / 4096;
+  const size_t na = copy_blocks(bytes1), nb = copy_blocks(bytes2);
   hipDevice_t dev = 0;
   const auto halves = [](const CopyRange& r) {
     return ((reinterpret_cast<uintptr_t>(r.src) | reinterpret_cast<uintptr_t>(r.dst) | r.bytes) & 1) == 0;
   };
-  const bool own = na + nb > 0 && na + nb <= 0x7fffffffu && halves(a) && halves(b) &&
+  const bool own = na + nb > 0 && copy_fits_launch(bytes1, bytes2) && halves(a) && halves(b) &&
                    hipStreamGetDevice(st, &dev) == hipSuccess && local_memory(src1, dev) && local_memory(dst1, dev) &&
                    (bytes2 == 0 || (local_memory(src2, dev) && local_memory(dst2, dev)));
   if (!own) {
