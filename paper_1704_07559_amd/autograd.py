@@ -13,7 +13,8 @@ sweep starts with; the reverse sweep reloads each earlier checkpoint, recomputes
 the records, then runs the adjoint steps backwards through the segment in one lbm_adjoint_steps
 call; lbm_init_adjoint maps the last adjoint state onto u0. Extra memory: ceil(N/every) - 1 states
 plus min(every, N) records. Without the last segment's recompute 20 steps at 128^3 in two segments
-take 3.67 ms instead of 4.42 (forward and backward).
+take 3.67 ms instead of 4.42 (forward and backward). An evaluation that no backward pass can follow
+(under no_grad, or of inputs without requires_grad) keeps neither states nor records.
 
 With ``record_all`` the forward sweep keeps every step's record instead (N records: 12 bytes
 per node and step for a constant viscosity, 40 for a strain-dependent one; 12.6 GB and
@@ -41,7 +42,9 @@ class StrainLossProblem:
 
 class StrainLoss(torch.autograd.Function):
     @staticmethod
-    def forward(ctx, u0: torch.Tensor, F: torch.Tensor, prob: StrainLossProblem):
+    def forward(ctx, u0: torch.Tensor, F: torch.Tensor, prob: StrainLossProblem, grad: bool | None = None):
+        # grad: whether a backward pass may follow (strain_loss says so: grad mode cannot be read here,
+        # and ctx.needs_input_grad holds under no_grad too); None, not known: states alone are kept.
         p0 = prob.params
         N = p0.N
         shape = (p0.nz, p0.ny, p0.nx)
@@ -51,14 +54,16 @@ class StrainLoss(torch.autograd.Function):
                            u0.detach().to(torch.float32).reshape(3, N)], dim=0).contiguous()
         sim = LBM(params, rho_u)
         checkpoints, rec = [], None
-        if prob.record_all:
+        if grad is False:
+            sim.step(prob.nsteps)
+        elif prob.record_all:
             rec = torch.empty((prob.nsteps, sim.save_planes, N), dtype=torch.float32, device=u0.device)
             if prob.nsteps:
                 sim.step(prob.nsteps, save=rec)
         else:
             for n0 in range(0, prob.nsteps, prob.every):
                 k = min(prob.every, prob.nsteps - n0)
-                if n0 + k < prob.nsteps or not any(ctx.needs_input_grad):
+                if n0 + k < prob.nsteps or not grad:
                     checkpoints.append(sim.save_state())
                     sim.step(k)
                 else:
@@ -83,13 +88,19 @@ class StrainLoss(torch.autograd.Function):
             ctx.rec = None
         else:
             rec, ctx.rec = ctx.rec, None
-            last = len(ctx.checkpoints) * prob.every  # the last segment's first step: its records are there
-            if prob.nsteps > last:
-                capi.lbm_adjoint_steps(sim.ctx, prob.nsteps - last, rec, lam, lam2, gF)
-            for state in reversed(ctx.checkpoints):
-                sim.load_state(state)
-                sim.step(prob.every, save=rec)
-                capi.lbm_adjoint_steps(sim.ctx, prob.every, rec, lam, lam2, gF)
+            end = prob.nsteps
+            if rec is None:
+                rec = torch.empty((min(prob.every, end), sim.save_planes, N), dtype=torch.float32, device=lam.device)
+            elif end:  # the last segment's records are there
+                k = end - len(ctx.checkpoints) * prob.every
+                capi.lbm_adjoint_steps(sim.ctx, k, rec, lam, lam2, gF)
+                end -= k
+            for seg in reversed(range(len(ctx.checkpoints))):
+                k = end - seg * prob.every
+                sim.load_state(ctx.checkpoints[seg])
+                sim.step(k, save=rec)
+                capi.lbm_adjoint_steps(sim.ctx, k, rec, lam, lam2, gF)
+                end -= k
         gu = torch.empty((3, N), dtype=torch.float32, device=lam.device)
         capi.lbm_init_adjoint(sim.ctx, ctx.rho_u, lam, gu)
         scale = gJ.to(torch.float32)
@@ -97,9 +108,10 @@ class StrainLoss(torch.autograd.Function):
         grad_F = (gF * scale).reshape((3,) + ctx.shape)
         sim.close()
         ctx.sim = None
-        return grad_u0, grad_F, None
+        return grad_u0, grad_F, None, None
 
 
 def strain_loss(u0: torch.Tensor, F: torch.Tensor, prob: StrainLossProblem) -> torch.Tensor:
     """J(u0, F) with gradients through the library's adjoint kernels."""
-    return StrainLoss.apply(u0, F, prob)
+    grad = torch.is_grad_enabled() and (u0.requires_grad or F.requires_grad)
+    return StrainLoss.apply(u0, F, prob, grad)
