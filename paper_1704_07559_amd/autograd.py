@@ -7,14 +7,17 @@ pre-collision state after N steps started from g^0 = g^eq(0, rho0 u0), with the 
 field F (Guo forcing), at the rate the viscosity model gives it (constant, lagged
 Smagorinsky or power law, implicit Smagorinsky). ``backward`` runs the hand-written adjoint
 kernels of the library: the forward sweep stores the state (populations and, for the lagged
-models, the s_nu field) every ``every`` steps, and the per-step adjoint record (3 floats per node
-for a constant viscosity: j; 10 for a strain-dependent one) of its last segment, which the reverse
-sweep starts with; the reverse sweep reloads each earlier checkpoint, recomputes its segment saving
-the records, then runs the adjoint steps backwards through the segment in one lbm_adjoint_steps
-call; lbm_init_adjoint maps the last adjoint state onto u0. Extra memory: ceil(N/every) - 1 states
-plus min(every, N) records. Without the last segment's recompute 20 steps at 128^3 in two segments
-take 3.67 ms instead of 4.42 (forward and backward). An evaluation that no backward pass can follow
-(under no_grad, or of inputs without requires_grad) keeps neither states nor records.
+models, the s_nu field) every ``every`` steps; the reverse sweep reloads each checkpoint,
+recomputes its segment saving the per-step adjoint record (3 floats per node for a constant
+viscosity: j; 10 for a strain-dependent one), then runs the adjoint steps backwards through
+the segment in one lbm_adjoint_steps call; lbm_init_adjoint maps the last adjoint state onto
+u0. The records of the last segment, which the reverse sweep starts with, are kept by the forward
+sweep in place of its checkpoint where they take no more memory than the states that the loss holds
+until its backward pass (the context's two and the earlier checkpoints), so that several
+losses held at once stay within twice the memory of their states. Without the last segment's
+recompute 20 steps at 128^3 in two segments take 3.67 ms instead of 4.42 (forward and backward).
+Peak extra memory: ceil(N/every) states plus ``every`` records. An evaluation that no backward
+pass can follow (under no_grad, or of inputs without requires_grad) keeps neither.
 
 With ``record_all`` the forward sweep keeps every step's record instead (N records: 12 bytes
 per node and step for a constant viscosity, 40 for a strain-dependent one; 12.6 GB and
@@ -63,13 +66,14 @@ class StrainLoss(torch.autograd.Function):
         else:
             for n0 in range(0, prob.nsteps, prob.every):
                 k = min(prob.every, prob.nsteps - n0)
-                if n0 + k < prob.nsteps or not grad:
+                # no more in records than the loss holds in states (the context's two and the checkpoints)
+                keep = grad and n0 + k == prob.nsteps and k * sim.save_planes <= 19 * (2 + len(checkpoints))
+                if keep:
+                    rec = torch.empty((k, sim.save_planes, N), dtype=torch.float32, device=u0.device)
+                    sim.step(k, save=rec)
+                else:
                     checkpoints.append(sim.save_state())
                     sim.step(k)
-                else:
-                    rec = torch.empty((min(prob.every, prob.nsteps), sim.save_planes, N), dtype=torch.float32,
-                                      device=u0.device)
-                    sim.step(k, save=rec)
         lam = torch.empty((sim.adjoint_planes, N), dtype=torch.float32, device=u0.device)
         gF = torch.zeros((3, N), dtype=torch.float32, device=u0.device)
         J = capi.lbm_strain_loss_seed(sim.ctx, lam, gF)
@@ -89,12 +93,13 @@ class StrainLoss(torch.autograd.Function):
         else:
             rec, ctx.rec = ctx.rec, None
             end = prob.nsteps
-            if rec is None:
-                rec = torch.empty((min(prob.every, end), sim.save_planes, N), dtype=torch.float32, device=lam.device)
-            elif end:  # the last segment's records are there
-                k = end - len(ctx.checkpoints) * prob.every
-                capi.lbm_adjoint_steps(sim.ctx, k, rec, lam, lam2, gF)
-                end -= k
+            if rec is not None:  # the last segment's
+                capi.lbm_adjoint_steps(sim.ctx, len(rec), rec, lam, lam2, gF)
+                end -= len(rec)
+            longest = min(prob.every, end)
+            if rec is None or len(rec) < longest:
+                rec = None  # (its memory is free for the longer one)
+                rec = torch.empty((longest, sim.save_planes, N), dtype=torch.float32, device=lam.device)
             for seg in reversed(range(len(ctx.checkpoints))):
                 k = end - seg * prob.every
                 sim.load_state(ctx.checkpoints[seg])

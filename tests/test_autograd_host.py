@@ -92,3 +92,22 @@ def test_the_reverse_sweep_takes_every_step_once_in_reverse(counter, entry, reco
     J.backward()
     assert sim.reverse == list(reversed(range(nsteps)))
     assert u0.grad is not None and F.grad is not None
+
+
+@pytest.mark.parametrize("visc", [capi.LBM_VISC_CONST, capi.LBM_VISC_SMAGORINSKY, capi.LBM_VISC_SMAGORINSKY_IMPLICIT])
+@pytest.mark.parametrize("nsteps,every", [(50, 50), (60, 50), (500, 50), (20, 10), (24, 24), (12, 12), (13, 13), (3, 3),
+                                          (4, 4), (1, 1)])
+def test_a_loss_holds_no_more_in_records_than_in_states(counter, nsteps, every, visc):
+    """Between the forward and the backward pass, where several losses may be alive at once."""
+    u0, F = _inputs(requires_grad=True)
+    J = autograd.strain_loss(u0, F, _problem(nsteps, every, visc))
+    sim, = counter.made
+    states = 2 + sum(what == "state" for what, _ in sim.log)
+    recorded = sum(n for what, n in sim.log if what == "record")
+    assert recorded * sim.save_planes <= 19 * states
+    last = nsteps - every * ((nsteps - 1) // every)
+    # the last segment is recorded whole, in place of its checkpoint, or not at all
+    assert recorded in (0, last) and states == 2 + -(-nsteps // every) - (recorded > 0)
+    assert (recorded > 0) == (last * sim.save_planes <= 19 * (2 + (nsteps - 1) // every))
+    J.backward()
+    assert sim.reverse == list(reversed(range(nsteps)))
