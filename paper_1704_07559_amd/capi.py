@@ -82,6 +82,10 @@ _sig = {
     "lbm_stream_copy": (ctypes.c_int, [_vp, _vp, ctypes.c_size_t, _vp]),
     "lbm_status_string": (ctypes.c_char_p, [ctypes.c_int]),
     "lbm_last_error": (ctypes.c_char_p, []),
+    # launch rules (see the end of this file)
+    "lbm_internal_pair_route": (ctypes.c_int, [ctypes.POINTER(lbm_params), ctypes.POINTER(ctypes.c_int)]),
+    "lbm_internal_take_pairs": (ctypes.c_int, [_ctx_p, ctypes.c_int, ctypes.c_int, ctypes.c_int, _vp]),
+    "lbm_internal_copy_is_one_launch": (ctypes.c_int, [ctypes.c_size_t, ctypes.c_size_t]),
 }
 for _name, (_res, _args) in _sig.items():
     _f = getattr(_lib, _name)
@@ -293,3 +297,21 @@ def lbm_status_string(status: int) -> str:
 
 def lbm_last_error() -> str:
     return _lib.lbm_last_error().decode()
+
+
+# --- launch rules, as the library applies them (host code; not part of the C ABI) -------------
+
+def pair_route(params: Params) -> dict:
+    """How the steps that lbm_step groups run on a box: ``steps`` per launch (1 or 2) and, for 2, the
+    ``tile`` (columns, rows, planes) of a block, the ``tiles`` and the ``threads`` per block."""
+    v = (ctypes.c_int * 6)()
+    _check(_lib.lbm_internal_pair_route(ctypes.byref(params.to_c()), v), "lbm_internal_pair_route")
+    return {"steps": v[0], "tile": (v[1], v[2], v[3]), "tiles": v[4], "threads": v[5]}
+
+
+def take_pairs(ctx: int, tile, snu_pair=None):
+    """Have a context's grouped steps run two per launch in tiles of (columns, rows, planes) nodes, whatever
+    the plan of its box; None: singly. ``snu_pair``: a second s_nu field for the lagged viscosity laws, to be
+    kept as long as the context."""
+    cols, rows, planes = tile or (0, 0, 0)
+    _check(_lib.lbm_internal_take_pairs(ctx, cols, rows, planes, _ptr(snu_pair)), "lbm_internal_take_pairs")

@@ -29,8 +29,7 @@ struct lbm_ctx {
   void* buf[2];
   int cur;          // buffer holding the current internal state
   float* snu;       // lagged s_nu field (variable viscosity) or nullptr
-  bool pairs;       // steps run two per launch where a call allows it
-  PairPlan pair_plan;  // (D3Q19, D3Q15)
+  PairPlan pair_plan;  // steps run two per launch where it is not empty and a call allows it
   float* snu_pair;  // two-step launches with a lagged s_nu: the field between two of them (in scratch's allocation)
   double* scratch;  // reduction partials (kReduceBlocks * 8) + result (8)
   long long step;
@@ -147,6 +146,15 @@ void fill_model(lbm_ctx* c) {
   c->F.strain_corr = (c->F.mode != 0 && p.strain_force_correction) ? 1 : 0;
 }
 
+// How the context's steps run two per launch (an empty plan: they do not).
+PairPlan plan_of(const lbm_ctx* c) {
+  switch (c->Q) {
+    case 19: return d3q19::pair_plan(c->p.storage, c->G, c->V, c->F);
+    case 15: return d3q15::pair_plan(c->p.storage, c->G, c->V, c->F);
+    default: return d2q9::pair_plan(c->p.storage, c->G, c->V);
+  }
+}
+
 // The adjoint and its per-step record are provided for D3Q19.
 bool has_adjoint(const lbm_ctx* c) { return c->Q == 19; }
 
@@ -235,14 +243,12 @@ lbm_status lbm_init(lbm_ctx** out, const lbm_params* p, void* f_a, void* f_b, fl
   // one allocation: the reduction scratch and, behind it, the second s_nu field of the two-step
   // launches (where there is no room for it, every step is a launch of its own)
   const size_t scratch_bytes = sizeof(double) * (kReduceBlocks + 1) * kReduceVals;
-  if (c->Q == 19) c->pair_plan = d3q19::pair_plan(p->storage, c->G, c->V, c->F);
-  else if (c->Q == 15) c->pair_plan = d3q15::pair_plan(p->storage, c->G, c->V, c->F);
-  c->pairs = c->Q == 9 ? d2q9::pair_supported(c->G) : c->pair_plan.planes > 0;
-  const size_t pair_bytes = c->pairs && c->snu ? sizeof(float) * N : 0;
+  c->pair_plan = plan_of(c);
+  const size_t pair_bytes = c->pair_plan.planes && c->snu ? sizeof(float) * N : 0;
   hipError_t e = hipMalloc(reinterpret_cast<void**>(&c->scratch), scratch_bytes + pair_bytes);
   if (e != hipSuccess && pair_bytes) {
     (void)hipGetLastError();
-    c->pairs = false;
+    c->pair_plan = PairPlan{};
     e = hipMalloc(reinterpret_cast<void**>(&c->scratch), scratch_bytes);
   }
   if (e != hipSuccess) {
@@ -250,7 +256,7 @@ lbm_status lbm_init(lbm_ctx** out, const lbm_params* p, void* f_a, void* f_b, fl
     (void)hipGetLastError();
     return fail(LBM_ENOMEM, std::string("hipMalloc of the reduction scratch failed: ") + hipGetErrorString(e));
   }
-  if (c->pairs && pair_bytes) c->snu_pair = reinterpret_cast<float*>(reinterpret_cast<char*>(c->scratch) + scratch_bytes);
+  if (c->pair_plan.planes && pair_bytes) c->snu_pair = reinterpret_cast<float*>(reinterpret_cast<char*>(c->scratch) + scratch_bytes);
   const hipStream_t s = as_stream(stream);
   switch (c->Q) {
     case 19: e = d3q19::launch_init(p->storage, c->G, c->M, c->buf[0], c->snu, rho_u, grad_u, s); break;
@@ -290,7 +296,7 @@ lbm_status lbm_step(lbm_ctx* c, int nsteps, float* S_out, int strain_kind, float
   // a run of 20 steps with the Yu strain, restore and diagnostics 136 us against 149; 600x201, 40 steps
   // with the Chai strain 260 and 265).
   int n = 0;
-  if (c->pairs && !save) {
+  if (c->pair_plan.planes && !save) {
     // two steps per launch, two launches at a time, so that the population buffers and the lagged
     // field end where single steps leave them (s_nu: field -> snu_pair -> field). The strain is the
     // last step's: D2Q9's last launch writes it itself, for the others that step runs singly.
@@ -307,7 +313,8 @@ lbm_status lbm_step(lbm_ctx* c, int nsteps, float* S_out, int strain_kind, float
           case 15: e = d3q15::launch_pair(c->pair_plan, c->G, c->M, c->V, src, dst, from, to, s); break;
           default:
             float* S = h == 1 && n + 4 == nsteps ? S_out : nullptr;
-            e = d2q9::launch_pair(c->p.storage, c->G, c->M, c->V, c->F, src, dst, from, to, S, S ? strain_kind : 0, s);
+            e = d2q9::launch_pair(c->pair_plan, c->p.storage, c->G, c->M, c->V, c->F, src, dst, from, to, S,
+                                  S ? strain_kind : 0, s);
         }
         if (e != hipSuccess) return hip_fail(e, "lbm_step");
         c->cur = 1 - c->cur;
@@ -615,6 +622,42 @@ const char* lbm_last_error(void) { return g_last_error.c_str(); }
 // Launch rules as the library applies them, for its tests and its benchmark: host code only, and not
 // part of the ABI (include/lbm.h).
 extern "C" {
+
+// How the steps of a box that run in groups of four run two per launch: steps per launch, columns, rows and planes
+// of a block's tile, tiles, threads.
+lbm_status lbm_internal_pair_route(const lbm_params* p, int out[6]) {
+  int Q;
+  size_t N;
+  const lbm_status st = check_params(p, &Q, &N);
+  if (st != LBM_OK) return st;
+  lbm_ctx c{};
+  c.p = *p;
+  c.Q = Q;
+  fill_model(&c);
+  const PairPlan P = plan_of(&c);
+  const int v[6] = {P.planes ? 2 : 1, P.cols, P.rows, P.planes, P.tiles, P.threads};
+  std::memcpy(out, v, sizeof(v));
+  return LBM_OK;
+}
+
+// Has a context's grouped steps run two per launch in tiles of cols x rows x planes, whether or not the plan of its
+// box says so (cols = 0: singly). snu_pair: the caller's second s_nu field, for the lagged laws.
+lbm_status lbm_internal_take_pairs(lbm_ctx* c, int cols, int rows, int planes, float* snu_pair) {
+  lbm_status st = check_ctx(c);
+  if (st != LBM_OK) return st;
+  PairPlan P{};
+  if (cols != 0) {
+    if (c->Q == 19) P = d3q19::pair_tiles(c->p.storage, c->G, c->V, c->F, cols, rows, planes);
+    else if (c->Q == 15) P = d3q15::pair_tiles(c->p.storage, c->G, c->V, c->F, cols, rows, planes);
+    else P = d2q9::pair_tiles(c->G, cols, rows);
+    if (!P.planes) return fail(LBM_EUNSUPPORTED, "no launch of two steps takes these tiles");
+    if (c->snu && (st = check_field(snu_pair, "snu_pair")) != LBM_OK) return st;
+    if (c->snu && snu_pair == c->snu) return fail(LBM_EINVAL, "snu_pair is the s_nu field");
+  }
+  c->pair_plan = P;
+  c->snu_pair = c->snu ? snu_pair : nullptr;
+  return LBM_OK;
+}
 
 int lbm_internal_copy_is_one_launch(size_t bytes1, size_t bytes2) { return copy_fits_launch(bytes1, bytes2) ? 1 : 0; }
 

@@ -536,9 +536,9 @@ hipError_t launch_step(int storage, const Geo& G, const ModelF& M, const ViscF& 
 }
 
 template <typename S, int B>
-static void launch_pair_b(hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V, const ForceF& Fo,
-                          const void* src, void* dst, const float* snu_in, float* snu_out, float* S_out, int emit) {
-  const int strips = pair_strips(G.nx, B), R = pair_rows<S>(strips, G.ny, B);
+static void launch_pair_b(const PairPlan& P, hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V,
+                          const ForceF& Fo, const void* src, void* dst, const float* snu_in, float* snu_out,
+                          float* S_out, int emit) {
   decltype(&pair_kernel<S, B, false, false, false>) k;
   switch ((G.walls ? 1 : 0) + (Fo.strain_corr ? 2 : 0) + (S_out ? 4 : 0)) {
     case 0: k = pair_kernel<S, B, false, false, false>; break;
@@ -550,32 +550,73 @@ static void launch_pair_b(hipStream_t st, const Geo& G, const ModelF& M, const V
     case 6: k = pair_kernel<S, B, false, true, true>; break;
     default: k = pair_kernel<S, B, true, true, true>; break;
   }
-  hipLaunchKernelGGL(k, dim3(strips, (G.ny + R - 1) / R, 1), dim3(B), 0, st, G, R, M, V, Fo, cb<S>(src),
-                     static_cast<S*>(dst), snu_in, snu_out, S_out, emit);
+  hipLaunchKernelGGL(k, dim3(P.tx, P.ty, 1), dim3(B), 0, st, G, P.rows, M, V, Fo, cb<S>(src), static_cast<S*>(dst),
+                     snu_in, snu_out, S_out, emit);
 }
 
 template <typename S>
-static void launch_pair_s(hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V, const ForceF& Fo,
-                          const void* src, void* dst, const float* snu_in, float* snu_out, float* S_out, int emit) {
-  if (pair_lanes(G.nx) == 128) launch_pair_b<S, 128>(st, G, M, V, Fo, src, dst, snu_in, snu_out, S_out, emit);
-  else launch_pair_b<S, 256>(st, G, M, V, Fo, src, dst, snu_in, snu_out, S_out, emit);
+static void launch_pair_s(const PairPlan& P, hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V,
+                          const ForceF& Fo, const void* src, void* dst, const float* snu_in, float* snu_out,
+                          float* S_out, int emit) {
+  if (P.threads == 128) launch_pair_b<S, 128>(P, st, G, M, V, Fo, src, dst, snu_in, snu_out, S_out, emit);
+  else launch_pair_b<S, 256>(P, st, G, M, V, Fo, src, dst, snu_in, snu_out, S_out, emit);
 }
 
-bool pair_supported(const Geo& G) {
-  // (the grid's y extent is at most 65535; boxes that tall have 6 rows or more per block)
-  return G.nz == 1 && (G.ny + 5) / 6 <= 65535;
+// Whether two steps per launch beat two launches. `filled` is the share of lanes that own a column, `work` the
+// level-1 nodes computed per node of the result; us per step below are single steps and pairs.
+// Up to 2^14 nodes (2^15 where half of the lanes are filled) both are a launch's latency (64x64 3.3 and 3.1).
+// Beyond, lanes without a column cost as much as the others (16x65536 18.6 and 34.9, 48x21845 15.9 and 19.6;
+// 64x16384, half filled, 14.7 and 14.2), and so do rows computed twice, most in boxes of one row per block,
+// whose single steps run out of the L2s (128x1024 3.8 and 4.5, 256x512 4.2 and 4.7, but 250x1048 6.2 and 5.2:
+// rows of a multiple of 64 nodes exchange through LDS in a single step, others are half again as slow there;
+// 250x16777 66 and 40). A 16-bit step has half the traffic to save (256x4096 12.2 and 14.9, 250x4194 15.6 and
+// 11.4), the power law and the implicit rate more arithmetic to do twice (power law FP32 90x11650 20.3 and
+// 19.7, 160x6553 17.0 and 20.2, FP16 250x1048 6.5 and 8.6; implicit FP16 64x16384 12.1 and 22.8).
+static bool pair_pays(int storage, const Geo& G, const ViscF& V, const PairPlan& P) {
+  const double lanes = static_cast<double>(P.threads) * P.tx, filled = G.nx / lanes;
+  const double work = (P.rows + 2) / (P.rows * filled);
+  const bool whole = G.nx % 64 == 0, wide = G.nx >= 256, half = storage != 0;
+  if (V.kind == 2) {
+    if (half) return !whole && work <= 1.5 && G.N >= (3u << 21);
+    return work <= (runs_aligned(G, 4, 64) ? 1.9 : 2.2);
+  }
+  // (16-bit rows of 256 nodes and more that are no multiple of 64 are pulled in parts by single steps)
+  const bool half_wide = half && wide && !whole && work <= 3.3;
+  if (half && V.kind == 3) return half_wide || (!whole && work <= 1.5);
+  if (G.N <= (1u << 14) || (G.N <= (1u << 15) && filled >= 0.5)) return true;
+  if (filled < (V.kind == 0 && !half ? 0.35 : 0.5)) return false;
+  if (half) return half_wide || (G.N >= 300000 && work <= (whole ? 1.7 : 3.1));
+  if (!wide && G.N < (11u << 14)) return false;
+  return work <= (!whole ? 3.9 : V.kind == 3 ? 2.5 : 3.1);
 }
 
-hipError_t launch_pair(int storage, const Geo& G, const ModelF& M, const ViscF& V, const ForceF& Fo, const void* src,
-                       void* dst, const float* snu_in, float* snu_out, float* S_out, int emit, hipStream_t st) {
-  if (!pair_supported(G)) return hipErrorInvalidValue;
+// The plan of `cols` (126 or 254) columns and `rows` rows per block, empty where no launch covers the box
+// with it (the grid's y extent is at most 65535).
+PairPlan pair_tiles(const Geo& G, int cols, int rows) {
+  if ((cols != 126 && cols != 254) || rows < 1 || G.nz != 1) return PairPlan{};
+  const int strips = pair_strips(G.nx, cols + 2), ty = (G.ny - 1) / rows + 1;
+  if (ty > 65535) return PairPlan{};
+  return PairPlan{cols, rows, 1, strips, ty, strips * ty, cols + 2};
+}
+
+PairPlan pair_plan(int storage, const Geo& G, const ViscF& V) {
+  const int B = pair_lanes(G.nx), strips = pair_strips(G.nx, B);
+  const int R = storage == 0 ? pair_rows<float>(strips, G.ny, B) : pair_rows<_Float16>(strips, G.ny, B);
+  const PairPlan P = pair_tiles(G, B - 2, R);
+  return P.planes && pair_pays(storage, G, V, P) ? P : PairPlan{};
+}
+
+hipError_t launch_pair(const PairPlan& P, int storage, const Geo& G, const ModelF& M, const ViscF& V, const ForceF& Fo,
+                       const void* src, void* dst, const float* snu_in, float* snu_out, float* S_out, int emit,
+                       hipStream_t st) {
+  if (P.planes != 1 || P.rows < 1 || (P.threads != 128 && P.threads != 256)) return hipErrorInvalidValue;
   if ((V.kind == 1 || V.kind == 2) != (snu_in != nullptr) || (snu_in != nullptr) != (snu_out != nullptr) ||
       (snu_in && snu_in == snu_out))
     return hipErrorInvalidValue;
   switch (storage) {
-    case 0: launch_pair_s<float>(st, G, M, V, Fo, src, dst, snu_in, snu_out, S_out, emit); break;
-    case 1: launch_pair_s<_Float16>(st, G, M, V, Fo, src, dst, snu_in, snu_out, S_out, emit); break;
-    case 2: launch_pair_s<__bf16>(st, G, M, V, Fo, src, dst, snu_in, snu_out, S_out, emit); break;
+    case 0: launch_pair_s<float>(P, st, G, M, V, Fo, src, dst, snu_in, snu_out, S_out, emit); break;
+    case 1: launch_pair_s<_Float16>(P, st, G, M, V, Fo, src, dst, snu_in, snu_out, S_out, emit); break;
+    case 2: launch_pair_s<__bf16>(P, st, G, M, V, Fo, src, dst, snu_in, snu_out, S_out, emit); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

@@ -128,6 +128,10 @@ PairPlan pair_plan(int storage, const Geo& G, const ViscF& V, const ForceF& Fo) 
   return plan_pairs(Q, storage, G, V, Fo);
 }
 
+PairPlan pair_tiles(int storage, const Geo& G, const ViscF& V, const ForceF& Fo, int cols, int rows, int planes) {
+  return march_tiles(storage, G, V, Fo, cols, rows, planes);
+}
+
 template <bool XCHG>
 static hipError_t launch_kind(const PairPlan& P, const Geo& G, const ModelF& M, const ViscF& V, const void* src, void* dst,
                               const float* snu_in, float* snu_out, hipStream_t st) {

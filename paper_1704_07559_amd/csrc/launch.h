@@ -12,7 +12,7 @@ namespace lbm {
 constexpr int kReduceBlocks = 4096;
 constexpr int kReduceVals = 8;
 
-// Two steps in one launch (the 3D lattices): src -> dst, the lagged s_nu field (if any) snu_in -> snu_out (distinct
+// Two steps in one launch: src -> dst, the lagged s_nu field (if any) snu_in -> snu_out (distinct
 // buffers). The result equals two launch_step calls bit for bit. The plan (how blocks of `cols` x `rows`
 // columns and `planes` planes cover the box) is empty, planes = 0, where single steps are to be taken.
 struct PairPlan {
@@ -41,6 +41,7 @@ hipError_t launch_loss_seed(int storage, const Geo&, const ModelF&, const ViscF&
 hipError_t launch_init_adjoint(const Geo&, const ModelF&, const float* rho_u, const float* lam0, float* grad_u0,
                                hipStream_t);
 PairPlan pair_plan(int storage, const Geo&, const ViscF&, const ForceF&);
+PairPlan pair_tiles(int storage, const Geo&, const ViscF&, const ForceF&, int cols, int rows, int planes);
 hipError_t launch_pair(const PairPlan&, const Geo&, const ModelF&, const ViscF&, const void* src, void* dst,
                        const float* snu_in, float* snu_out, hipStream_t);
 }  // namespace d3q19
@@ -56,13 +57,12 @@ hipError_t launch_get(int storage, const Geo&, const void* buf, float* canon, hi
 hipError_t launch_set(int storage, const Geo&, void* buf, const float* canon, hipStream_t);
 hipError_t launch_reduce(int storage, const Geo&, const ModelF&, const ViscF&, const ForceF&, const void* buf,
                          const float* snu, double* partials, double* out, hipStream_t);
-// Two steps in one launch (periodic or with walls in y): src -> dst, the lagged s_nu field (if
-// any) snu_in -> snu_out (distinct buffers);
-// S_out (or nullptr) receives the strain (emit 1 Yu, 2 Chai) of the second step. The result
-// equals two launch_step calls bit for bit.
-bool pair_supported(const Geo&);
-hipError_t launch_pair(int storage, const Geo&, const ModelF&, const ViscF&, const ForceF&, const void* src, void* dst,
-                       const float* snu_in, float* snu_out, float* S_out, int emit, hipStream_t);
+PairPlan pair_plan(int storage, const Geo&, const ViscF&);
+PairPlan pair_tiles(const Geo&, int cols, int rows);
+// S_out (or nullptr) receives the strain (emit 1 Yu, 2 Chai) of the second step.
+hipError_t launch_pair(const PairPlan&, int storage, const Geo&, const ModelF&, const ViscF&, const ForceF&,
+                       const void* src, void* dst, const float* snu_in, float* snu_out, float* S_out, int emit,
+                       hipStream_t);
 }  // namespace d2q9
 
 namespace d3q15 {
@@ -77,6 +77,7 @@ hipError_t launch_set(int storage, const Geo&, void* buf, const float* canon, hi
 hipError_t launch_reduce(int storage, const Geo&, const ModelF&, const ViscF&, const ForceF&, const void* buf,
                          const float* snu, double* partials, double* out, hipStream_t);
 PairPlan pair_plan(int storage, const Geo&, const ViscF&, const ForceF&);
+PairPlan pair_tiles(int storage, const Geo&, const ViscF&, const ForceF&, int cols, int rows, int planes);
 hipError_t launch_pair(const PairPlan&, const Geo&, const ModelF&, const ViscF&, const void* src, void* dst,
                        const float* snu_in, float* snu_out, hipStream_t);
 }  // namespace d3q15

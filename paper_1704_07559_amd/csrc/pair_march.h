@@ -159,6 +159,22 @@ hipError_t launch_march(const PairPlan& P, hipStream_t st, const Geo& G, const M
   return hipGetLastError();
 }
 
+// What the kernel computes.
+inline bool march_takes(int storage, const ViscF& V, const ForceF& Fo) {
+  return storage == 0 && !Fo.mode && V.kind != 2 && !(V.kind != 0 && V.drive_chai);
+}
+
+// The plan of tiles of cols x rows columns and `planes` planes, empty where the kernel does not take it.
+inline PairPlan march_tiles(int storage, const Geo& G, const ViscF& V, const ForceF& Fo, int cols, int rows,
+                            int planes) {
+  if (!march_takes(storage, V, Fo) || cols < 1 || rows < 1 || planes < 1) return PairPlan{};
+  if (cols > kPairNodes || rows > kPairNodes || (cols + 2) * (rows + 2) > kPairNodes) return PairPlan{};
+  const int tx = (G.nx - 1) / cols + 1, ty = (G.ny - 1) / rows + 1, tz = (G.nz - 1) / planes + 1;
+  const long long tiles = static_cast<long long>(tx) * ty * tz;
+  if (tiles > (1 << 20)) return PairPlan{};  // (far more than a plan takes)
+  return PairPlan{cols, rows, planes, tx, ty, static_cast<int>(tiles), ((cols + 2) * (rows + 2) + 63) / 64 * 64};
+}
+
 // The tile and the planes per block that take the least: rounds of blocks over the CUs (one block each,
 // for its LDS), times the planes one marches through (two more than it stores), times ns a plane.
 // A plane takes 217 ns per wave and 80 per 128-byte line of its tile's rows (64 x 13 6.9 us, 64 x 9 5.0,
@@ -172,8 +188,7 @@ hipError_t launch_march(const PairPlan& P, hipStream_t st, const Geo& G, const M
 // Up to 2^18 nodes single steps run out of the L2s (64^3 7.1, two 64 x 9 tiles' planes 7.6).
 inline PairPlan plan_pairs(int q, int storage, const Geo& G, const ViscF& V, const ForceF& Fo) {
   PairPlan best{};
-  if (storage != 0 || Fo.mode || Fo.strain_corr || G.N <= (1u << 18)) return best;
-  if (V.kind == 2 || (V.kind != 0 && V.drive_chai)) return best;
+  if (!march_takes(storage, V, Fo) || G.N <= (1u << 18)) return best;
   constexpr long long kCus = 256;
   long long least = 0;
   const bool whole = runs_aligned(G, sizeof(float), 64) && pair_stream(G, q);  // tiles meet between lines

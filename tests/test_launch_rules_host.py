@@ -1,13 +1,18 @@
 """Launch rules of the library at the edges where they change, asked from the library itself (host
 code; no GPU)."""
-import ctypes
-
 import pytest
 
+RATES = {19: [0.0, 1.19, 1.4, 0.0, 1.2, 0.0, 1.2, 0.0, 1.2, 1.7, 1.4, 1.7, 1.4, 1.7, 1.7, 1.7, 1.98, 1.98, 1.98],
+         15: [0.0, 1.6, 1.2, 0.0, 1.55, 0.0, 1.6, 0.0, 1.65, 1.7, 1.7, 1.7, 1.7, 1.7, 1.2],
+         9: [0.0, 1.6, 1.2, 0.0, 1.6, 0.0, 1.6, 1.7, 1.7]}
+LAWS = {"const": 0, "smag": 1, "power": 2, "implicit": 3}
 
-def _lib():
+
+def _params(lattice, box, law, storage=0, **kw):
     from paper_1704_07559_amd import capi
-    return capi._lib
+    nx, ny, nz = box
+    kw.setdefault("visc_strain", capi.LBM_STRAIN_CHAI if law == "power" else capi.LBM_STRAIN_YU)
+    return capi.Params(lattice=lattice, nx=nx, ny=ny, nz=nz, storage=storage, s=RATES[lattice], visc_kind=LAWS[law], **kw)
 
 
 @pytest.mark.parametrize("populations,rates,one_launch", [
@@ -20,8 +25,41 @@ def _lib():
     (76 * ((1 << 30) - 1), 4 * ((1 << 30) - 1), False),
 ])
 def test_state_copy_stays_within_one_launch(populations, rates, one_launch):
-    f = _lib().lbm_internal_copy_is_one_launch
-    f.argtypes, f.restype = [ctypes.c_size_t, ctypes.c_size_t], ctypes.c_int
-    assert bool(f(populations, rates)) is one_launch
+    from paper_1704_07559_amd import capi
+    assert bool(capi._lib.lbm_internal_copy_is_one_launch(populations, rates)) is one_launch
     blocks = -(-populations // 4096) - (-rates // 4096)
     assert (blocks * 256 < 1 << 32) is one_launch
+
+
+F32, F16 = 0, 1
+
+
+@pytest.mark.parametrize("box,law,storage,steps", [
+    # lanes without a column: narrow and tall boxes
+    ((1, 131072), "smag", F32, 1), ((4, 262144), "smag", F16, 1), ((16, 65536), "const", F32, 1),
+    ((32, 4096), "smag", F32, 1), ((48, 21845), "smag", F32, 1), ((1, 131072), "power", F16, 1),
+    # one row per block, rows of 64 n nodes, in boxes that single steps run out of the L2s
+    ((64, 2048), "smag", F32, 1), ((128, 1024), "smag", F32, 1), ((256, 512), "const", F32, 1),
+    ((128, 2879), "smag", 2, 1), ((128, 1119), "smag", F16, 1), ((56, 2411), "smag", F16, 1),
+    # twice the arithmetic
+    ((62, 770), "power", F32, 1), ((128, 256), "power", F32, 1), ((1000, 1048), "power", F16, 1),
+    ((64, 16384), "implicit", F16, 1), ((160, 1280), "implicit", F16, 1),
+    # a launch's latency
+    ((1, 1), "smag", F32, 2), ((64, 64), "const", F32, 2), ((100, 100), "smag", F16, 2), ((200, 100), "implicit", F32, 2),
+    # filled strips
+    ((250, 1048), "smag", F32, 2), ((250, 16777), "smag", F16, 2), ((600, 201), "implicit", F32, 2),
+    ((100, 10485), "smag", F32, 2), ((64, 65536), "smag", F32, 2), ((4096, 4096), "smag", F32, 2),
+    ((4096, 4096), "smag", F16, 2), ((4096, 4096), "const", 2, 2), ((3000, 3000), "power", F32, 2),
+    ((250, 6000), "implicit", F16, 2), ((3000, 3000), "power", F16, 2),
+    # more blocks of rows than a grid has
+    ((20, 400000), "const", F32, 1),
+])
+def test_d2q9_steps_per_launch(box, law, storage, steps):
+    from paper_1704_07559_amd import capi
+    r = capi.pair_route(_params(9, box + (1,), law, storage))
+    assert r["steps"] == steps
+    if steps == 2:
+        cols, rows, planes = r["tile"]
+        assert r["threads"] == cols + 2 and r["threads"] in (128, 256) and planes == 1
+        assert 1 <= rows <= (6 if storage == 0 else 12)
+        assert r["tiles"] == -(-box[0] // cols) * -(-box[1] // rows) and -(-box[1] // rows) <= 65535
