@@ -84,6 +84,7 @@ _sig = {
     "lbm_last_error": (ctypes.c_char_p, []),
     # launch rules (see the end of this file)
     "lbm_internal_pair_route": (ctypes.c_int, [ctypes.POINTER(lbm_params), ctypes.POINTER(ctypes.c_int)]),
+    "lbm_internal_step_route": (ctypes.c_int, [ctypes.POINTER(lbm_params), ctypes.POINTER(ctypes.c_int)]),
     "lbm_internal_take_pairs": (ctypes.c_int, [_ctx_p, ctypes.c_int, ctypes.c_int, ctypes.c_int, _vp]),
     "lbm_internal_copy_is_one_launch": (ctypes.c_int, [ctypes.c_size_t, ctypes.c_size_t]),
 }
@@ -307,6 +308,14 @@ def pair_route(params: Params) -> dict:
     v = (ctypes.c_int * 6)()
     _check(_lib.lbm_internal_pair_route(ctypes.byref(params.to_c()), v), "lbm_internal_pair_route")
     return {"steps": v[0], "tile": (v[1], v[2], v[3]), "tiles": v[4], "threads": v[5]}
+
+
+def step_route(params: Params) -> dict:
+    """How single steps of a D3Q19 box are launched: the pull ``mode`` (0 part rows, 1 whole rows, 2 whole rows
+    exchanged through LDS, 3 whole rows stored packed) and the ``blocks`` per CU (0: no cap)."""
+    v = (ctypes.c_int * 2)()
+    _check(_lib.lbm_internal_step_route(ctypes.byref(params.to_c()), v), "lbm_internal_step_route")
+    return {"mode": v[0], "blocks": v[1]}
 
 
 def take_pairs(ctx: int, tile, snu_pair=None):

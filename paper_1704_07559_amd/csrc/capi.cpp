@@ -621,22 +621,43 @@ const char* lbm_last_error(void) { return g_last_error.c_str(); }
 
 // Launch rules as the library applies them, for its tests and its benchmark: host code only, and not
 // part of the ABI (include/lbm.h).
+namespace {
+
+// A context without buffers, for what depends on the parameters alone.
+lbm_status model_of(const lbm_params* p, lbm_ctx* c) {
+  size_t N;
+  const lbm_status st = check_params(p, &c->Q, &N);
+  if (st != LBM_OK) return st;
+  c->p = *p;
+  fill_model(c);
+  return LBM_OK;
+}
+
+}  // namespace
+
 extern "C" {
 
 // How the steps of a box that run in groups of four run two per launch: steps per launch, columns, rows and planes
 // of a block's tile, tiles, threads.
 lbm_status lbm_internal_pair_route(const lbm_params* p, int out[6]) {
-  int Q;
-  size_t N;
-  const lbm_status st = check_params(p, &Q, &N);
-  if (st != LBM_OK) return st;
   lbm_ctx c{};
-  c.p = *p;
-  c.Q = Q;
-  fill_model(&c);
+  const lbm_status st = model_of(p, &c);
+  if (st != LBM_OK) return st;
   const PairPlan P = plan_of(&c);
   const int v[6] = {P.planes ? 2 : 1, P.cols, P.rows, P.planes, P.tiles, P.threads};
   std::memcpy(out, v, sizeof(v));
+  return LBM_OK;
+}
+
+// How a D3Q19 box's single steps are launched: pull mode, blocks per CU (0: no cap).
+lbm_status lbm_internal_step_route(const lbm_params* p, int out[2]) {
+  lbm_ctx c{};
+  const lbm_status st = model_of(p, &c);
+  if (st != LBM_OK) return st;
+  if (c.Q != 19) return fail(LBM_EUNSUPPORTED, "the step's route is told for D3Q19 only");
+  const StepRoute r = d3q19::step_route(c.p.storage, c.G, c.V, c.F);
+  out[0] = r.mode;
+  out[1] = r.blocks;
   return LBM_OK;
 }
 

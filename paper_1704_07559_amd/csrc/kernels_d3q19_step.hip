@@ -209,10 +209,30 @@ __global__ __launch_bounds__(XMODE == 3 ? kMaxPackedBlock : kMaxBlock, (kMinWave
   }
 }
 
+// Blocks per CU, 0 for as many as the registers allow (5 in FP32). FP32: fewer in the two shapes where that was
+// measured faster. Whole 256-node rows, us a step: 4 blocks (256^3 Smagorinsky 423 and 429 with 5; power law
+// between walls 422 and 415, but 3 blocks 465), in large boxes without walls or force 3 (256^3 416, constant
+// viscosity 414 and 422 with 4; but 256 x 256 x 4, 4 blocks to a CU, 10.2 and 7.4, and between walls with a
+// force 5 % more at every size). 128 x 2 part rows: 4 blocks, +1.8 % at 384^3. Whole 128-node rows (the 128 x
+// 128 x 512 channel) ran as fast uncapped and 4.4 % slower capped, so other shapes keep their occupancy. The
+// 16-bit steps want more waves, not fewer.
+static StepRoute route_of(size_t elem, const Launch& L, const Geo& G, const ViscF& V, const ForceF& Fo) {
+  if (packed_rows(G, elem)) return StepRoute{3, 0};
+  StepRoute r{pull_mode(G, L.block), 0};
+  if (elem == 4) {
+    if (r.mode == 2 && L.block.x == 256 && L.block.y == 1)
+      r.blocks = G.N >= (1u << 23) && !G.walls && !Fo.mode && V.kind != 2 ? 3 : 4;
+    else if (r.mode == 0 && L.block.x == 128 && L.block.y == 2)
+      r.blocks = 4;
+  }
+  return r;
+}
+
 template <typename S, bool CORR>
 static void launch_step_c(bool walls, const Launch& L, hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V,
                           const ForceF& Fo, const StepIO& io) {
-  if (packed_rows(G, sizeof(S))) {
+  const StepRoute route = route_of(sizeof(S), L, G, V, Fo);
+  if (route.mode == 3) {
     const Launch R = packed_launch(G);
     StepIO pio = io;
     pio.stream = packed_stream(G, Q, sizeof(S));
@@ -225,18 +245,8 @@ static void launch_step_c(bool walls, const Launch& L, hipStream_t st, const Geo
     else hipLaunchKernelGGL((step_kernel<S, false, 3, CORR>), R.grid, R.block, chunk, st, G, M, V, Fo, pio);
     return;
   }
-  const int mode = pull_mode(G, L.block);
-  // FP32: fewer blocks per CU than the 5 its registers allow, in the two shapes where that was
-  // measured faster (whole 256-node rows: 3 blocks, 415 us at 256^3 against 419 with 4 and 425 with
-  // 5, constant viscosity 419 against 427; 128 x 2 part rows: 4 blocks, +1.8 % at 384^3); whole
-  // 128-node rows (the 128 x 128 x 512 channel) ran as fast uncapped and 4.4 % slower capped, so
-  // other shapes keep their occupancy. The 16-bit steps want more waves, not fewer.
-  size_t lds = 0;
-  if constexpr (sizeof(S) == 4) {
-    if (mode == 2 && L.block.x == 256 && L.block.y == 1) lds = lds_cap_bytes(3, staged_lds_bytes<Lat>());
-    else if (mode == 0 && L.block.x == 128 && L.block.y == 2) lds = lds_cap_bytes(4, 0);
-  }
-  switch (mode + (walls ? 3 : 0)) {
+  const size_t lds = lds_cap_bytes(route.blocks, route.mode == 2 ? staged_lds_bytes<Lat>() : 0);
+  switch (route.mode + (walls ? 3 : 0)) {
     case 0: hipLaunchKernelGGL((step_kernel<S, false, 0, CORR>), L.grid, L.block, lds, st, G, M, V, Fo, io); break;
     case 1: hipLaunchKernelGGL((step_kernel<S, false, 1, CORR>), L.grid, L.block, lds, st, G, M, V, Fo, io); break;
     case 2: hipLaunchKernelGGL((step_kernel<S, false, 2, CORR>), L.grid, L.block, lds, st, G, M, V, Fo, io); break;
@@ -253,8 +263,7 @@ static void launch_step_t(bool walls, const Launch& L, hipStream_t st, const Geo
   else launch_step_c<S, false>(walls, L, st, G, M, V, Fo, io);
 }
 
-hipError_t launch_step(int storage, const Geo& G, const ModelF& M, const ViscF& V, const ForceF& Fo, const StepIO& io,
-                       hipStream_t st) {
+static Launch step_launch(int storage, const Geo& G) {
   Launch L = node_launch(G);
   // 16-bit storage: part-row blocks hold one row segment (128 x 1 ran 1 % faster than 128 x 2
   // in FP16 and BF16 at 384^3, while FP32 runs 3 % faster with two rows)
@@ -262,6 +271,16 @@ hipError_t launch_step(int storage, const Geo& G, const ModelF& M, const ViscF& 
     L.block.y = 1;
     L.grid.y = G.ny;
   }
+  return L;
+}
+
+StepRoute step_route(int storage, const Geo& G, const ViscF& V, const ForceF& Fo) {
+  return route_of(storage == 0 ? 4 : 2, step_launch(storage, G), G, V, Fo);
+}
+
+hipError_t launch_step(int storage, const Geo& G, const ModelF& M, const ViscF& V, const ForceF& Fo, const StepIO& io,
+                       hipStream_t st) {
+  const Launch L = step_launch(storage, G);
   switch (storage) {
     case 0: launch_step_t<float>(G.walls != 0, L, st, G, M, V, Fo, io); break;
     case 1: launch_step_t<_Float16>(G.walls != 0, L, st, G, M, V, Fo, io); break;

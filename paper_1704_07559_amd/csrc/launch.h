@@ -19,7 +19,14 @@ struct PairPlan {
   int cols, rows, planes, tx, ty, tiles, threads;
 };
 
+// How a single step is launched: the pull mode (pull_mode, 3 for packed rows) and the blocks per CU (0: as many
+// as the registers allow).
+struct StepRoute {
+  int mode, blocks;
+};
+
 namespace d3q19 {
+StepRoute step_route(int storage, const Geo&, const ViscF&, const ForceF&);
 hipError_t launch_init(int storage, const Geo&, const ModelF&, void* buf, float* snu, const float* rho_u,
                        const float* grad_u, hipStream_t);
 hipError_t launch_step(int storage, const Geo&, const ModelF&, const ViscF&, const ForceF&, const StepIO&,

@@ -63,3 +63,20 @@ def test_d2q9_steps_per_launch(box, law, storage, steps):
         assert r["threads"] == cols + 2 and r["threads"] in (128, 256) and planes == 1
         assert 1 <= rows <= (6 if storage == 0 else 12)
         assert r["tiles"] == -(-box[0] // cols) * -(-box[1] // rows) and -(-box[1] // rows) <= 65535
+
+
+@pytest.mark.parametrize("box,law,storage,more,mode,blocks", [
+    # whole 256-node rows: three blocks per CU in large boxes without walls or force
+    ((256, 256, 256), "smag", F32, {}, 2, 3), ((256, 256, 256), "const", F32, {}, 2, 3),
+    ((256, 256, 128), "implicit", F32, {}, 2, 3), ((256, 256, 127), "implicit", F32, {}, 2, 4),
+    ((256, 256, 4), "smag", F32, {}, 2, 4), ((256, 64, 32), "const", F32, {}, 2, 4),
+    ((256, 256, 256), "power", F32, {}, 2, 4), ((256, 256, 256), "smag", F32, {"walls_y": 1}, 2, 4),
+    ((256, 256, 256), "smag", F32, {"force": (1e-6, 0.0, 0.0)}, 2, 4),
+    ((256, 256, 256), "smag", F16, {}, 2, 0),
+    ((128, 128, 512), "power", F32, {"walls_y": 1}, 2, 0), ((384, 384, 384), "smag", F32, {}, 0, 4),
+    ((384, 384, 384), "smag", F16, {}, 0, 0), ((96, 96, 96), "smag", F32, {}, 1, 0),
+    ((32, 32, 32), "const", F32, {}, 1, 0), ((64, 6, 64), "const", F32, {}, 1, 0),
+])
+def test_d3q19_step_launch(box, law, storage, more, mode, blocks):
+    from paper_1704_07559_amd import capi
+    assert capi.step_route(_params(19, box, law, storage, **more)) == {"mode": mode, "blocks": blocks}
