@@ -312,10 +312,11 @@ def pair_route(params: Params) -> dict:
 
 def step_route(params: Params) -> dict:
     """How single steps of a D3Q19 box are launched: the pull ``mode`` (0 part rows, 1 whole rows, 2 whole rows
-    exchanged through LDS, 3 whole rows stored packed) and the ``blocks`` per CU (0: no cap)."""
-    v = (ctypes.c_int * 2)()
+    exchanged through LDS, 3 whole rows stored packed), the ``blocks`` per CU (0: no cap), and whether mode 2
+    loads the lagged rate ``late``, at its use."""
+    v = (ctypes.c_int * 3)()
     _check(_lib.lbm_internal_step_route(ctypes.byref(params.to_c()), v), "lbm_internal_step_route")
-    return {"mode": v[0], "blocks": v[1]}
+    return {"mode": v[0], "blocks": v[1], "late": bool(v[2])}
 
 
 def take_pairs(ctx: int, tile, snu_pair=None):

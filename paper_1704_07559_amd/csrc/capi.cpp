@@ -649,8 +649,8 @@ lbm_status lbm_internal_pair_route(const lbm_params* p, int out[6]) {
   return LBM_OK;
 }
 
-// How a D3Q19 box's single steps are launched: pull mode, blocks per CU (0: no cap).
-lbm_status lbm_internal_step_route(const lbm_params* p, int out[2]) {
+// How a D3Q19 box's single steps are launched: pull mode, blocks per CU (0: no cap), rate loaded at its use (0, 1).
+lbm_status lbm_internal_step_route(const lbm_params* p, int out[3]) {
   lbm_ctx c{};
   const lbm_status st = model_of(p, &c);
   if (st != LBM_OK) return st;
@@ -658,6 +658,7 @@ lbm_status lbm_internal_step_route(const lbm_params* p, int out[2]) {
   const StepRoute r = d3q19::step_route(c.p.storage, c.G, c.V, c.F);
   out[0] = r.mode;
   out[1] = r.blocks;
+  out[2] = r.late ? 1 : 0;
   return LBM_OK;
 }
 

@@ -164,14 +164,19 @@ __device__ __forceinline__ void node_update(float (&g)[Q], unsigned self, const 
 // The fused step: one thread per node
 // ------------------------------------------------------------------------------------------
 // XMODE: how a block pulls along x (pull_mode: 0 part rows, 1 whole rows, 2 whole rows with
-// the LDS exchange, 3 whole rows, cached loads and packed stores). CORR: the force-corrected strain (a separate instance, so that the plain
+// the LDS exchange, 3 whole rows, cached loads and packed stores), 4 as 2 with the lagged rate
+// loaded at its use. CORR: the force-corrected strain (a separate instance, so that the plain
 // step keeps its register budget).
 // FP16 storage without the LDS exchange (whose x-shifted values arrive through LDS as FP32)
 // keeps the pulled values packed; that instance fits 80 VGPRs without spilling and is asked
 // for 6 waves per SIMD (the 16-bit step moves half the bytes per wave, so it needs the extra
 // wave in flight: 4 instead of 5 waves cost it 6.5 %, 6 instead of 5 gained 3.7 %).
 template <typename S, int XMODE>
-constexpr bool kPackHalves = Codec<S>::kMixedFma && XMODE != 2;
+constexpr bool kPackHalves = Codec<S>::kMixedFma && XMODE != 2 && XMODE != 4;
+// Where the lagged rate is loaded ahead of its use (see node_update). FP16 part rows gain nothing from it and lose
+// on ragged rows (1000x200x40 153 us a step against 144, 384x384x96 188 and 187).
+template <typename S, int XMODE>
+constexpr bool kRateAhead = XMODE == 2 || XMODE == 3 || (XMODE == 0 && !kPackHalves<S, XMODE>);
 template <typename S, int XMODE, bool CORR>
 constexpr int kMinWavesPerEU = (kPackHalves<S, XMODE> && !CORR && XMODE != 3) ? 6 : 1;
 
@@ -197,14 +202,15 @@ __global__ __launch_bounds__(XMODE == 3 ? kMaxPackedBlock : kMaxBlock, (kMinWave
     const Rows<Q, S> r = rows_of<Q, S>(G, x, y, z);
     const unsigned self = node_index(G, x, y, z);
     float g[Q], snu_ahead = 0.0f;
-    if constexpr (XMODE == 2) {
-      if (io.snu) snu_ahead = io.snu[self];
+    constexpr bool ahead = kRateAhead<S, XMODE>;
+    if constexpr (XMODE == 2 || XMODE == 4) {
+      if (ahead && io.snu) snu_ahead = io.snu[self];
       pull_rows_staged<Lat, S, WALLS>(static_cast<const S*>(io.src), G, r, y, g);
     } else {
       pull_rows<Lat, S, WALLS, XMODE == 1>(static_cast<const S*>(io.src), G, r, y, g);
-      if (XMODE != 1 && io.snu) snu_ahead = io.snu[self];
+      if (ahead && io.snu) snu_ahead = io.snu[self];
     }
-    node_update<CORR, kPackHalves<S, XMODE>, XMODE != 1>(g, self, G, M, V, Fo, io, snu_ahead);
+    node_update<CORR, kPackHalves<S, XMODE>, ahead>(g, self, G, M, V, Fo, io, snu_ahead);
     store_rows<Q>(static_cast<S*>(io.dst), G, r, g);
   }
 }
@@ -217,14 +223,22 @@ __global__ __launch_bounds__(XMODE == 3 ? kMaxPackedBlock : kMaxBlock, (kMinWave
 // 128 x 512 channel) ran as fast uncapped and 4.4 % slower capped, so other shapes keep their occupancy. The
 // 16-bit steps want more waves, not fewer.
 static StepRoute route_of(size_t elem, const Launch& L, const Geo& G, const ViscF& V, const ForceF& Fo) {
-  if (packed_rows(G, elem)) return StepRoute{3, 0};
-  StepRoute r{pull_mode(G, L.block), 0};
+  if (packed_rows(G, elem)) return StepRoute{3, 0, false};
+  StepRoute r{pull_mode(G, L.block), 0, false};
   if (elem == 4) {
     if (r.mode == 2 && L.block.x == 256 && L.block.y == 1)
       r.blocks = G.N >= (1u << 23) && !G.walls && !Fo.mode && V.kind != 2 ? 3 : 4;
     else if (r.mode == 0 && L.block.x == 128 && L.block.y == 2)
       r.blocks = 4;
   }
+  // The rate loaded ahead takes the exchange's kernel from 6 blocks per CU to 5. It pays in small launches and in
+  // large ones; between, where the sixth block saves a round, the rate is loaded at its use (64x64x128 FP16 9.1 us
+  // a step and 9.9 ahead, 128x108x20 FP32 8.5 and 9.7; but 128x128x96 FP16 24.7 and 22.5), and so it is where
+  // there is no rate, from fewer blocks on (128x128x20 implicit 8.4 and 10.4, 64x64x48 const 6.1 and 6.3; 64x64x16
+  // 4.8 and 4.4).
+  const bool lagged = V.kind == 1 || V.kind == 2;
+  const unsigned blocks = L.grid.x * L.grid.y * L.grid.z;
+  r.late = r.mode == 2 && blocks > (lagged ? 1024 : 640) && blocks <= (r.blocks ? r.blocks * 256u : 2304);
   return r;
 }
 
@@ -249,10 +263,17 @@ static void launch_step_c(bool walls, const Launch& L, hipStream_t st, const Geo
   switch (route.mode + (walls ? 3 : 0)) {
     case 0: hipLaunchKernelGGL((step_kernel<S, false, 0, CORR>), L.grid, L.block, lds, st, G, M, V, Fo, io); break;
     case 1: hipLaunchKernelGGL((step_kernel<S, false, 1, CORR>), L.grid, L.block, lds, st, G, M, V, Fo, io); break;
-    case 2: hipLaunchKernelGGL((step_kernel<S, false, 2, CORR>), L.grid, L.block, lds, st, G, M, V, Fo, io); break;
+    case 2: {
+      const auto k = route.late ? step_kernel<S, false, 4, CORR> : step_kernel<S, false, 2, CORR>;
+      hipLaunchKernelGGL(k, L.grid, L.block, lds, st, G, M, V, Fo, io);
+      break;
+    }
     case 3: hipLaunchKernelGGL((step_kernel<S, true, 0, CORR>), L.grid, L.block, lds, st, G, M, V, Fo, io); break;
     case 4: hipLaunchKernelGGL((step_kernel<S, true, 1, CORR>), L.grid, L.block, lds, st, G, M, V, Fo, io); break;
-    default: hipLaunchKernelGGL((step_kernel<S, true, 2, CORR>), L.grid, L.block, lds, st, G, M, V, Fo, io); break;
+    default: {
+      const auto k = route.late ? step_kernel<S, true, 4, CORR> : step_kernel<S, true, 2, CORR>;
+      hipLaunchKernelGGL(k, L.grid, L.block, lds, st, G, M, V, Fo, io);
+    }
   }
 }
 

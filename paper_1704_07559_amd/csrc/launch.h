@@ -19,10 +19,11 @@ struct PairPlan {
   int cols, rows, planes, tx, ty, tiles, threads;
 };
 
-// How a single step is launched: the pull mode (pull_mode, 3 for packed rows) and the blocks per CU (0: as many
-// as the registers allow).
+// How a single step is launched: the pull mode (pull_mode, 3 for packed rows), the blocks per CU (0: as many
+// as the registers allow), and whether rows exchanged through LDS load the lagged rate at its use.
 struct StepRoute {
   int mode, blocks;
+  bool late;
 };
 
 namespace d3q19 {

@@ -79,4 +79,21 @@ def test_d2q9_steps_per_launch(box, law, storage, steps):
 ])
 def test_d3q19_step_launch(box, law, storage, more, mode, blocks):
     from paper_1704_07559_amd import capi
-    assert capi.step_route(_params(19, box, law, storage, **more)) == {"mode": mode, "blocks": blocks}
+    r = capi.step_route(_params(19, box, law, storage, **more))
+    assert (r["mode"], r["blocks"]) == (mode, blocks)
+
+
+@pytest.mark.parametrize("box,law,storage,late", [
+    # where the sixth block per CU saves a round: 1024 to 2304 blocks with a rate, 640 without
+    ((64, 64, 64), "smag", F32, False), ((64, 64, 65), "smag", F32, True), ((64, 64, 128), "smag", F16, True),
+    ((64, 64, 144), "smag", 2, True), ((64, 64, 145), "smag", F32, False), ((128, 128, 96), "smag", F16, False),
+    ((128, 128, 20), "implicit", F32, True), ((64, 64, 40), "const", F32, False), ((64, 64, 41), "const", F32, True),
+    ((64, 64, 128), "power", F32, True), ((128, 128, 512), "power", F32, False),
+    # four blocks per CU anyway
+    ((256, 64, 32), "smag", F32, False), ((256, 64, 16), "const", F32, True), ((256, 65, 16), "const", F32, False),
+    # no exchange
+    ((96, 96, 40), "smag", F32, False), ((384, 384, 8), "smag", F32, False),
+])
+def test_d3q19_rate_at_its_use(box, law, storage, late):
+    from paper_1704_07559_amd import capi
+    assert capi.step_route(_params(19, box, law, storage))["late"] is late
