@@ -311,7 +311,7 @@ def pair_route(params: Params) -> dict:
 
 
 def step_route(params: Params) -> dict:
-    """How single steps of a D3Q19 box are launched: the pull ``mode`` (0 part rows, 1 whole rows, 2 whole rows
+    """How single steps of a 3D box are launched: the pull ``mode`` (0 part rows, 1 whole rows, 2 whole rows
     exchanged through LDS, 3 whole rows stored packed), the ``blocks`` per CU (0: no cap), and whether mode 2
     loads the lagged rate ``late``, at its use."""
     v = (ctypes.c_int * 3)()

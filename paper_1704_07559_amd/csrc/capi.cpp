@@ -649,13 +649,13 @@ lbm_status lbm_internal_pair_route(const lbm_params* p, int out[6]) {
   return LBM_OK;
 }
 
-// How a D3Q19 box's single steps are launched: pull mode, blocks per CU (0: no cap), rate loaded at its use (0, 1).
+// How a 3D box's single steps are launched: pull mode, blocks per CU (0: no cap), rate loaded at its use (0, 1).
 lbm_status lbm_internal_step_route(const lbm_params* p, int out[3]) {
   lbm_ctx c{};
   const lbm_status st = model_of(p, &c);
   if (st != LBM_OK) return st;
-  if (c.Q != 19) return fail(LBM_EUNSUPPORTED, "the step's route is told for D3Q19 only");
-  const StepRoute r = d3q19::step_route(c.p.storage, c.G, c.V, c.F);
+  if (c.Q == 9) return fail(LBM_EUNSUPPORTED, "the step's route is told for the 3D lattices");
+  const StepRoute r = c.Q == 19 ? d3q19::step_route(c.p.storage, c.G, c.V, c.F) : d3q15::step_route(c.p.storage, c.G);
   out[0] = r.mode;
   out[1] = r.blocks;
   out[2] = r.late ? 1 : 0;

@@ -299,18 +299,25 @@ __device__ __forceinline__ void pull_staged(const S* __restrict__ src, const Geo
   });
 }
 
-// Boxes whose steps store their rows packed (store_rows_packed) and load the populations through
-// the caches: runs that do not start on 64-byte boundaries (and FP32 rows between 256 and 512
-// nodes that no 64-node segment divides), where nontemporal loads fetch the line that two runs
-// share twice. A D3Q19 LES step, us, before and now: FP32 171x133x95 72 and 59, 250^3 550 and 432,
+// Rows whose runs do not start on 64-byte boundaries (and FP32 rows between 256 and 512 nodes that no
+// 64-node segment divides): nontemporal loads fetch the line that two runs share twice.
+inline bool ragged_rows(const Geo& G, size_t elem) {
+  return G.nx <= 512 && ((G.nx * elem) % 64 != 0 || (elem == 4 && G.nx > 256 && G.nx % 64 != 0));
+}
+// Boxes of ragged rows whose steps store them packed (store_rows_packed) and load the populations through
+// the caches. A D3Q19 LES step, us, before and now: FP32 171x133x95 72 and 59, 250^3 550 and 432,
 // 200^3 250 and 220, 300x200x200 571 and 328 (its second 256-lane segment was mostly idle),
 // 257x200x200 497 and 303, 288x200x200 381 and 315; FP16 200^3 150 and 138, 300x200x200 333 and
 // 257. Not below 2^18 nodes, where a launch is bound by one block's chain of latencies and
 // the extra barrier shows (60^3 8.5 and 9.5), nor for 16-bit runs of a multiple of 64 bytes
-// (224 x 200 x 200 138 and 145; 352 x 150 x 150 151 and 164).
-inline bool packed_rows(const Geo& G, size_t elem) {
-  if (G.nx > 512 || G.N < (1u << 18)) return false;
-  return (G.nx * elem) % 64 != 0 || (elem == 4 && G.nx > 256 && G.nx % 64 != 0);
+// (224 x 200 x 200 138 and 145; 352 x 150 x 150 151 and 164), nor where both buffers fit well in the
+// 32 MB of the L2s, out of which a shared line costs nothing twice (FP16 104x60x43, 9.7 MB a buffer, 8.7 and
+// 12.3, D3Q15 BF16 100x60x60 8.5 and 10.5, D3Q15 BF16 40x93x112, 12 MB, 9.6 and 7.6; BF16 24x230x73, whose
+// masked lanes packed rows fill, 13.0 and 10.1), nor for fewer rows of a block each than four to a CU (power law 511x24x24 10.7 and 13.5).
+inline bool packed_rows(const Geo& G, int q, size_t elem) {
+  if (!ragged_rows(G, elem) || G.N < (1u << 18)) return false;
+  if (G.nx >= 40 && G.N * elem * q < (size_t(12) << 20)) return false;
+  return G.nx <= 256 || G.ny * G.nz >= 1024;
 }
 // Their stores stream only where the two population buffers outgrow the 256 MB last-level cache
 // (171x133x95 FP16, 82 MB a buffer: 35 us cached, 40 streamed; 250^3 FP32 462 and 432).

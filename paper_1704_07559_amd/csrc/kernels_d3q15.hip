@@ -381,10 +381,21 @@ static const S* cb(const void* p) {
   return static_cast<const S*>(p);
 }
 
+// FP32 in whole 256-node rows: 4 blocks per CU instead of 7 (+4.4 % at 256^3; 3 blocks lost
+// 2 %). See lds_cap_bytes.
+static StepRoute route_of(size_t elem, const Launch& L, const Geo& G) {
+  if (packed_rows(G, Q, elem)) return StepRoute{3, 0, false};
+  const int mode = pull_mode(G, L.block);
+  return StepRoute{mode, elem == 4 && mode == 2 && L.block.x == 256 && L.block.y == 1 ? 4 : 0, false};
+}
+
+StepRoute step_route(int storage, const Geo& G) { return route_of(storage == 0 ? 4 : 2, node_launch(G), G); }
+
 template <typename S, bool CORR>
 static void launch_step_c(bool walls, const Launch& L, hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V,
                           const ForceF& Fo, const StepIO& io) {
-  if (packed_rows(G, sizeof(S))) {
+  const StepRoute route = route_of(sizeof(S), L, G);
+  if (route.mode == 3) {
     const Launch R = packed_launch(G);
     const size_t chunk = packed_lds_bytes<Q, S>(R.block.x, R.block.y);
     StepIO pio = io;
@@ -393,14 +404,8 @@ static void launch_step_c(bool walls, const Launch& L, hipStream_t st, const Geo
     else hipLaunchKernelGGL((step_kernel<S, false, 3, CORR>), R.grid, R.block, chunk, st, G, M, V, Fo, pio);
     return;
   }
-  const int mode = pull_mode(G, L.block);
-  // FP32 in whole 256-node rows: 4 blocks per CU instead of 7 (+4.4 % at 256^3; 3 blocks lost
-  // 2 %). See lds_cap_bytes.
-  size_t lds = 0;
-  if constexpr (sizeof(S) == 4) {
-    if (mode == 2 && L.block.x == 256 && L.block.y == 1) lds = lds_cap_bytes(4, staged_lds_bytes<Lat>());
-  }
-  switch (mode + (walls ? 3 : 0)) {
+  const size_t lds = lds_cap_bytes(route.blocks, route.mode == 2 ? staged_lds_bytes<Lat>() : 0);
+  switch (route.mode + (walls ? 3 : 0)) {
     case 0: hipLaunchKernelGGL((step_kernel<S, false, 0, CORR>), L.grid, L.block, lds, st, G, M, V, Fo, io); break;
     case 1: hipLaunchKernelGGL((step_kernel<S, false, 1, CORR>), L.grid, L.block, lds, st, G, M, V, Fo, io); break;
     case 2: hipLaunchKernelGGL((step_kernel<S, false, 2, CORR>), L.grid, L.block, lds, st, G, M, V, Fo, io); break;

@@ -216,7 +216,7 @@ inline PairPlan plan_pairs(int q, int storage, const Geo& G, const ViscF& V, con
     }
   }
   // least / N is 2 steps' ns a node
-  const long long ps = !pair_fits(G, q) ? 26 : packed_rows(G, sizeof(float)) ? 60 : 37;
+  const long long ps = !pair_fits(G, q) ? 26 : ragged_rows(G, sizeof(float)) ? 60 : 37;
   if (500 * least > ps * G.N) return PairPlan{};
   return best;
 }

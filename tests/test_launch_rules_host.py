@@ -97,3 +97,23 @@ def test_d3q19_step_launch(box, law, storage, more, mode, blocks):
 def test_d3q19_rate_at_its_use(box, law, storage, late):
     from paper_1704_07559_amd import capi
     assert capi.step_route(_params(19, box, law, storage))["late"] is late
+
+
+@pytest.mark.parametrize("lattice,box,storage,packed", [
+    (19, (171, 133, 95), F32, True), (19, (171, 133, 95), F16, True), (19, (200, 200, 200), F16, True),
+    (19, (200, 200, 200), F32, True), (19, (300, 200, 200), F32, True), (19, (256, 256, 256), F32, False),
+    (19, (224, 200, 200), F16, False), (19, (600, 200, 200), F32, False),
+    # a launch of less than a round of blocks
+    (19, (60, 60, 60), F32, False), (19, (100, 64, 40), F16, False),
+    # both buffers in the L2s
+    (19, (104, 60, 43), F16, False), (19, (100, 82, 40), F16, False), (19, (100, 83, 40), F16, True),
+    (19, (67, 64, 65), F32, True), (19, (30, 30, 300), F16, True),
+    # few rows of a block each
+    (19, (511, 24, 24), F32, False), (19, (511, 32, 31), F32, False), (19, (511, 32, 32), F32, True),
+    (15, (200, 200, 200), F32, True), (15, (100, 60, 60), 2, False), (15, (43, 512, 13), 2, False), (15, (40, 93, 112), 2, False),
+    (15, (129, 65, 62), 2, True),
+    (15, (33, 100, 100), 2, True), (15, (256, 256, 256), F32, False),
+])
+def test_packed_rows(lattice, box, storage, packed):
+    from paper_1704_07559_amd import capi
+    assert (capi.step_route(_params(lattice, box, "power", storage))["mode"] == 3) is packed
