@@ -85,6 +85,7 @@ _sig = {
     # launch rules (see the end of this file)
     "lbm_internal_pair_route": (ctypes.c_int, [ctypes.POINTER(lbm_params), ctypes.POINTER(ctypes.c_int)]),
     "lbm_internal_step_route": (ctypes.c_int, [ctypes.POINTER(lbm_params), ctypes.POINTER(ctypes.c_int)]),
+    "lbm_internal_query_route": (ctypes.c_int, [ctypes.POINTER(lbm_params), ctypes.POINTER(ctypes.c_int)]),
     "lbm_internal_take_pairs": (ctypes.c_int, [_ctx_p, ctypes.c_int, ctypes.c_int, ctypes.c_int, _vp]),
     "lbm_internal_copy_is_one_launch": (ctypes.c_int, [ctypes.c_size_t, ctypes.c_size_t]),
 }
@@ -317,6 +318,14 @@ def step_route(params: Params) -> dict:
     v = (ctypes.c_int * 3)()
     _check(_lib.lbm_internal_step_route(ctypes.byref(params.to_c()), v), "lbm_internal_step_route")
     return {"mode": v[0], "blocks": v[1], "late": bool(v[2])}
+
+
+def query_route(params: Params) -> dict:
+    """Whether the ``strain`` and the ``populations`` query of a box load through the caches, and the mode of its
+    ``adjoint`` step (1 direct, 2 LDS exchange, 3 through the caches; 0 where there is none)."""
+    v = (ctypes.c_int * 3)()
+    _check(_lib.lbm_internal_query_route(ctypes.byref(params.to_c()), v), "lbm_internal_query_route")
+    return {"strain": bool(v[0]), "populations": bool(v[1]), "adjoint": v[2]}
 
 
 def take_pairs(ctx: int, tile, snu_pair=None):

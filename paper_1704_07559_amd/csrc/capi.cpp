@@ -662,6 +662,19 @@ lbm_status lbm_internal_step_route(const lbm_params* p, int out[3]) {
   return LBM_OK;
 }
 
+// How the read-only kernels and the reverse step access a box: strain query and populations query through the
+// caches (0, 1), adjoint mode (1 direct, 2 LDS exchange, 3 through the caches; 0 where there is none).
+lbm_status lbm_internal_query_route(const lbm_params* p, int out[3]) {
+  lbm_ctx c{};
+  const lbm_status st = model_of(p, &c);
+  if (st != LBM_OK) return st;
+  const size_t elem = elem_size(p->storage);
+  out[0] = cached_strain(c.G, c.Q, elem) ? 1 : 0;
+  out[1] = cached_get(c.G, c.Q, elem) ? 1 : 0;
+  out[2] = has_adjoint(&c) ? d3q19::adjoint_mode(c.G, c.V) : 0;
+  return LBM_OK;
+}
+
 // Has a context's grouped steps run two per launch in tiles of cols x rows x planes, whether or not the plan of its
 // box says so (cols = 0: singly). snu_pair: the caller's second s_nu field, for the lagged laws.
 lbm_status lbm_internal_take_pairs(lbm_ctx* c, int cols, int rows, int planes, float* snu_pair) {

@@ -439,16 +439,28 @@ __global__ __launch_bounds__(kMaxBlock) void init_adjoint_kernel(Geo G, ModelF M
   grad_u0[2 * N + self] = M.rho0 * (gz - 3.0f * uz * sl);
 }
 
+// How a reverse step accesses the adjoint state (XMODE). Rows that share 32-byte sectors go through the caches
+// while a step's arrays (record, adjoint state in and out, force gradient) are at most 384 MB, and again where
+// they are far beyond the 256 MB last-level cache; between, and in rows wider than a block, streaming accesses
+// leave it to the record (us a step in a sweep, streaming and cached: 100^3 Smagorinsky 44.6 and 38.8, 187^3 307
+// and 291; 228x96x160 141 and 155, 700x60x60 109 and 124, constant viscosity 98 and 104; 173^3 constant 202 and
+// 196; 388x576x32 399 and 421). Not in boxes whose step is one latency long (101x17x75 7.5 and 8.8, 60^3 11.0 and
+// 9.7). Whole-row blocks (pull_mode 2) exchange the x-shifted adjoint elements through LDS.
+int adjoint_mode(const Geo& G, const ViscF& V) {
+  const int pull = pull_mode(G, node_launch(G).block);
+  const bool lagged = V.kind == 1 || V.kind == 2;
+  const size_t bytes = sizeof(float) * G.N * (save_planes(V) + 2 * (lagged ? 20 : 19) + 6);
+  bool cached = !runs_aligned(G, sizeof(float), 32) && G.N >= (3u << 16);
+  if (bytes > (size_t(384) << 20)) cached &= G.nx <= 256 && (V.kind == 0 || G.N >= 5500000);
+  return cached ? 3 : (pull == 2 ? 2 : 1);
+}
+
 template <bool IN_ROWS, bool OUT_ROWS>
 static hipError_t launch_adjoint_layout(const Geo& G, const ModelF& M, const ViscF& V, const ForceF& Fo,
                                         const float* rec, const float* lam_in, float* lam_out, float* grad_force,
                                         hipStream_t st) {
   const Launch L = node_launch(G);
-  // rows that share 32-byte sectors go through the caches (100x90x80 29 us a step and 24, 171x133x95 85
-  // and 80; 200^3, rows of 800 bytes, 289 and 297), except in boxes whose step is one latency long
-  // (101x17x75 7.5 us streaming and 8.8 cached, 60^3 11.0 and 9.7); whole-row blocks (pull_mode 2)
-  // exchange the x-shifted adjoint elements through LDS
-  const int mode = !runs_aligned(G, sizeof(float), 32) && G.N >= (3u << 16) ? 3 : (pull_mode(G, L.block) == 2 ? 2 : 1);
+  const int mode = adjoint_mode(G, V);
   // constant viscosity, whole 256-node rows: 6 blocks per CU instead of 7 (+2.5 % at 256^3;
   // 4 blocks lost 4 %; the 128^3 shape and the lagged kernel run as fast uncapped)
   const size_t lds =

@@ -28,6 +28,7 @@ struct StepRoute {
 
 namespace d3q19 {
 StepRoute step_route(int storage, const Geo&, const ViscF&, const ForceF&);
+int adjoint_mode(const Geo&, const ViscF&);
 hipError_t launch_init(int storage, const Geo&, const ModelF&, void* buf, float* snu, const float* rho_u,
                        const float* grad_u, hipStream_t);
 hipError_t launch_step(int storage, const Geo&, const ModelF&, const ViscF&, const ForceF&, const StepIO&,

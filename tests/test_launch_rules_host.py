@@ -117,3 +117,18 @@ def test_d3q19_rate_at_its_use(box, law, storage, late):
 def test_packed_rows(lattice, box, storage, packed):
     from paper_1704_07559_amd import capi
     assert (capi.step_route(_params(lattice, box, "power", storage))["mode"] == 3) is packed
+
+
+@pytest.mark.parametrize("box,law,mode", [
+    ((128, 128, 128), "const", 2), ((256, 256, 256), "smag", 2), ((200, 200, 200), "smag", 1), ((320, 100, 100), "const", 1),
+    # rows that share sectors: through the caches from 196608 nodes on
+    ((60, 60, 54), "smag", 1), ((60, 60, 55), "smag", 3), ((65, 80, 80), "smag", 3), ((100, 100, 100), "power", 3),
+    ((257, 40, 40), "const", 3),
+    # not where a step's arrays pass 384 MB, unless they are far beyond the last-level cache or, at constant viscosity,
+    # a block holds the row
+    ((228, 96, 160), "smag", 1), ((235, 20, 544), "implicit", 1), ((700, 60, 60), "smag", 1), ((700, 60, 60), "const", 1),
+    ((173, 173, 173), "const", 3), ((187, 187, 187), "smag", 3), ((388, 576, 32), "smag", 1), ((388, 576, 32), "const", 1),
+])
+def test_adjoint_access(box, law, mode):
+    from paper_1704_07559_amd import capi
+    assert capi.query_route(_params(19, box, law))["adjoint"] == mode
