@@ -132,3 +132,15 @@ def test_packed_rows(lattice, box, storage, packed):
 def test_adjoint_access(box, law, mode):
     from paper_1704_07559_amd import capi
     assert capi.query_route(_params(19, box, law))["adjoint"] == mode
+
+
+@pytest.mark.parametrize("lattice,box,storage,cached", [
+    (19, (128, 128, 128), F32, True), (19, (256, 256, 256), F32, False), (19, (256, 256, 256), F16, False),
+    (19, (171, 133, 95), F32, True), (19, (300, 100, 100), F32, True), (19, (200, 200, 200), F16, True),
+    (19, (200, 200, 200), F32, False), (19, (181, 181, 181), F32, True), (19, (190, 190, 190), F32, False),
+    (19, (250, 250, 250), F32, False), (15, (250, 250, 250), F32, False), (19, (250, 250, 250), F16, True),
+    (9, (2701, 2700, 1), F32, True), (9, (3001, 3000, 1), F32, False), (9, (4097, 4096, 1), F32, False), (9, (4097, 4096, 1), F16, True),
+])
+def test_strain_query_access(lattice, box, storage, cached):
+    from paper_1704_07559_amd import capi
+    assert capi.query_route(_params(lattice, box, "smag", storage))["strain"] is cached
