@@ -3,6 +3,8 @@
 // query, canonical gather/scatter and the diagnostics reduction. One thread per node.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 // Contraction of a product and a sum into an FMA only within one expression of the source
 // (for this file and the headers it includes): left to the code generator, which product of
 // a sum gets fused depends on the code around it, and the two-step kernel below must round
@@ -456,17 +458,17 @@ __global__ __launch_bounds__(kMaxBlock) void set_kernel(Geo G, S* buf, const flo
   scatter_rows<Lat, S>(buf, G, nb.rows, y, g);
 }
 
-template <typename S, bool CORR, bool IMPLICIT>
+// ROWS: blocks take whole rows in turn instead of nodes in their order in memory (reduce_by_rows).
+template <typename S, bool CORR, bool IMPLICIT, bool ROWS>
 __global__ __launch_bounds__(256) void reduce_kernel(Geo G, ModelF M, ViscF V, ForceF Fo, NodeWalk W, const S* buf,
                                                      const float* snu_f, double* partials) {
   double acc[kReduceVals] = {0, 0, 0, 0, 0, 0, 0, 0};
   const double per_jj = 0.5 / M.rho0;
-  for (unsigned self = blockIdx.x * 256 + threadIdx.x; self < G.N; self += gridDim.x * 256) {
-    const Coord c = coord_of(G, W, self);
+  const auto add = [&](unsigned self, int x, int y) {
     // (loaded ahead of the populations: behind them its latency would stand alone)
     float snu = (!IMPLICIT && snu_f) ? snu_f[self] : M.s[7];
     float g[Q];
-    pull_rows<Lat, S, true, false>(buf, G, rows_of<Q, S>(G, c.x, c.y, c.z), c.y, g);
+    pull_rows<Lat, S, true, ROWS>(buf, G, rows_of<Q, S>(G, x, y, 0), y, g);
     const Pairs P = make_pairs(g);
     const float drho = delta_rho(P);
     // (their sum is non-finite where a population is, so that finite nodes pay one test)
@@ -494,6 +496,15 @@ __global__ __launch_bounds__(256) void reduce_kernel(Geo G, ModelF M, ViscF V, F
     acc[5] += static_cast<double>(S3[0]) * S3[0] + static_cast<double>(S3[1]) * S3[1] +
               2.0 * static_cast<double>(S3[2]) * S3[2];
     acc[6] = fmax(acc[6], jj);  // max |j|^2: the final pass takes sqrt(.) / rho0 once
+  };
+  if constexpr (ROWS) {
+    for (int y = blockIdx.x; y < G.ny; y += gridDim.x)
+      for (int x = threadIdx.x; x < G.nx; x += 256) add(node_index(G, x, y, 0), x, y);
+  } else {
+    for (unsigned self = blockIdx.x * 256 + threadIdx.x; self < G.N; self += gridDim.x * 256) {
+      const Coord c = coord_of(G, W, self);
+      add(self, c.x, c.y);
+    }
   }
   block_reduce_store(acc, partials);
 }
@@ -684,25 +695,37 @@ hipError_t launch_set(int storage, const Geo& G, void* buf, const float* canon, 
   return hipGetLastError();
 }
 
+// Wide rows that fill their blocks' last 256 nodes and are many enough are taken whole: the division that finds a
+// node's coordinates costs more there than a row's end (4096^2 FP16 67.6 us against 77.4, implicit 91 against 109,
+// 961x737 FP32 14.0 against 15.5; but 920x4096 FP16 29.8 against 27.1, 4096x520 22.9 against 19.8, 300x10000 30.4
+// against 23.5).
+static bool reduce_by_rows(const Geo& G) {
+  const int lanes = (G.nx + 255) / 256 * 256;
+  return G.nx >= 900 && 25 * G.nx >= 23 * lanes && G.ny >= 512 && 5 * G.ny >= G.nx;
+}
+
 // The force-corrected strain and the implicit rate are instances of their own: their code costs
 // the plain diagnostics 10 VGPRs and a tenth of its instructions.
 template <typename S>
 static void launch_reduce_t(unsigned nb, hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V,
                             const ForceF& Fo, const S* buf, const float* snu, double* partials) {
-  constexpr size_t cap = 0;
-  decltype(&reduce_kernel<S, false, false>) f;
-  switch ((Fo.strain_corr ? 1 : 0) + (V.kind == 3 ? 2 : 0)) {
-    case 0: f = reduce_kernel<S, false, false>; break;
-    case 1: f = reduce_kernel<S, true, false>; break;
-    case 2: f = reduce_kernel<S, false, true>; break;
-    default: f = reduce_kernel<S, true, true>; break;
+  decltype(&reduce_kernel<S, false, false, false>) f;
+  switch ((Fo.strain_corr ? 1 : 0) + (V.kind == 3 ? 2 : 0) + (reduce_by_rows(G) ? 4 : 0)) {
+    case 0: f = reduce_kernel<S, false, false, false>; break;
+    case 1: f = reduce_kernel<S, true, false, false>; break;
+    case 2: f = reduce_kernel<S, false, true, false>; break;
+    case 3: f = reduce_kernel<S, true, true, false>; break;
+    case 4: f = reduce_kernel<S, false, false, true>; break;
+    case 5: f = reduce_kernel<S, true, false, true>; break;
+    case 6: f = reduce_kernel<S, false, true, true>; break;
+    default: f = reduce_kernel<S, true, true, true>; break;
   }
-  hipLaunchKernelGGL(f, dim3(nb), dim3(256), cap, st, G, M, V, Fo, node_walk(G), buf, snu, partials);
+  hipLaunchKernelGGL(f, dim3(nb), dim3(256), 0, st, G, M, V, Fo, node_walk(G), buf, snu, partials);
 }
 
 hipError_t launch_reduce(int storage, const Geo& G, const ModelF& M, const ViscF& V, const ForceF& Fo,
                          const void* buf, const float* snu, double* partials, double* out, hipStream_t st) {
-  const unsigned nb = reduce_blocks(G);
+  const unsigned nb = reduce_by_rows(G) ? static_cast<unsigned>(std::min(G.ny, kReduceBlocks)) : reduce_blocks(G);
   switch (storage) {
     case 0: launch_reduce_t<float>(nb, st, G, M, V, Fo, cb<float>(buf), snu, partials); break;
     case 1: launch_reduce_t<_Float16>(nb, st, G, M, V, Fo, cb<_Float16>(buf), snu, partials); break;
