@@ -634,22 +634,22 @@ hipError_t launch_pair(const PairPlan& P, int storage, const Geo& G, const Model
 }
 
 template <typename S>
-static void launch_strain_t(const Launch& L, size_t lds, hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V,
+static void launch_strain_t(const Launch& L, hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V,
                             const ForceF& Fo, const void* buf, const float* snu, int kind, float* S_out) {
   // (rows whose runs are aligned are multiples of 8 nodes)
   const auto k = !cached_strain(G, Q, sizeof(S)) ? strain_kernel<S, false, true>
                  : plane_stream(G)               ? strain_kernel<S, true, true>
                                                  : strain_kernel<S, true, false>;
-  hipLaunchKernelGGL(k, L.grid, L.block, lds, st, G, M, V, Fo, cb<S>(buf), snu, kind, S_out);
+  hipLaunchKernelGGL(k, L.grid, L.block, 0, st, G, M, V, Fo, cb<S>(buf), snu, kind, S_out);
 }
 
 hipError_t launch_strain(int storage, const Geo& G, const ModelF& M, const ViscF& V, const ForceF& Fo, const void* buf,
                          const float* snu, int kind, float* S_out, hipStream_t st) {
   const Launch L = node_launch(G);
   switch (storage) {
-    case 0: launch_strain_t<float>(L, 0, st, G, M, V, Fo, buf, snu, kind, S_out); break;
-    case 1: launch_strain_t<_Float16>(L, 0, st, G, M, V, Fo, buf, snu, kind, S_out); break;
-    case 2: launch_strain_t<__bf16>(L, 0, st, G, M, V, Fo, buf, snu, kind, S_out); break;
+    case 0: launch_strain_t<float>(L, st, G, M, V, Fo, buf, snu, kind, S_out); break;
+    case 1: launch_strain_t<_Float16>(L, st, G, M, V, Fo, buf, snu, kind, S_out); break;
+    case 2: launch_strain_t<__bf16>(L, st, G, M, V, Fo, buf, snu, kind, S_out); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

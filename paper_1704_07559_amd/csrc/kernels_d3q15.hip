@@ -435,22 +435,22 @@ hipError_t launch_step(int storage, const Geo& G, const ModelF& M, const ViscF& 
 }
 
 template <typename S>
-static void launch_strain_t(const Launch& L, size_t lds, hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V,
+static void launch_strain_t(const Launch& L, hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V,
                             const ForceF& Fo, const void* buf, const float* snu, int kind, float* S_out) {
   // (rows whose runs are aligned are multiples of 8 nodes)
   const auto k = !cached_strain(G, Q, sizeof(S)) ? strain_kernel<S, false, true>
                  : plane_stream(G)               ? strain_kernel<S, true, true>
                                                  : strain_kernel<S, true, false>;
-  hipLaunchKernelGGL(k, L.grid, L.block, lds, st, G, M, V, Fo, cb<S>(buf), snu, kind, S_out);
+  hipLaunchKernelGGL(k, L.grid, L.block, 0, st, G, M, V, Fo, cb<S>(buf), snu, kind, S_out);
 }
 
 hipError_t launch_strain(int storage, const Geo& G, const ModelF& M, const ViscF& V, const ForceF& Fo, const void* buf,
                          const float* snu, int kind, float* S_out, hipStream_t st) {
   const Launch L = node_launch(G);
   switch (storage) {
-    case 0: launch_strain_t<float>(L, 0, st, G, M, V, Fo, buf, snu, kind, S_out); break;
-    case 1: launch_strain_t<_Float16>(L, 0, st, G, M, V, Fo, buf, snu, kind, S_out); break;
-    case 2: launch_strain_t<__bf16>(L, 0, st, G, M, V, Fo, buf, snu, kind, S_out); break;
+    case 0: launch_strain_t<float>(L, st, G, M, V, Fo, buf, snu, kind, S_out); break;
+    case 1: launch_strain_t<_Float16>(L, st, G, M, V, Fo, buf, snu, kind, S_out); break;
+    case 2: launch_strain_t<__bf16>(L, st, G, M, V, Fo, buf, snu, kind, S_out); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -501,7 +501,6 @@ hipError_t launch_set(int storage, const Geo& G, void* buf, const float* canon, 
 template <typename S>
 static void launch_reduce_t(unsigned nb, hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V,
                             const ForceF& Fo, const S* buf, const float* snu, double* partials) {
-  constexpr size_t cap = 0;
   decltype(&reduce_kernel<S, false, false>) f;
   switch ((Fo.strain_corr ? 1 : 0) + (V.kind == 3 ? 2 : 0)) {
     case 0: f = reduce_kernel<S, false, false>; break;
@@ -509,7 +508,7 @@ static void launch_reduce_t(unsigned nb, hipStream_t st, const Geo& G, const Mod
     case 2: f = reduce_kernel<S, false, true>; break;
     default: f = reduce_kernel<S, true, true>; break;
   }
-  hipLaunchKernelGGL(f, dim3(nb), dim3(256), cap, st, G, M, V, Fo, node_walk(G), buf, snu, partials);
+  hipLaunchKernelGGL(f, dim3(nb), dim3(256), 0, st, G, M, V, Fo, node_walk(G), buf, snu, partials);
 }
 
 hipError_t launch_reduce(int storage, const Geo& G, const ModelF& M, const ViscF& V, const ForceF& Fo,
