@@ -655,7 +655,8 @@ lbm_status lbm_internal_step_route(const lbm_params* p, int out[3]) {
   const lbm_status st = model_of(p, &c);
   if (st != LBM_OK) return st;
   if (c.Q == 9) return fail(LBM_EUNSUPPORTED, "the step's route is told for the 3D lattices");
-  const StepRoute r = c.Q == 19 ? d3q19::step_route(c.p.storage, c.G, c.V, c.F) : d3q15::step_route(c.p.storage, c.G);
+  const StepRoute r = c.Q == 19 ? d3q19::step_route(c.p.storage, c.G, c.V, c.F)
+                                : d3q15::step_route(c.p.storage, c.G, c.V);
   out[0] = r.mode;
   out[1] = r.blocks;
   out[2] = r.late ? 1 : 0;

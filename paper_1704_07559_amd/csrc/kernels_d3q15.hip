@@ -113,7 +113,8 @@ __device__ __forceinline__ float implicit_rate(const Pairs& P_, float drho, floa
 }
 
 // XMODE: how a block pulls along x (pull_mode: 0 part rows, 1 whole rows, 2 whole rows with
-// the LDS exchange, 3 whole rows, cached loads and packed stores). CORR: the force-corrected strain (a separate instance, so that the plain
+// the LDS exchange, 3 whole rows, cached loads and packed stores), 4 as 2 with the lagged rate
+// loaded at its use. CORR: the force-corrected strain (a separate instance, so that the plain
 // step keeps its register budget).
 template <typename S, bool WALLS, int XMODE, bool CORR>
 __global__ __launch_bounds__(XMODE == 3 ? kMaxPackedBlock : kMaxBlock) void step_kernel(Geo G, ModelF M, ViscF V,
@@ -132,13 +133,14 @@ __global__ __launch_bounds__(XMODE == 3 ? kMaxPackedBlock : kMaxBlock) void step
     const Rows<Q, S> r = rows_of<Q, S>(G, x, y, z);
     // the rate's latency hides behind the populations' (loaded ahead of the exchange's barrier, else
     // after their loads: in front of them its branch drags every kernel argument's load there)
+    constexpr bool ahead = XMODE != 1 && XMODE != 4;
     float snu_ahead = 0.0f;
-    if constexpr (XMODE == 2) {
-      if (io.snu) snu_ahead = io.snu[self];
+    if constexpr (XMODE == 2 || XMODE == 4) {
+      if (ahead && io.snu) snu_ahead = io.snu[self];
       pull_rows_staged<Lat, S, WALLS>(static_cast<const S*>(io.src), G, r, y, g);
     } else {
       pull_rows<Lat, S, WALLS, XMODE == 1, XMODE == 3>(static_cast<const S*>(io.src), G, r, y, g);
-      if (XMODE != 1 && io.snu) snu_ahead = io.snu[self];
+      if (ahead && io.snu) snu_ahead = io.snu[self];
     }
     const Pairs P = make_pairs(g);
     const float drho = delta_rho(P);
@@ -179,7 +181,7 @@ __global__ __launch_bounds__(XMODE == 3 ? kMaxPackedBlock : kMaxBlock) void step
       // of a sum the compiler fuses)
       float snu_prev = M.s[9];
       if (io.snu) {
-        if constexpr (XMODE != 1) {
+        if constexpr (ahead) {
           asm volatile("" : "+v"(snu_ahead));
           snu_prev = snu_ahead;
         } else {
@@ -382,19 +384,27 @@ static const S* cb(const void* p) {
 }
 
 // FP32 in whole 256-node rows: 4 blocks per CU instead of 7 (+4.4 % at 256^3; 3 blocks lost
-// 2 %). See lds_cap_bytes.
-static StepRoute route_of(size_t elem, const Launch& L, const Geo& G) {
+// 2 %). See lds_cap_bytes. Other exchanged rows load the rate at its use where the block per CU that loading
+// it ahead costs would cost a round too (us a step ahead and at its use: 64x356x20 Smagorinsky FP32 11.6 and 9.5,
+// FP16 7.0 and 6.3, 64x220x20 without a rate 7.9 and 7.0; but 64x48x20 4.6 and 4.9).
+static StepRoute route_of(size_t elem, const Launch& L, const Geo& G, const ViscF& V) {
   if (packed_rows(G, Q, elem)) return StepRoute{3, 0, false};
-  const int mode = pull_mode(G, L.block);
-  return StepRoute{mode, elem == 4 && mode == 2 && L.block.x == 256 && L.block.y == 1 ? 4 : 0, false};
+  StepRoute r{pull_mode(G, L.block), 0, false};
+  if (elem == 4 && r.mode == 2 && L.block.x == 256 && L.block.y == 1) r.blocks = 4;
+  const bool lagged = V.kind == 1 || V.kind == 2;
+  const unsigned blocks = L.grid.x * L.grid.y * L.grid.z;
+  r.late = r.mode == 2 && !r.blocks && blocks > 1024 && blocks <= (lagged ? 3072 : 1536);
+  return r;
 }
 
-StepRoute step_route(int storage, const Geo& G) { return route_of(storage == 0 ? 4 : 2, node_launch(G), G); }
+StepRoute step_route(int storage, const Geo& G, const ViscF& V) {
+  return route_of(storage == 0 ? 4 : 2, node_launch(G), G, V);
+}
 
 template <typename S, bool CORR>
 static void launch_step_c(bool walls, const Launch& L, hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V,
                           const ForceF& Fo, const StepIO& io) {
-  const StepRoute route = route_of(sizeof(S), L, G);
+  const StepRoute route = route_of(sizeof(S), L, G, V);
   if (route.mode == 3) {
     const Launch R = packed_launch(G);
     const size_t chunk = packed_lds_bytes<Q, S>(R.block.x, R.block.y);
@@ -408,10 +418,17 @@ static void launch_step_c(bool walls, const Launch& L, hipStream_t st, const Geo
   switch (route.mode + (walls ? 3 : 0)) {
     case 0: hipLaunchKernelGGL((step_kernel<S, false, 0, CORR>), L.grid, L.block, lds, st, G, M, V, Fo, io); break;
     case 1: hipLaunchKernelGGL((step_kernel<S, false, 1, CORR>), L.grid, L.block, lds, st, G, M, V, Fo, io); break;
-    case 2: hipLaunchKernelGGL((step_kernel<S, false, 2, CORR>), L.grid, L.block, lds, st, G, M, V, Fo, io); break;
+    case 2: {
+      const auto k = route.late ? step_kernel<S, false, 4, CORR> : step_kernel<S, false, 2, CORR>;
+      hipLaunchKernelGGL(k, L.grid, L.block, lds, st, G, M, V, Fo, io);
+      break;
+    }
     case 3: hipLaunchKernelGGL((step_kernel<S, true, 0, CORR>), L.grid, L.block, lds, st, G, M, V, Fo, io); break;
     case 4: hipLaunchKernelGGL((step_kernel<S, true, 1, CORR>), L.grid, L.block, lds, st, G, M, V, Fo, io); break;
-    default: hipLaunchKernelGGL((step_kernel<S, true, 2, CORR>), L.grid, L.block, lds, st, G, M, V, Fo, io); break;
+    default: {
+      const auto k = route.late ? step_kernel<S, true, 4, CORR> : step_kernel<S, true, 2, CORR>;
+      hipLaunchKernelGGL(k, L.grid, L.block, lds, st, G, M, V, Fo, io);
+    }
   }
 }
 

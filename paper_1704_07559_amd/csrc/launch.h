@@ -75,7 +75,7 @@ hipError_t launch_pair(const PairPlan&, int storage, const Geo&, const ModelF&, 
 }  // namespace d2q9
 
 namespace d3q15 {
-StepRoute step_route(int storage, const Geo&);
+StepRoute step_route(int storage, const Geo&, const ViscF&);
 hipError_t launch_init(int storage, const Geo&, const ModelF&, void* buf, float* snu, const float* rho_u,
                        const float* grad_u, hipStream_t);
 hipError_t launch_step(int storage, const Geo&, const ModelF&, const ViscF&, const ForceF&, const StepIO&,

@@ -84,6 +84,16 @@ def test_d3q19_step_launch(box, law, storage, more, mode, blocks):
 
 
 @pytest.mark.parametrize("box,law,storage,late", [
+    ((64, 64, 64), "smag", F32, False), ((64, 64, 65), "smag", F32, True), ((64, 64, 192), "smag", F16, True),
+    ((64, 64, 193), "smag", F16, False), ((64, 64, 96), "const", F16, True), ((64, 64, 97), "implicit", F32, False),
+    ((256, 64, 20), "smag", F32, False), ((256, 64, 20), "smag", F16, True), ((96, 96, 40), "smag", F32, False),
+])
+def test_d3q15_rate_at_its_use(box, law, storage, late):
+    from paper_1704_07559_amd import capi
+    assert capi.step_route(_params(15, box, law, storage))["late"] is late
+
+
+@pytest.mark.parametrize("box,law,storage,late", [
     # where the sixth block per CU saves a round: 1024 to 2304 blocks with a rate, 640 without
     ((64, 64, 64), "smag", F32, False), ((64, 64, 65), "smag", F32, True), ((64, 64, 128), "smag", F16, True),
     ((64, 64, 144), "smag", 2, True), ((64, 64, 145), "smag", F32, False), ((128, 128, 96), "smag", F16, False),
