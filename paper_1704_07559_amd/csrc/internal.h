@@ -313,11 +313,14 @@ inline bool ragged_rows(const Geo& G, size_t elem) {
 // (224 x 200 x 200 138 and 145; 352 x 150 x 150 151 and 164), nor where both buffers fit well in the
 // 32 MB of the L2s, out of which a shared line costs nothing twice (FP16 104x60x43, 9.7 MB a buffer, 8.7 and
 // 12.3, D3Q15 BF16 100x60x60 8.5 and 10.5, D3Q15 BF16 40x93x112, 12 MB, 9.6 and 7.6; BF16 24x230x73, whose
-// masked lanes packed rows fill, 13.0 and 10.1), nor for fewer rows of a block each than four to a CU (power law 511x24x24 10.7 and 13.5).
-inline bool packed_rows(const Geo& G, int q, size_t elem) {
+// masked lanes packed rows fill, 13.0 and 10.1; the power law, whose arithmetic the barrier holds up longer, FP16
+// 56x463x16, 15 MB, 11.4 and 13.4, FP32 28x64x156, 20 MB, 9.5 and 10.4), nor for fewer rows of a block each than
+// three to a CU (power law 511x24x24 10.7 and 13.5).
+inline bool packed_rows(const Geo& G, int q, size_t elem, const ViscF& V) {
   if (!ragged_rows(G, elem) || G.N < (1u << 18)) return false;
-  if (G.nx >= 40 && G.N * elem * q < (size_t(12) << 20)) return false;
-  return G.nx <= 256 || G.ny * G.nz >= 1024;
+  const bool power = V.kind == 2;
+  if (G.nx >= (power ? 20 : 40) && G.N * elem * q < (size_t(power ? 21 : 12) << 20)) return false;
+  return G.nx <= 256 || G.ny * G.nz >= 768;
 }
 // Their stores stream only where the two population buffers outgrow the 256 MB last-level cache
 // (171x133x95 FP16, 82 MB a buffer: 35 us cached, 40 streamed; 250^3 FP32 462 and 432).

@@ -388,7 +388,7 @@ static const S* cb(const void* p) {
 // it ahead costs would cost a round too (us a step ahead and at its use: 64x356x20 Smagorinsky FP32 11.6 and 9.5,
 // FP16 7.0 and 6.3, 64x220x20 without a rate 7.9 and 7.0; but 64x48x20 4.6 and 4.9).
 static StepRoute route_of(size_t elem, const Launch& L, const Geo& G, const ViscF& V) {
-  if (packed_rows(G, Q, elem)) return StepRoute{3, 0, false};
+  if (packed_rows(G, Q, elem, V)) return StepRoute{3, 0, false};
   StepRoute r{pull_mode(G, L.block), 0, false};
   if (elem == 4 && r.mode == 2 && L.block.x == 256 && L.block.y == 1) r.blocks = 4;
   const bool lagged = V.kind == 1 || V.kind == 2;

@@ -145,7 +145,7 @@ static hipError_t launch_kind(const PairPlan& P, const Geo& G, const ModelF& M, 
 
 hipError_t launch_pair(const PairPlan& P, const Geo& G, const ModelF& M, const ViscF& V, const void* src, void* dst,
                        const float* snu_in, float* snu_out, hipStream_t st) {
-  const bool xchg = !packed_rows(G, Q, sizeof(float)) && pull_mode(G, node_launch(G).block) == 2;
+  const bool xchg = !packed_rows(G, Q, sizeof(float), V) && pull_mode(G, node_launch(G).block) == 2;
   return xchg ? launch_kind<true>(P, G, M, V, src, dst, snu_in, snu_out, st)
               : launch_kind<false>(P, G, M, V, src, dst, snu_in, snu_out, st);
 }

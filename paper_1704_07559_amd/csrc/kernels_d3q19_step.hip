@@ -223,7 +223,7 @@ __global__ __launch_bounds__(XMODE == 3 ? kMaxPackedBlock : kMaxBlock, (kMinWave
 // 128 x 512 channel) ran as fast uncapped and 4.4 % slower capped, so other shapes keep their occupancy. The
 // 16-bit steps want more waves, not fewer.
 static StepRoute route_of(size_t elem, const Launch& L, const Geo& G, const ViscF& V, const ForceF& Fo) {
-  if (packed_rows(G, Q, elem)) return StepRoute{3, 0, false};
+  if (packed_rows(G, Q, elem, V)) return StepRoute{3, 0, false};
   StepRoute r{pull_mode(G, L.block), 0, false};
   if (elem == 4) {
     if (r.mode == 2 && L.block.x == 256 && L.block.y == 1)

@@ -16,8 +16,8 @@ def _mode(cp):
     return capi.step_route(cp)["mode"]
 
 
-@pytest.mark.parametrize("shape", [(41, 42, 171), (34, 85, 100), (67, 66, 65), (34, 32, 511), (34, 35, 257), (35, 33, 288),
-                                   (64, 220, 20), (512, 190, 3)])
+@pytest.mark.parametrize("shape", [(53, 42, 171), (46, 85, 100), (88, 66, 65), (34, 32, 511), (46, 35, 257), (45, 33, 288),
+                                   (90, 220, 20), (512, 190, 3)])
 @pytest.mark.parametrize("case", sorted(packed.KW))
 @pytest.mark.parametrize("lat", ["d3q19", "d3q15"])
 def test_packed_rows_against_oracle(lat, case, shape):

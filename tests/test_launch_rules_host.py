@@ -109,24 +109,27 @@ def test_d3q19_rate_at_its_use(box, law, storage, late):
     assert capi.step_route(_params(19, box, law, storage))["late"] is late
 
 
-@pytest.mark.parametrize("lattice,box,storage,packed", [
-    (19, (171, 133, 95), F32, True), (19, (171, 133, 95), F16, True), (19, (200, 200, 200), F16, True),
-    (19, (200, 200, 200), F32, True), (19, (300, 200, 200), F32, True), (19, (256, 256, 256), F32, False),
-    (19, (224, 200, 200), F16, False), (19, (600, 200, 200), F32, False),
+@pytest.mark.parametrize("lattice,box,law,storage,packed", [
+    (19, (171, 133, 95), "smag", F32, True), (19, (171, 133, 95), "power", F16, True), (19, (200, 200, 200), "const", F16, True),
+    (19, (200, 200, 200), "power", F32, True), (19, (300, 200, 200), "smag", F32, True),
+    (19, (256, 256, 256), "smag", F32, False), (19, (224, 200, 200), "smag", F16, False),
+    (19, (600, 200, 200), "smag", F32, False), (15, (200, 200, 200), "implicit", F32, True),
+    (15, (256, 256, 256), "const", F32, False),
     # a launch of less than a round of blocks
-    (19, (60, 60, 60), F32, False), (19, (100, 64, 40), F16, False),
+    (19, (60, 60, 60), "smag", F32, False), (19, (100, 64, 40), "smag", F16, False),
     # both buffers in the L2s
-    (19, (104, 60, 43), F16, False), (19, (100, 82, 40), F16, False), (19, (100, 83, 40), F16, True),
-    (19, (67, 64, 65), F32, True), (19, (30, 30, 300), F16, True),
+    (19, (104, 60, 43), "const", F16, False), (19, (100, 82, 40), "smag", F16, False), (19, (100, 83, 40), "smag", F16, True),
+    (19, (67, 64, 65), "smag", F32, True), (19, (30, 30, 300), "smag", F16, True), (15, (100, 60, 60), "const", 2, False),
+    (15, (43, 512, 13), "smag", 2, False), (15, (40, 93, 112), "smag", 2, False), (15, (129, 65, 62), "const", 2, True),
+    (15, (33, 100, 100), "smag", 2, True),
+    (19, (104, 60, 43), "power", F16, False), (19, (56, 463, 16), "power", F16, False), (19, (28, 64, 156), "power", F32, False),
+    (19, (127, 140, 16), "power", F32, False), (19, (28, 64, 164), "power", F32, True), (19, (19, 100, 150), "power", F16, True), (15, (37, 112, 64), "power", F16, False),
     # few rows of a block each
-    (19, (511, 24, 24), F32, False), (19, (511, 32, 31), F32, False), (19, (511, 32, 32), F32, True),
-    (15, (200, 200, 200), F32, True), (15, (100, 60, 60), 2, False), (15, (43, 512, 13), 2, False), (15, (40, 93, 112), 2, False),
-    (15, (129, 65, 62), 2, True),
-    (15, (33, 100, 100), 2, True), (15, (256, 256, 256), F32, False),
+    (19, (511, 24, 24), "smag", F32, False), (19, (511, 32, 23), "const", F32, False), (19, (511, 32, 24), "const", F32, True),
 ])
-def test_packed_rows(lattice, box, storage, packed):
+def test_packed_rows(lattice, box, law, storage, packed):
     from paper_1704_07559_amd import capi
-    assert (capi.step_route(_params(lattice, box, "power", storage))["mode"] == 3) is packed
+    assert (capi.step_route(_params(lattice, box, law, storage))["mode"] == 3) is packed
 
 
 @pytest.mark.parametrize("box,law,mode", [
