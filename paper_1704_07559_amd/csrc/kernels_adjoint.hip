@@ -451,7 +451,7 @@ int adjoint_mode(const Geo& G, const ViscF& V) {
   const bool lagged = V.kind == 1 || V.kind == 2;
   const size_t bytes = sizeof(float) * G.N * (save_planes(V) + 2 * (lagged ? 20 : 19) + 6);
   bool cached = !runs_aligned(G, sizeof(float), 32) && G.N >= (3u << 16);
-  if (bytes > (size_t(384) << 20)) cached &= G.nx <= 256 && (V.kind == 0 || G.N >= 5500000);
+  if (bytes > (size_t(384) << 20)) cached &= G.nx <= 256 ? V.kind == 0 || G.N >= 5500000 : G.N >= 7500000;
   return cached ? 3 : (pull == 2 ? 2 : 1);
 }
 
