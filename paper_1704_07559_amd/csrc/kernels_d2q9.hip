@@ -212,10 +212,10 @@ __global__ __launch_bounds__(kMaxBlock) void step_kernel(Geo G, ModelF M, ViscF 
   if (x >= G.nx || y >= G.ny) return;
   const unsigned self = node_index(G, x, y, 0);
   const Rows<Q, S> r = rows_of<Q, S>(G, x, y, 0);
-  // The rate is loaded ahead of the populations, its latency hidden behind theirs (FP16 64x16384 13.4 us
-  // against 14.6, FP32 184x712 3.8 against 4.0), but not in FP32 boxes whose buffers fill the L2s (100x3932 9.0
-  // us ahead, 7.3 at its use; beyond 600k nodes alike).
-  const bool ahead = sizeof(S) == 2 || G.N < (11u << 14);
+  // The rate is loaded ahead of the populations, its latency hidden behind theirs (us a step ahead and at its use:
+  // FP16 64x16384 9.4 and 10.2, FP32 184x712 4.3 and 4.5, power law 1161x3328 57.8 and 61.3), but not in FP32
+  // boxes whose buffers fill the L2s (100x3932 9.1 and 7.4, 3000x349 power law 5 % more ahead).
+  const bool ahead = sizeof(S) == 2 || G.N < (11u << 14) || G.N >= (3u << 19);
   const float snu_prev = ahead && io.snu ? io.snu[self] : M.s[7];
   float g[Q];
   if constexpr (XMODE == 2) pull_rows_staged<Lat, S, WALLS>(static_cast<const S*>(io.src), G, r, y, g);
