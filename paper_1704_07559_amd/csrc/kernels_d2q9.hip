@@ -593,8 +593,9 @@ static bool pair_pays(int storage, const Geo& G, const ViscF& V, const PairPlan&
   }
   // (16-bit rows of 256 nodes and more that are no multiple of 64 are pulled in parts by single steps)
   const bool half_wide = half && wide && !whole && work <= 3.3;
+  if (G.N <= (1u << 14)) return true;
   if (half && V.kind == 3) return half_wide || (!whole && work <= 1.5);
-  if (G.N <= (1u << 14) || (G.N <= (1u << 15) && filled >= 0.5)) return true;
+  if (G.N <= (1u << 15) && filled >= 0.5) return true;
   if (filled < (V.kind == 0 && !half ? 0.35 : 0.5)) return false;
   if (half) return half_wide || (G.N >= 300000 && work <= (whole ? 1.7 : 3.1));
   if (!wide && G.N < (11u << 14)) return false;

@@ -45,7 +45,8 @@ F32, F16 = 0, 1
     ((62, 770), "power", F32, 1), ((128, 256), "power", F32, 1), ((1000, 1048), "power", F16, 1),
     ((64, 16384), "implicit", F16, 1), ((160, 1280), "implicit", F16, 1),
     # a launch's latency
-    ((1, 1), "smag", F32, 2), ((64, 64), "const", F32, 2), ((100, 100), "smag", F16, 2), ((200, 100), "implicit", F32, 2),
+    ((1, 1), "smag", F32, 2), ((64, 64), "const", F32, 2), ((100, 100), "smag", F16, 2), ((200, 100), "implicit", F32, 2), ((61, 160), "implicit", F16, 2),
+    ((100, 300), "implicit", F16, 1),
     # filled strips
     ((250, 1048), "smag", F32, 2), ((250, 16777), "smag", F16, 2), ((600, 201), "implicit", F32, 2),
     ((100, 10485), "smag", F32, 2), ((64, 65536), "smag", F32, 2), ((4096, 4096), "smag", F32, 2),
