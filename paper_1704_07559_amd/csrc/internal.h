@@ -342,13 +342,15 @@ inline bool runs_aligned(const Geo& G, size_t elem, size_t bytes) { return (G.nx
 // fits the 256 MB last-level cache, which nontemporal loads do not fill. us, streaming and cached:
 // FP32 171x133x95 42.5 and 36, 300x100x100 78 and 59, FP16 200^3 114 and 97; FP32 128^3 (159 MB) 35.6
 // and 30.5, 128x128x192 (239 MB) 51 and 44, but 128x128x256 (319 MB) 74 and 74, 256^3 253 and 296, and
-// 200^3 (runs of 800 bytes) 154 and 160. FP32 states far beyond it stream whatever their rows (190^3, 521 MB, 134
-// and 139, 250^3 296 and 323, D3Q15 250^3 267 and 276; FP16 250^3 213 and 206), in 2D all that pass it (3701^2 121
-// and 133, 4001^2 144 and 160).
+// 200^3 (runs of 800 bytes) 154 and 160. FP32 states far beyond it stream where one block, or one and a little,
+// holds a row (190^3, 521 MB, 134 and 139, 250^3 296 and 323, D3Q15 250^3 267 and 276; but D3Q15 78x572x208 183 and
+// 158, D3Q19 349x416x64 221 and 207, FP16 250^3 213 and 206), in 2D all that pass it (3701^2 121 and 133, 4001^2
+// 144 and 160).
 inline bool cached_strain(const Geo& G, int q, size_t elem) {
   const size_t bytes = G.N * elem * q;
   if (bytes <= (size_t(1) << 28)) return true;
-  return !runs_aligned(G, elem, 32) && (elem == 2 || (q != 9 && bytes <= (size_t(480) << 20)));
+  if (runs_aligned(G, elem, 32)) return false;
+  return elem == 2 || (q != 9 && (bytes <= (size_t(480) << 20) || G.nx <= 128 || G.nx > 320));
 }
 // The populations query (canonical planes out, as many bytes again) loads and stores through the
 // caches where runs share lines, and where both ends fit: FP32 171x133x95 110 and 66, 200^3 321 and

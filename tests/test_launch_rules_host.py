@@ -152,6 +152,7 @@ def test_adjoint_access(box, law, mode):
     (19, (128, 128, 128), F32, True), (19, (256, 256, 256), F32, False), (19, (256, 256, 256), F16, False),
     (19, (171, 133, 95), F32, True), (19, (300, 100, 100), F32, True), (19, (200, 200, 200), F16, True),
     (19, (200, 200, 200), F32, False), (19, (181, 181, 181), F32, True), (19, (190, 190, 190), F32, False),
+    (15, (78, 572, 208), F32, True), (19, (349, 416, 64), F32, True), (19, (301, 301, 301), F32, False),
     (19, (250, 250, 250), F32, False), (15, (250, 250, 250), F32, False), (19, (250, 250, 250), F16, True),
     (9, (2701, 2700, 1), F32, True), (9, (3001, 3000, 1), F32, False), (9, (4097, 4096, 1), F32, False), (9, (4097, 4096, 1), F16, True),
 ])
