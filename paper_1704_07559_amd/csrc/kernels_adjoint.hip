@@ -441,11 +441,11 @@ __global__ __launch_bounds__(kMaxBlock) void init_adjoint_kernel(Geo G, ModelF M
 
 // How a reverse step accesses the adjoint state (XMODE). Rows that share 32-byte sectors go through the caches
 // while a step's arrays (record, adjoint state in and out, force gradient) are at most 384 MB, and again where
-// they are far beyond the 256 MB last-level cache; between, and in rows wider than a block, streaming accesses
-// leave it to the record (us a step in a sweep, streaming and cached: 100^3 Smagorinsky 44.6 and 38.8, 187^3 307
-// and 291; 228x96x160 141 and 155, 700x60x60 109 and 124, constant viscosity 98 and 104; 173^3 constant 202 and
-// 196; 388x576x32 399 and 421). Not in boxes whose step is one latency long (101x17x75 7.5 and 8.8, 60^3 11.0 and
-// 9.7). Whole-row blocks (pull_mode 2) exchange the x-shifted adjoint elements through LDS.
+// they are far beyond the 256 MB last-level cache; between, streaming accesses leave it to the record, at constant
+// viscosity (a short record) only in rows wider than a block (us a step in a sweep, streaming and cached: 100^3
+// Smagorinsky 44.6 and 38.8, 187^3 307 and 291, 470x88x192 424 and 403; 228x96x160 141 and 155, 700x60x60 109 and
+// 124, constant viscosity 98 and 104, 388x576x32 399 and 421; 173^3 constant 202 and 196). Not in boxes whose step
+// is one latency long (101x17x75 7.5 and 8.8, 60^3 11.0 and 9.7). Whole-row blocks (pull_mode 2) exchange the x-shifted adjoint elements through LDS.
 int adjoint_mode(const Geo& G, const ViscF& V) {
   const int pull = pull_mode(G, node_launch(G).block);
   const bool lagged = V.kind == 1 || V.kind == 2;

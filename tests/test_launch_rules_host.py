@@ -142,6 +142,7 @@ def test_packed_rows(lattice, box, law, storage, packed):
     # a block holds the row
     ((228, 96, 160), "smag", 1), ((235, 20, 544), "implicit", 1), ((700, 60, 60), "smag", 1), ((700, 60, 60), "const", 1),
     ((173, 173, 173), "const", 3), ((187, 187, 187), "smag", 3), ((388, 576, 32), "smag", 1), ((388, 576, 32), "const", 1),
+    ((470, 88, 192), "smag", 3), ((500, 63, 250), "const", 3),
 ])
 def test_adjoint_access(box, law, mode):
     from paper_1704_07559_amd import capi
