@@ -238,59 +238,42 @@ def leg(torch, capi, sim, nodes, steps, warmup, bytes_per_node, **extra):
     return out, r
 
 
+def _box(nx, ny, nz, q=19, storage="f32", law="smagorinsky", walls=False):
+    """Library parameters of a box, for its launch rules."""
+    from paper_1704_07559_amd import capi
+    return capi.Params(lattice=q, nx=nx, ny=ny, nz=nz, walls_y=int(walls), s=rates(0.51) if q == 19 else rates15(0.51),
+                       storage={"f32": capi.LBM_F32, "f16": capi.LBM_F16, "bf16": capi.LBM_BF16}[storage],
+                       visc_kind={"smagorinsky": capi.LBM_VISC_SMAGORINSKY, "powerlaw": capi.LBM_VISC_POWERLAW,
+                                  "implicit": capi.LBM_VISC_SMAGORINSKY_IMPLICIT}[law],
+                       visc_strain=capi.LBM_STRAIN_CHAI if law == "powerlaw" else capi.LBM_STRAIN_YU)
+
+
 def pair_plan(nx, ny, nz, q=19):
-    """Whether the library takes two FP32 steps per launch on a box (its launch rule restated), for the
-    cases it groups: no body force, constant viscosity or Smagorinsky with the Yu strain."""
-    n = nx * ny * nz
-    if n <= 1 << 18:
-        return False
-    fits, aligned, least = n * q * 4 <= 1 << 27, nx % 16 == 0, None
-    for tx in range((nx + 125) // 126, (nx + 125) // 126 + 6):
-        cols = -(-nx // tx)
-        if not fits and aligned and tx > 1:
-            cols = -(-cols // 16) * 16
-        most = 1024 // (cols + 2) - 2
-        for rows in range(most, max(3, most // 2), -1) if cols <= 126 else ():
-            columns, waves = -(-nx // cols) * -(-ny // rows), ((cols + 2) * (rows + 2) + 63) // 64
-            plane = 217 * waves + (rows + 2) * (78 + (cols + 2) * 5 // 2)
-            for rounds in range(-(-columns // 256), -(-columns // 256) + 8):
-                planes = -(-nz // min(256 * rounds // columns, nz))
-                cost = -(-columns * -(-nz // planes) // 256) * (planes + 2) * plane
-                least = cost if least is None else min(least, cost)
-    packed = nx <= 512 and (nx % 16 != 0 or (nx > 256 and nx % 64 != 0))
-    return least is not None and 500 * least <= (26 if not fits else 60 if packed else 37) * n
+    """Whether the library takes two FP32 LES steps per launch on a box (it is asked)."""
+    from paper_1704_07559_amd import capi
+    return capi.pair_route(_box(nx, ny, nz, q))["steps"] == 2
 
 
 def les_step(n, solve=False):
     """(kernel instance, bytes per node and step, source sha, steps per launch) of the FP32 LES step on n^3."""
-    if not pair_plan(n, n, n):
-        return step_kernel_name(n, n), 152 if solve else 160, kernel_source_sha(), 1
-    whole = "true" if step_kernel_name(n, n).split(", ")[2] == "2" else "false"
-    stream = "false" if n ** 3 * 76 <= 1 << 27 or (n % 16 and n ** 3 * 76 > 1 << 28) else "true"
-    return (f"lbm::pair_kernel<lbm::d3q19::PairUpdate<{3 if solve else 1}, {whole}>, false, {stream}>",
-            76 if solve else 80, kernel_source_sha(PAIR_SOURCES), 2)
+    from paper_1704_07559_amd import capi
+    law = "implicit" if solve else "smagorinsky"
+    box = _box(n, n, n, law=law)
+    route = capi.pair_route(box)
+    if route["steps"] != 2:
+        return step_kernel_name(n, n, nz=n, law=law), 152 if solve else 160, kernel_source_sha(), 1
+    exchanged = str(capi.step_route(box)["mode"] == 2).lower()
+    return (f"lbm::pair_kernel<lbm::d3q19::PairUpdate<{3 if solve else 1}, {exchanged}>, false, "
+            f"{str(route['stream']).lower()}>", 76 if solve else 80, kernel_source_sha(PAIR_SOURCES), 2)
 
 
-def step_kernel_name(nx, ny, storage="f32", walls=False, corrected=False):
-    """The D3Q19 step kernel instance the library launches for a box (its launch rule restated:
-    rows split into segments of the widest power of two <= 256 dividing nx when nx is a
-    multiple of 64, else one masked segment; pull mode 2 (whole rows, LDS exchange) when one
-    block holds whole rows of >= 64 nodes and its rows tile ny, 1 when a segment covers the
-    row, 0 for part rows)."""
-    tx = 256
-    if nx % 64 == 0:
-        while nx % tx:
-            tx //= 2
-    else:
-        tx = 1
-        while tx < nx and tx < 256:
-            tx *= 2
-    py = 1
-    while py < ny:
-        py *= 2
-    ty = min(256 // tx, py)
-    mode = 2 if (tx == nx and tx >= 64 and ny % ty == 0) else (1 if tx >= nx else 0)
+def step_kernel_name(nx, ny, storage="f32", walls=False, corrected=False, nz=1, law="smagorinsky"):
+    """The D3Q19 step kernel instance the library launches for a box (it is asked for the pull mode; the
+    exchange with the rate loaded at its use is instance 4)."""
+    from paper_1704_07559_amd import capi
+    r = capi.step_route(_box(nx, ny, nz, 19, storage, law, walls))
     st = {"f32": "float", "f16": "_Float16", "bf16": "__bf16"}[storage]
+    mode = 4 if r["late"] else r["mode"]
     return f"lbm::d3q19::step_kernel<{st}, {str(walls).lower()}, {mode}, {str(corrected).lower()}>"
 
 
@@ -307,7 +290,7 @@ def channel_runs(torch, capi, lbm, steps, warmup):
         sim = lbm.LBM(w.params(cfg, n_pl=n_pl))
         log(f"power-law channel n={n_pl}")
         o, r = leg(torch, capi, sim, N, steps, warmup, 160, umax=None,
-                   kernel=step_kernel_name(nx, ny, walls=True))
+                   kernel=step_kernel_name(nx, ny, walls=True, nz=nz, law="powerlaw"))
         o["umax"] = r["diag"]["umax"]
         sim.close()
         out[f"n{n_pl}"] = o
@@ -785,7 +768,7 @@ def main():
     torch.cuda.empty_cache()
     wall, kern, diag = r["wall"], r["kernel_s"], r["diag"]
     mlups = N * args.steps / wall / 1e6
-    # 160 B a node and launch; the library takes two steps per launch where pair_plan says so
+    # 160 B a node and launch; the library takes two steps per launch where its launch rule says so
     kernel, bytes_per_node, psha, per_launch = les_step(n)
     achieved = bytes_per_node * N / kern / 1e9
     sha = kernel_source_sha()
@@ -836,7 +819,7 @@ def main():
             s3 = lbm.LBM(les_params(capi, m, st), rho_u3)
             log(f"{name} {m}^3")
             o, r3 = leg(torch, capi, s3, m ** 3, K, W, bpn,
-                        kernel=les_step(m)[0] if name == "f32" else step_kernel_name(m, m, name))
+                        kernel=les_step(m)[0] if name == "f32" else step_kernel_name(m, m, name, nz=m))
             if name == "f16":
                 o["valu_issue_frac"] = valu_frac(read_valu("f16_les384", sha), r3["kernel_s"])
             extra[f"les384_{name}"] = o
@@ -854,7 +837,7 @@ def main():
         log(f"f16 {m}x{m}x{zs} slab")
         halo = 2 * 5 * m * m * 2  # the 5 populations with c_z = +1 and the 5 with c_z = -1, FP16
         extra["slab_384x384x48_f16"], _ = leg(torch, capi, ss, m * m * zs, K, W, 84, halo_bytes_per_step=halo,
-                                              kernel=step_kernel_name(m, m, "f16"))
+                                              kernel=step_kernel_name(m, m, "f16", nz=zs))
         ss.close()
         del ss, slab, rho_u3
         torch.cuda.empty_cache()

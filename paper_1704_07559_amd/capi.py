@@ -305,10 +305,11 @@ def lbm_last_error() -> str:
 
 def pair_route(params: Params) -> dict:
     """How the steps that lbm_step groups run on a box: ``steps`` per launch (1 or 2) and, for 2, the
-    ``tile`` (columns, rows, planes) of a block, the ``tiles`` and the ``threads`` per block."""
-    v = (ctypes.c_int * 6)()
+    ``tile`` (columns, rows, planes) of a block, the ``tiles``, the ``threads`` per block, and whether the 3D
+    lattices' stores ``stream``."""
+    v = (ctypes.c_int * 7)()
     _check(_lib.lbm_internal_pair_route(ctypes.byref(params.to_c()), v), "lbm_internal_pair_route")
-    return {"steps": v[0], "tile": (v[1], v[2], v[3]), "tiles": v[4], "threads": v[5]}
+    return {"steps": v[0], "tile": (v[1], v[2], v[3]), "tiles": v[4], "threads": v[5], "stream": bool(v[6])}
 
 
 def step_route(params: Params) -> dict:

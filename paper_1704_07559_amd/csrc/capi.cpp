@@ -638,13 +638,14 @@ lbm_status model_of(const lbm_params* p, lbm_ctx* c) {
 extern "C" {
 
 // How the steps of a box that run in groups of four run two per launch: steps per launch, columns, rows and planes
-// of a block's tile, tiles, threads.
-lbm_status lbm_internal_pair_route(const lbm_params* p, int out[6]) {
+// of a block's tile, tiles, threads, streamed stores (0, 1; the 3D lattices).
+lbm_status lbm_internal_pair_route(const lbm_params* p, int out[7]) {
   lbm_ctx c{};
   const lbm_status st = model_of(p, &c);
   if (st != LBM_OK) return st;
   const PairPlan P = plan_of(&c);
-  const int v[6] = {P.planes ? 2 : 1, P.cols, P.rows, P.planes, P.tiles, P.threads};
+  const int stream = P.planes && c.Q != 9 && pair_stream(c.G, c.Q) ? 1 : 0;
+  const int v[7] = {P.planes ? 2 : 1, P.cols, P.rows, P.planes, P.tiles, P.threads, stream};
   std::memcpy(out, v, sizeof(v));
   return LBM_OK;
 }

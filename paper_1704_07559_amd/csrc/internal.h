@@ -326,6 +326,17 @@ inline bool packed_rows(const Geo& G, int q, size_t elem, const ViscF& V) {
 // (171x133x95 FP16, 82 MB a buffer: 35 us cached, 40 streamed; 250^3 FP32 462 and 432).
 inline bool packed_stream(const Geo& G, int q, size_t elem) { return G.N * elem * q > (size_t(128) << 20); }
 
+// The 3D two-step launches store through the caches where both population buffers fit the 256 MB
+// last-level cache, which then holds the state from one launch to the next, and where tiles meet inside
+// lines in boxes far beyond it (us a step, constant viscosity, streamed and cached: 96^3 21.3 and 16.2,
+// 120^3 37.9 and 27.6, but 128^3, 159 MB a buffer, 40.9 and 44.3; rows of 16 n + r floats: 150^3, 245 MB a
+// buffer, 85 and 87, 180^3 130 and 117, 250^3 319 and 286).
+inline bool pair_fits(const Geo& G, int q) { return !packed_stream(G, q, sizeof(float)); }
+inline bool pair_stream(const Geo& G, int q) {
+  if (pair_fits(G, q)) return false;
+  return (G.nx * sizeof(float)) % 64 == 0 || size_t(G.N) * sizeof(float) * q <= (size_t(1) << 28);
+}
+
 // How a step launch pulls along x: 0 blocks hold part of a row (x-shifted loads cached, as
 // a neighbouring block reads their edge lines too); 1 blocks hold whole rows with masked
 // lanes (every load streams); 2 blocks hold whole rows exactly (LDS exchange above).

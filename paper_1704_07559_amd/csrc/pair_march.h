@@ -133,17 +133,6 @@ __global__ __launch_bounds__(kPairNodes, 4) void pair_kernel(Geo G, PairPlan P, 
   }
 }
 
-// Stores go through the caches where both population buffers fit the 256 MB last-level cache, which
-// then holds the state from one launch to the next, and where tiles meet inside lines in boxes far
-// beyond it (us a step, constant viscosity, streamed and cached: 96^3 21.3 and 16.2, 120^3 37.9 and 27.6,
-// but 128^3, 159 MB a buffer, 40.9 and 44.3; rows of 16 n + r floats: 150^3, 245 MB a buffer, 85 and 87,
-// 180^3 130 and 117, 250^3 319 and 286).
-inline bool pair_fits(const Geo& G, int q) { return !packed_stream(G, q, sizeof(float)); }
-inline bool pair_stream(const Geo& G, int q) {
-  if (pair_fits(G, q)) return false;
-  return runs_aligned(G, sizeof(float), 64) || size_t(G.N) * sizeof(float) * q <= (size_t(1) << 28);
-}
-
 template <class Update>
 hipError_t launch_march(const PairPlan& P, hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V,
                         const void* src, void* dst, const float* snu_in, float* snu_out) {
