@@ -241,7 +241,8 @@ def leg(torch, capi, sim, nodes, steps, warmup, bytes_per_node, **extra):
 def _box(nx, ny, nz, q=19, storage="f32", law="smagorinsky", walls=False):
     """Library parameters of a box, for its launch rules."""
     from paper_1704_07559_amd import capi
-    return capi.Params(lattice=q, nx=nx, ny=ny, nz=nz, walls_y=int(walls), s=rates(0.51) if q == 19 else rates15(0.51),
+    return capi.Params(lattice=q, nx=nx, ny=ny, nz=nz, walls_y=int(walls),
+                       s=rates(0.51) if q == 19 else rates15(0.51),
                        storage={"f32": capi.LBM_F32, "f16": capi.LBM_F16, "bf16": capi.LBM_BF16}[storage],
                        visc_kind={"smagorinsky": capi.LBM_VISC_SMAGORINSKY, "powerlaw": capi.LBM_VISC_POWERLAW,
                                   "implicit": capi.LBM_VISC_SMAGORINSKY_IMPLICIT}[law],

@@ -29,7 +29,8 @@
  *   - Every pointer argument named as a field is a DEVICE pointer, caller-owned, and must
  *     stay valid while the context uses it. Population buffers must be 256-byte aligned,
  *     other fields 4-byte aligned. No entry point allocates device memory except lbm_init
- *     (a small reduction scratch, with a second s_nu field behind it where steps are grouped) and none frees caller memory.
+ *     (a small reduction scratch, with a second s_nu field behind it where steps are grouped)
+ *     and none frees caller memory.
  *   - `stream` is a hipStream_t passed as void* (NULL = the null stream). Every call is
  *     asynchronous on that stream, except where a host result is returned (lbm_reduce,
  *     lbm_strain_loss_seed), which synchronise the stream before returning
@@ -129,9 +130,10 @@ size_t lbm_population_bytes(const lbm_params* p);
  * Create a context over caller-owned device buffers and write the initial state.
  *  f_a, f_b     two distinct population buffers of lbm_population_bytes(p) bytes.
  *  s_nu_field   device float[N]; required for LBM_VISC_SMAGORINSKY and LBM_VISC_POWERLAW
- *               (may be NULL otherwise). Filled with the initial s_nu. For D2Q9, whose
- *               steps go two per launch (see lbm_step), the context allocates a second
- *               float[N] for the field between the two launches of a four-step group.
+ *               (may be NULL otherwise). Filled with the initial s_nu. With a lagged law
+ *               the context of a box whose steps go two per launch (see lbm_step; any
+ *               lattice) allocates a second float[N] for the field between the two
+ *               launches of a four-step group; where it cannot, its steps run singly.
  *  rho_u        device float[4*N]: planes delta_rho, u_x, u_y, u_z (u_z ignored for D2Q9);
  *               NULL = fluid at rest. Initial populations are g^eq(delta_rho, rho0 u)
  *               (the delta-rho form of Eq. edf).
@@ -148,12 +150,12 @@ lbm_status lbm_init(lbm_ctx** out, const lbm_params* p, void* f_a, void* f_b, fl
 
 /*
  * Advance nsteps steps of Eq. mrteq (collide with moment-space relaxation, Eq. mrteqvT,
- * then pull streaming), one fused kernel per step. D2Q9, and D3Q19 and D3Q15 in FP32 without body
- * force or `save`, at constant viscosity or either Smagorinsky model with the Yu strain (boxes
- * beyond 2^18 nodes that the launch fills well), take their steps in groups of four
- * as two launches of two steps each (the intermediate level never leaves the chip: half the HBM
- * traffic, half the launches); the remaining steps run singly. The result is the same, bit for
- * bit, as that of nsteps single steps.
+ * then pull streaming), one fused kernel per step. Where it is faster, steps go in groups of
+ * four as two launches of two steps each (the intermediate level never leaves the chip: half
+ * the HBM traffic, half the launches): D2Q9 boxes whose width fills the launch's lanes, and
+ * boxes of D3Q19 and D3Q15 beyond 2^18 nodes in FP32 without body force or `save`, at constant
+ * viscosity or either Smagorinsky model with the Yu strain. The remaining steps run singly. The
+ * result is the same, bit for bit, as that of nsteps single steps.
  *  S_out        device float[6*N] (D3Q19, D3Q15) / [3*N] (D2Q9) or NULL: the strain (formula
  *               `strain_kind`) of the last step's pre-collision state, i.e. of the state at
  *               level n_end - 1.

@@ -256,7 +256,8 @@ lbm_status lbm_init(lbm_ctx** out, const lbm_params* p, void* f_a, void* f_b, fl
     (void)hipGetLastError();
     return fail(LBM_ENOMEM, std::string("hipMalloc of the reduction scratch failed: ") + hipGetErrorString(e));
   }
-  if (c->pair_plan.planes && pair_bytes) c->snu_pair = reinterpret_cast<float*>(reinterpret_cast<char*>(c->scratch) + scratch_bytes);
+  if (c->pair_plan.planes && pair_bytes)
+    c->snu_pair = reinterpret_cast<float*>(reinterpret_cast<char*>(c->scratch) + scratch_bytes);
   const hipStream_t s = as_stream(stream);
   switch (c->Q) {
     case 19: e = d3q19::launch_init(p->storage, c->G, c->M, c->buf[0], c->snu, rho_u, grad_u, s); break;

@@ -446,8 +446,8 @@ constexpr size_t packed_lds_bytes(int nx, int rows) {
   return (static_cast<size_t>(rows) * Q * nx + 16 / sizeof(S) - 1) * sizeof(S);
 }
 template <int Q, typename S>
-__device__ __forceinline__ void store_rows_packed(S* __restrict__ dst, const Geo& G, S* sh, bool on, int z, bool stream,
-                                                  const float (&g)[Q]) {
+__device__ __forceinline__ void store_rows_packed(S* __restrict__ dst, const Geo& G, S* sh, bool on, int z,
+                                                  bool stream, const float (&g)[Q]) {
   constexpr unsigned V = 16 / sizeof(S);
   const int y0 = blockIdx.y * blockDim.y;
   const unsigned rows = min(static_cast<int>(blockDim.y), G.ny - y0);

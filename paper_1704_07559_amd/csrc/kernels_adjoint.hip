@@ -445,7 +445,8 @@ __global__ __launch_bounds__(kMaxBlock) void init_adjoint_kernel(Geo G, ModelF M
 // viscosity (a short record) only in rows wider than a block (us a step in a sweep, streaming and cached: 100^3
 // Smagorinsky 44.6 and 38.8, 187^3 307 and 291, 470x88x192 424 and 403; 228x96x160 141 and 155, 700x60x60 109 and
 // 124, constant viscosity 98 and 104, 388x576x32 399 and 421; 173^3 constant 202 and 196). Not in boxes whose step
-// is one latency long (101x17x75 7.5 and 8.8, 60^3 11.0 and 9.7). Whole-row blocks (pull_mode 2) exchange the x-shifted adjoint elements through LDS.
+// is one latency long (101x17x75 7.5 and 8.8, 60^3 11.0 and 9.7). Whole-row blocks (pull_mode 2) exchange the
+// x-shifted adjoint elements through LDS.
 int adjoint_mode(const Geo& G, const ViscF& V) {
   const int pull = pull_mode(G, node_launch(G).block);
   const bool lagged = V.kind == 1 || V.kind == 2;
@@ -495,9 +496,18 @@ hipError_t launch_loss_seed(int storage, const Geo& G, const ModelF& M, const Vi
   const unsigned nb = reduce_blocks(G);
   const NodeWalk W = node_walk(G);
   switch (storage) {
-    case 0: hipLaunchKernelGGL(loss_seed_kernel<float>, dim3(nb), dim3(256), 0, st, G, M, V, Fo, W, static_cast<const float*>(buf), snu, lam_out, grad_force, partials); break;
-    case 1: hipLaunchKernelGGL(loss_seed_kernel<_Float16>, dim3(nb), dim3(256), 0, st, G, M, V, Fo, W, static_cast<const _Float16*>(buf), snu, lam_out, grad_force, partials); break;
-    case 2: hipLaunchKernelGGL(loss_seed_kernel<__bf16>, dim3(nb), dim3(256), 0, st, G, M, V, Fo, W, static_cast<const __bf16*>(buf), snu, lam_out, grad_force, partials); break;
+    case 0:
+      hipLaunchKernelGGL(loss_seed_kernel<float>, dim3(nb), dim3(256), 0, st, G, M, V, Fo, W,
+                         static_cast<const float*>(buf), snu, lam_out, grad_force, partials);
+      break;
+    case 1:
+      hipLaunchKernelGGL(loss_seed_kernel<_Float16>, dim3(nb), dim3(256), 0, st, G, M, V, Fo, W,
+                         static_cast<const _Float16*>(buf), snu, lam_out, grad_force, partials);
+      break;
+    case 2:
+      hipLaunchKernelGGL(loss_seed_kernel<__bf16>, dim3(nb), dim3(256), 0, st, G, M, V, Fo, W,
+                         static_cast<const __bf16*>(buf), snu, lam_out, grad_force, partials);
+      break;
     default: return hipErrorInvalidValue;
   }
   hipError_t e = hipGetLastError();

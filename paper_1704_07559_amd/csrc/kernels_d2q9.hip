@@ -250,9 +250,9 @@ __global__ __launch_bounds__(kMaxBlock) void step_kernel(Geo G, ModelF M, ViscF 
 // blocks to overlap one another's barriers and memory waits, and a longer chain of rows (about
 // 2 us each) where the blocks do not fill the chip. Large boxes, 4096^2: FP32 160 us per step
 // at 6 rows, 176 at 2, 163 at 8 and 162 at 12; FP16 111 at 12, 116 at 6, 143 at 2. Below 1280
-// blocks of 256 lanes (5 per CU; 2560 of 128) every row fewer wins: 600 x 201 between walls 5.0 us per step at 1 row, 5.7
-// at 2, 8.7 at 6; 256^2 4.4, 5.0, 8.4; 1024^2 FP32 18.3 at 1, 13.6 at 4 (1280 blocks), 14.5 at 6,
-// FP16 15.5, 11.0, 12.1 and 16.3 at 12; 100 x 3000 (128 lanes) 6.3 at 1, 6.1 at 2, 6.4 at 3.
+// blocks of 256 lanes (5 per CU; 2560 of 128) every row fewer wins: 600 x 201 between walls 5.0 us per
+// step at 1 row, 5.7 at 2, 8.7 at 6; 256^2 4.4, 5.0, 8.4; 1024^2 FP32 18.3 at 1, 13.6 at 4 (1280 blocks), 14.5
+// at 6, FP16 15.5, 11.0, 12.1 and 16.3 at 12; 100 x 3000 (128 lanes) 6.3 at 1, 6.1 at 2, 6.4 at 3.
 template <typename S>
 constexpr int kPairMaxRows = sizeof(S) == 4 ? 6 : 12;
 template <typename S>
@@ -285,9 +285,9 @@ constexpr int ring_row(int i) { return i == 0 ? 0 : ring_row<WALLS>(i - 1) + rin
 // the second step's incoming state, which single steps leave in S_out last); a template
 // parameter, as its code costs the instances without it 15 VGPRs otherwise.
 template <typename S, int B, bool WALLS, bool CORR, bool EMIT>
-__global__ __launch_bounds__(B) void pair_kernel(Geo G, int R, ModelF M, ViscF V, ForceF Fo, const S* __restrict__ src,
-                                                 S* __restrict__ dst, const float* snu_in, float* snu_out,
-                                                 float* S_out, int emit) {
+__global__ __launch_bounds__(B) void pair_kernel(Geo G, int R, ModelF M, ViscF V, ForceF Fo,
+                                                 const S* __restrict__ src, S* __restrict__ dst,
+                                                 const float* snu_in, float* snu_out, float* S_out, int emit) {
   // (in the storage type: level 1 is rounded to it anyway, and 16-bit rows halve the LDS)
   __shared__ S ring[ring_row<WALLS>(Q)][B];
   const int lane = threadIdx.x;
@@ -318,7 +318,8 @@ __global__ __launch_bounds__(B) void pair_kernel(Geo G, int R, ModelF M, ViscF V
       float Fx, Fy;
       load_force(Fo, G.N, self1, Fx, Fy);
       snu1 = collide<CORR>(
-          G, M, V, Fo, self1, [&] { return ahead || !snu_in ? snu0 : snu_in[self1]; }, [](float) {}, Fx, Fy, nullptr, 0, g);
+          G, M, V, Fo, self1, [&] { return ahead || !snu_in ? snu0 : snu_in[self1]; }, [](float) {}, Fx, Fy,
+          nullptr, 0, g);
       static_for<Q>([&](auto ii) {
         constexpr int i = ii;
         if constexpr (sizeof(S) == 2) g[i] = static_cast<float>(static_cast<S>(g[i]));
@@ -618,8 +619,8 @@ PairPlan pair_plan(int storage, const Geo& G, const ViscF& V) {
   return P.planes && pair_pays(storage, G, V, P) ? P : PairPlan{};
 }
 
-hipError_t launch_pair(const PairPlan& P, int storage, const Geo& G, const ModelF& M, const ViscF& V, const ForceF& Fo,
-                       const void* src, void* dst, const float* snu_in, float* snu_out, float* S_out, int emit,
+hipError_t launch_pair(const PairPlan& P, int storage, const Geo& G, const ModelF& M, const ViscF& V,
+                       const ForceF& Fo, const void* src, void* dst, const float* snu_in, float* snu_out, float* S_out, int emit,
                        hipStream_t st) {
   if (P.planes != 1 || P.rows < 1 || (P.threads != 128 && P.threads != 256)) return hipErrorInvalidValue;
   if ((V.kind == 1 || V.kind == 2) != (snu_in != nullptr) || (snu_in != nullptr) != (snu_out != nullptr) ||

@@ -117,8 +117,8 @@ __device__ __forceinline__ float implicit_rate(const Pairs& P_, float drho, floa
 // loaded at its use. CORR: the force-corrected strain (a separate instance, so that the plain
 // step keeps its register budget).
 template <typename S, bool WALLS, int XMODE, bool CORR>
-__global__ __launch_bounds__(XMODE == 3 ? kMaxPackedBlock : kMaxBlock) void step_kernel(Geo G, ModelF M, ViscF V,
-                                                                                       ForceF Fo, StepIO io) {
+__global__ __launch_bounds__(XMODE == 3 ? kMaxPackedBlock : kMaxBlock)
+void step_kernel(Geo G, ModelF M, ViscF V, ForceF Fo, StepIO io) {
   const int x = blockIdx.x * blockDim.x + threadIdx.x;
   const int y = blockIdx.y * blockDim.y + threadIdx.y;
   const int z = blockIdx.z;
@@ -384,9 +384,10 @@ static const S* cb(const void* p) {
 }
 
 // FP32 in whole 256-node rows: 4 blocks per CU instead of 7 (+4.4 % at 256^3; 3 blocks lost
-// 2 %). See lds_cap_bytes. Other exchanged rows load the rate at its use where the block per CU that loading
-// it ahead costs would cost a round too (us a step ahead and at its use: 64x356x20 Smagorinsky FP32 11.6 and 9.5,
-// FP16 7.0 and 6.3, 64x220x20 without a rate 7.9 and 7.0; but 64x48x20 4.6 and 4.9).
+// 2 %). See lds_cap_bytes. Other exchanged rows load the rate at its use between 4 and 12 blocks per CU, 4 and 6
+// without a rate (us a step ahead and at its use: 64x356x20 Smagorinsky FP32 11.6 and 9.5, FP16 7.0 and 6.3,
+// 64x220x20 without a rate 7.9 and 7.0; but 64x48x20 4.6 and 4.9). The lines are measured: registers and blocks
+// per CU are the same either way.
 static StepRoute route_of(size_t elem, const Launch& L, const Geo& G, const ViscF& V) {
   if (packed_rows(G, Q, elem, V)) return StepRoute{3, 0, false};
   StepRoute r{pull_mode(G, L.block), 0, false};

@@ -1,5 +1,5 @@
-// D3Q15, two steps per launch: FP32 storage, periodic boxes, no body force, constant viscosity or the
-// lagged Smagorinsky model with the Yu-type strain.
+// D3Q15, two steps per launch: FP32 storage, periodic or with walls, no body force, constant viscosity or the
+// Smagorinsky model, lagged or implicit, with the Yu-type strain.
 #include <hip/hip_runtime.h>
 
 #include "d3q15.h"
@@ -56,7 +56,8 @@ struct PairUpdate {
     if constexpr (KIND == 3) {
       // implicit_rate: strain_yu at (s_e, 0) and at (0, 1)
       const float a = M.s[1] * n1;
-      const float Pm[6] = {-a * (0.5f * ir), -(2.0f * a) * (0.25f * ir), -(2.0f * a) * (0.25f * ir), 0.0f, 0.0f, 0.0f};
+      const float Pm[6] = {-a * (0.5f * ir), -(2.0f * a) * (0.25f * ir), -(2.0f * a) * (0.25f * ir), 0.0f, 0.0f,
+                           0.0f};
       const float A[6] = {-n9 * (0.5f * ir), -fma3(3.0f, n10, -n9) * (0.25f * ir), fma3(3.0f, n10, n9) * (0.25f * ir),
                           -1.5f * n11 * ir,  -1.5f * n12 * ir,                    -1.5f * n13 * ir};
       snu = implicit_smagorinsky(Pm, A, V.nu0, V.csmag2);

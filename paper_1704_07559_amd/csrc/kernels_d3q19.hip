@@ -181,8 +181,8 @@ static const S* cbuf(const void* p) {
 }
 
 template <typename S>
-static void launch_strain_t(const Launch& L, size_t lds, hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V,
-                            const ForceF& Fo, const void* buf, const float* snu, int kind, float* S_out) {
+static void launch_strain_t(const Launch& L, size_t lds, hipStream_t st, const Geo& G, const ModelF& M,
+                            const ViscF& V, const ForceF& Fo, const void* buf, const float* snu, int kind, float* S_out) {
   // (rows whose runs are aligned are multiples of 8 nodes)
   const auto k = !cached_strain(G, Q, sizeof(S)) ? strain_kernel<S, false, true>
                  : plane_stream(G)               ? strain_kernel<S, true, true>
@@ -249,7 +249,7 @@ hipError_t launch_set(int storage, const Geo& G, void* buf, const float* canon, 
 template <typename S>
 static void launch_reduce_t(unsigned nb, hipStream_t st, const Geo& G, const ModelF& M, const ViscF& V,
                             const ForceF& Fo, const S* buf, const float* snu, double* partials) {
-  // FP32 with more blocks than fit at once: 4 blocks per CU instead of the 6 its registers allow
+  // FP32 with more blocks than fit at once: 4 blocks per CU instead of the 7 its registers allow
   // (3.5 % less time per call at 256^3; 3 blocks 7 % more)
   const size_t cap = sizeof(S) == 4 && nb > kReduceFill ? lds_cap_bytes(4, 4 * kReduceVals * sizeof(double)) : 0;
   decltype(&reduce_kernel<S, false, false>) f;

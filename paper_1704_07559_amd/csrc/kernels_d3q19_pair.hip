@@ -1,5 +1,5 @@
-// D3Q19, two steps per launch: FP32 storage, periodic boxes, no body force, constant viscosity or
-// the lagged Smagorinsky model with the Yu strain. Reference: the pipeline of two ordinary steps.
+// D3Q19, two steps per launch: FP32 storage, periodic or with walls, no body force, constant viscosity or the
+// Smagorinsky model, lagged or implicit, with the Yu strain. Reference: the pipeline of two ordinary steps.
 #include <hip/hip_runtime.h>
 
 #include "d3q19.h"
@@ -14,7 +14,9 @@ namespace d3q19 {
 // to the compiler which product of a sum is fused; what it picks there depends on the code around
 // the sum, so the same source in this kernel rounds differently. The picks below are theirs:
 // all pull modes share them but the LDS exchange (XCHG), whose instances differ in two sums (o[3],
-// o[4]). Two steps of this kernel therefore equal two single steps bit for bit.
+// o[4]). Two steps of this kernel therefore equal two single steps bit for bit. That holds for the compiler
+// these picks were read from: another may fuse the step kernels' sums differently, which the tests of pairs
+// against single steps (every pull mode, law and lattice) then show, and the picks are to be renewed.
 template <int KIND, bool XCHG>
 struct PairUpdate {
   using Lat = d3q19::Lat;
@@ -133,8 +135,8 @@ PairPlan pair_tiles(int storage, const Geo& G, const ViscF& V, const ForceF& Fo,
 }
 
 template <bool XCHG>
-static hipError_t launch_kind(const PairPlan& P, const Geo& G, const ModelF& M, const ViscF& V, const void* src, void* dst,
-                              const float* snu_in, float* snu_out, hipStream_t st) {
+static hipError_t launch_kind(const PairPlan& P, const Geo& G, const ModelF& M, const ViscF& V, const void* src,
+                              void* dst, const float* snu_in, float* snu_out, hipStream_t st) {
   switch (V.kind) {
     case 0: return launch_march<PairUpdate<0, XCHG>>(P, st, G, M, V, src, dst, snu_in, snu_out);
     case 1: return launch_march<PairUpdate<1, XCHG>>(P, st, G, M, V, src, dst, snu_in, snu_out);

@@ -28,10 +28,11 @@ namespace d3q19 {
 // through mixed-precision FMAs. snu_ahead (AHEAD): the node's lagged rate (read only where io.snu is
 // given), which the caller loads along with the populations, so that its latency hides behind theirs
 // (ahead of the exchange's barrier, else right after their loads: in front of them its branch drags
-// every kernel argument's load there, 0.3 us more in a small box): at its use it cost 7 % of the BF16 384 x 384 x 48 step (105 us against 97.5) and 9 % of FP16
-// 200^3 (139 against 126). It is taken over inside the branch, and opaque, because merging that
-// branch into the code around changes which products of a sum the compiler fuses. Whole rows
-// pulled directly (small ragged boxes) keep the late load: 60^3 8.1 us a step against 8.8.
+// every kernel argument's load there, 0.3 us more in a small box): at its use it cost 7 % of the BF16
+// 384 x 384 x 48 step (105 us against 97.5) and 9 % of FP16 200^3 (139 against 126). It is taken over inside
+// the branch, and opaque, because merging that branch into the code around changes which products of a sum the
+// compiler fuses. Whole rows pulled directly (small ragged boxes) keep the late load: 60^3 8.1 us a step
+// against 8.8; so do exchanged rows in launches of a middle size (route_of).
 template <bool CORR, bool PACK, bool AHEAD>
 __device__ __forceinline__ void node_update(float (&g)[Q], unsigned self, const Geo& G, const ModelF& M,
                                             const ViscF& V, const ForceF& Fo, const StepIO& io, float snu_ahead) {
@@ -181,8 +182,8 @@ template <typename S, int XMODE, bool CORR>
 constexpr int kMinWavesPerEU = (kPackHalves<S, XMODE> && !CORR && XMODE != 3) ? 6 : 1;
 
 template <typename S, bool WALLS, int XMODE, bool CORR>
-__global__ __launch_bounds__(XMODE == 3 ? kMaxPackedBlock : kMaxBlock, (kMinWavesPerEU<S, XMODE, CORR>)) void step_kernel(Geo G, ModelF M, ViscF V,
-                                                                                       ForceF Fo, StepIO io) {
+__global__ __launch_bounds__(XMODE == 3 ? kMaxPackedBlock : kMaxBlock, (kMinWavesPerEU<S, XMODE, CORR>))
+void step_kernel(Geo G, ModelF M, ViscF V, ForceF Fo, StepIO io) {
   const int x = blockIdx.x * blockDim.x + threadIdx.x;
   const int y = blockIdx.y * blockDim.y + threadIdx.y;
   const int z = blockIdx.z;
@@ -231,11 +232,11 @@ static StepRoute route_of(size_t elem, const Launch& L, const Geo& G, const Visc
     else if (r.mode == 0 && L.block.x == 128 && L.block.y == 2)
       r.blocks = 4;
   }
-  // The rate loaded ahead takes the exchange's kernel from 6 blocks per CU to 5. It pays in small launches and in
-  // large ones; between, where the sixth block saves a round, the rate is loaded at its use (64x64x128 FP16 9.1 us
-  // a step and 9.9 ahead, 128x108x20 FP32 8.5 and 9.7; but 128x128x96 FP16 24.7 and 22.5), and so it is where
-  // there is no rate, from fewer blocks on (128x128x20 implicit 8.4 and 10.4, 64x64x48 const 6.1 and 6.3; 64x64x16
-  // 4.8 and 4.4).
+  // The exchange's kernel loads the rate ahead in small launches and in large ones (128x128x96 FP16 22.5 us a step
+  // and 24.7 at its use), but at its use between 4 and 9 blocks per CU, in every storage type (64x64x128 FP16 9.9
+  // ahead and 9.1, 128x108x20 FP32 9.7 and 8.5), and so it does where there is no rate, from fewer blocks on
+  // (128x128x20 implicit 10.4 and 8.4, 64x64x48 const 6.3 and 6.1; 64x64x16 4.4 and 4.8). The lines are measured:
+  // registers (87 and 90) and blocks per CU (5) are the same either way.
   const bool lagged = V.kind == 1 || V.kind == 2;
   const unsigned blocks = L.grid.x * L.grid.y * L.grid.z;
   r.late = r.mode == 2 && blocks > (lagged ? 1024 : 640) && blocks <= (r.blocks ? r.blocks * 256u : 2304);

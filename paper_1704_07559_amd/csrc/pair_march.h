@@ -1,5 +1,6 @@
 // Two steps per launch for the 3D lattices (FP32 storage, periodic or with walls, no body force, constant
-// viscosity or Smagorinsky, lagged or implicit, with the Yu strain): the marching kernel, its launch rule and its launch.
+// viscosity or Smagorinsky, lagged or implicit, with the Yu strain): the marching kernel, its launch rule
+// and its launch.
 // A lattice gives its node update as a type (Lat, kLagged, run).
 #pragma once
 #include <hip/hip_runtime.h>
@@ -31,7 +32,9 @@ __device__ __forceinline__ float fma3(float a, float b, float c) { return __buil
 // us a step, against single steps, Smagorinsky: D3Q19 256^3 297 (418), 384x384x128 316 (490), 200^3 153 (217),
 // 128^3 42 (54), 96^3 17.0 (24.8), D3Q15 256^3 252 (325), 200^3 125 (180), 96^3 14.7 (21.0); constant viscosity
 // at 256^3 270 (418) and 231 (323), implicit 299 (419) and 262 (320), Smagorinsky between walls 335 (446; that
-// instance spills 44 bytes) and 246 (337). Measured on the way, D3Q19 256^3: blocks dealt out over the XCDs in
+// D3Q19 instance fills 128 VGPRs and spills 44 bytes) and 246 (337). One block runs on a CU: its two LDS planes are
+// sized for 1024 nodes whatever the tile. At 256^3 a block has 704 threads (11 of the 16 waves that 126 VGPRs
+// allow) and uses 103 of its 160 KB. Measured on the way, D3Q19 256^3: blocks dealt out over the XCDs in
 // turn 325, two barriers and one plane of LDS 310, without the early loads 304.
 template <class Update, bool WALLS, bool STREAM>
 __global__ __launch_bounds__(kPairNodes, 4) void pair_kernel(Geo G, PairPlan P, ModelF M, ViscF V,

@@ -63,11 +63,11 @@ __device__ __forceinline__ Coord coord_of(const Geo& G, const NodeWalk& W, unsig
   return Coord{static_cast<int>(n - r * G.nx), static_cast<int>(r - z * G.ny), static_cast<int>(z)};
 }
 
-// Blocks of a reduction: one node per thread up to 1280 blocks (what fits the chip at the 5
-// blocks per CU the D3Q19 kernel's registers allow), then 16 nodes per thread up to
-// kReduceBlocks. The fold at a block's end costs as much as a few nodes: at 128^3 1280 blocks
-// take 35 us and 4096 take 41; at 256^3, where a block has 16 nodes per thread either way,
-// 4096 blocks balance better (221 against 224 us).
+// Blocks of a reduction: one node per thread up to 1280 blocks (5 per CU; the D3Q19 kernel's
+// registers allow 7), then as many as leave a thread 16 nodes, up to kReduceBlocks. Both lines are
+// measured: the fold at a block's end costs as much as a few nodes, so that at 128^3 1280 blocks
+// take 35 us and 4096 take 41, while at 256^3 4096 blocks (16 nodes per thread) balance better than
+// 1280 (51 per thread; 221 against 224 us).
 constexpr unsigned kReduceFill = 1280;
 inline unsigned reduce_blocks(const Geo& G) {
   const unsigned all = (G.N + 255) / 256;

@@ -12,7 +12,8 @@ def _params(lattice, box, law, storage=0, **kw):
     from paper_1704_07559_amd import capi
     nx, ny, nz = box
     kw.setdefault("visc_strain", capi.LBM_STRAIN_CHAI if law == "power" else capi.LBM_STRAIN_YU)
-    return capi.Params(lattice=lattice, nx=nx, ny=ny, nz=nz, storage=storage, s=RATES[lattice], visc_kind=LAWS[law], **kw)
+    return capi.Params(lattice=lattice, nx=nx, ny=ny, nz=nz, storage=storage, s=RATES[lattice],
+                       visc_kind=LAWS[law], **kw)
 
 
 @pytest.mark.parametrize("populations,rates,one_launch", [
@@ -45,7 +46,8 @@ F32, F16 = 0, 1
     ((62, 770), "power", F32, 1), ((128, 256), "power", F32, 1), ((1000, 1048), "power", F16, 1),
     ((64, 16384), "implicit", F16, 1), ((160, 1280), "implicit", F16, 1),
     # a launch's latency
-    ((1, 1), "smag", F32, 2), ((64, 64), "const", F32, 2), ((100, 100), "smag", F16, 2), ((200, 100), "implicit", F32, 2), ((61, 160), "implicit", F16, 2),
+    ((1, 1), "smag", F32, 2), ((64, 64), "const", F32, 2), ((100, 100), "smag", F16, 2),
+    ((200, 100), "implicit", F32, 2), ((61, 160), "implicit", F16, 2),
     ((100, 300), "implicit", F16, 1),
     # filled strips
     ((250, 1048), "smag", F32, 2), ((250, 16777), "smag", F16, 2), ((600, 201), "implicit", F32, 2),
@@ -95,7 +97,7 @@ def test_d3q15_rate_at_its_use(box, law, storage, late):
 
 
 @pytest.mark.parametrize("box,law,storage,late", [
-    # where the sixth block per CU saves a round: 1024 to 2304 blocks with a rate, 640 without
+    # 1024 to 2304 blocks with a rate, 640 to 2304 without
     ((64, 64, 64), "smag", F32, False), ((64, 64, 65), "smag", F32, True), ((64, 64, 128), "smag", F16, True),
     ((64, 64, 144), "smag", 2, True), ((64, 64, 145), "smag", F32, False), ((128, 128, 96), "smag", F16, False),
     ((128, 128, 20), "implicit", F32, True), ((64, 64, 40), "const", F32, False), ((64, 64, 41), "const", F32, True),
@@ -111,7 +113,8 @@ def test_d3q19_rate_at_its_use(box, law, storage, late):
 
 
 @pytest.mark.parametrize("lattice,box,law,storage,packed", [
-    (19, (171, 133, 95), "smag", F32, True), (19, (171, 133, 95), "power", F16, True), (19, (200, 200, 200), "const", F16, True),
+    (19, (171, 133, 95), "smag", F32, True), (19, (171, 133, 95), "power", F16, True),
+    (19, (200, 200, 200), "const", F16, True),
     (19, (200, 200, 200), "power", F32, True), (19, (300, 200, 200), "smag", F32, True),
     (19, (256, 256, 256), "smag", F32, False), (19, (224, 200, 200), "smag", F16, False),
     (19, (600, 200, 200), "smag", F32, False), (15, (200, 200, 200), "implicit", F32, True),
@@ -119,14 +122,19 @@ def test_d3q19_rate_at_its_use(box, law, storage, late):
     # a launch of less than a round of blocks
     (19, (60, 60, 60), "smag", F32, False), (19, (100, 64, 40), "smag", F16, False),
     # both buffers in the L2s
-    (19, (104, 60, 43), "const", F16, False), (19, (100, 82, 40), "smag", F16, False), (19, (100, 83, 40), "smag", F16, True),
-    (19, (67, 64, 65), "smag", F32, True), (19, (30, 30, 300), "smag", F16, True), (15, (100, 60, 60), "const", 2, False),
+    (19, (104, 60, 43), "const", F16, False), (19, (100, 82, 40), "smag", F16, False),
+    (19, (100, 83, 40), "smag", F16, True),
+    (19, (67, 64, 65), "smag", F32, True), (19, (30, 30, 300), "smag", F16, True),
+    (15, (100, 60, 60), "const", 2, False),
     (15, (43, 512, 13), "smag", 2, False), (15, (40, 93, 112), "smag", 2, False), (15, (129, 65, 62), "const", 2, True),
     (15, (33, 100, 100), "smag", 2, True),
-    (19, (104, 60, 43), "power", F16, False), (19, (56, 463, 16), "power", F16, False), (19, (28, 64, 156), "power", F32, False),
-    (19, (127, 140, 16), "power", F32, False), (19, (28, 64, 164), "power", F32, True), (19, (19, 100, 150), "power", F16, True), (15, (37, 112, 64), "power", F16, False),
+    (19, (104, 60, 43), "power", F16, False), (19, (56, 463, 16), "power", F16, False),
+    (19, (28, 64, 156), "power", F32, False),
+    (19, (127, 140, 16), "power", F32, False), (19, (28, 64, 164), "power", F32, True),
+    (19, (19, 100, 150), "power", F16, True), (15, (37, 112, 64), "power", F16, False),
     # few rows of a block each
-    (19, (511, 24, 24), "smag", F32, False), (19, (511, 32, 23), "const", F32, False), (19, (511, 32, 24), "const", F32, True),
+    (19, (511, 24, 24), "smag", F32, False), (19, (511, 32, 23), "const", F32, False),
+    (19, (511, 32, 24), "const", F32, True),
 ])
 def test_packed_rows(lattice, box, law, storage, packed):
     from paper_1704_07559_amd import capi
@@ -134,14 +142,17 @@ def test_packed_rows(lattice, box, law, storage, packed):
 
 
 @pytest.mark.parametrize("box,law,mode", [
-    ((128, 128, 128), "const", 2), ((256, 256, 256), "smag", 2), ((200, 200, 200), "smag", 1), ((320, 100, 100), "const", 1),
+    ((128, 128, 128), "const", 2), ((256, 256, 256), "smag", 2), ((200, 200, 200), "smag", 1),
+    ((320, 100, 100), "const", 1),
     # rows that share sectors: through the caches from 196608 nodes on
     ((60, 60, 54), "smag", 1), ((60, 60, 55), "smag", 3), ((65, 80, 80), "smag", 3), ((100, 100, 100), "power", 3),
     ((257, 40, 40), "const", 3),
     # not where a step's arrays pass 384 MB, unless they are far beyond the last-level cache or, at constant viscosity,
     # a block holds the row
-    ((228, 96, 160), "smag", 1), ((235, 20, 544), "implicit", 1), ((700, 60, 60), "smag", 1), ((700, 60, 60), "const", 1),
-    ((173, 173, 173), "const", 3), ((187, 187, 187), "smag", 3), ((388, 576, 32), "smag", 1), ((388, 576, 32), "const", 1),
+    ((228, 96, 160), "smag", 1), ((235, 20, 544), "implicit", 1), ((700, 60, 60), "smag", 1),
+    ((700, 60, 60), "const", 1),
+    ((173, 173, 173), "const", 3), ((187, 187, 187), "smag", 3), ((388, 576, 32), "smag", 1),
+    ((388, 576, 32), "const", 1),
     ((470, 88, 192), "smag", 3), ((500, 63, 250), "const", 3),
 ])
 def test_adjoint_access(box, law, mode):
@@ -155,7 +166,8 @@ def test_adjoint_access(box, law, mode):
     (19, (200, 200, 200), F32, False), (19, (181, 181, 181), F32, True), (19, (190, 190, 190), F32, False),
     (15, (78, 572, 208), F32, True), (19, (349, 416, 64), F32, True), (19, (301, 301, 301), F32, False),
     (19, (250, 250, 250), F32, False), (15, (250, 250, 250), F32, False), (19, (250, 250, 250), F16, True),
-    (9, (2701, 2700, 1), F32, True), (9, (3001, 3000, 1), F32, False), (9, (4097, 4096, 1), F32, False), (9, (4097, 4096, 1), F16, True),
+    (9, (2701, 2700, 1), F32, True), (9, (3001, 3000, 1), F32, False), (9, (4097, 4096, 1), F32, False),
+    (9, (4097, 4096, 1), F16, True),
 ])
 def test_strain_query_access(lattice, box, storage, cached):
     from paper_1704_07559_amd import capi
