@@ -154,8 +154,9 @@ lbm_status lbm_init(lbm_ctx** out, const lbm_params* p, void* f_a, void* f_b, fl
  * four as two launches of two steps each (the intermediate level never leaves the chip: half
  * the HBM traffic, half the launches): D2Q9 boxes whose width fills the launch's lanes, and
  * boxes of D3Q19 and D3Q15 beyond 2^18 nodes in FP32 without body force or `save`, at constant
- * viscosity or either Smagorinsky model with the Yu strain. The remaining steps run singly. The
- * result is the same, bit for bit, as that of nsteps single steps.
+ * viscosity or either Smagorinsky model with the Yu strain. The remaining steps run singly (with
+ * S_out the last step of a 3D call too, so its last one to four). The result is the same, bit
+ * for bit, as that of nsteps single steps.
  *  S_out        device float[6*N] (D3Q19, D3Q15) / [3*N] (D2Q9) or NULL: the strain (formula
  *               `strain_kind`) of the last step's pre-collision state, i.e. of the state at
  *               level n_end - 1.
